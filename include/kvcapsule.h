@@ -37,10 +37,11 @@
  *    tokens; the same per-layer parameters serve every block and every batch
  *    element), m = ceil((1 - c) n) compressed length for compression ratio c,
  *    t text tokens in the cache.
- *  - The matrix-core (MFMA) kernels cover bf16 with d = 128: compression for n a multiple of 64;
- *    decode for n in {256, 576, 1024}, G in {1, 2, 4, 6, 7, 8} and at most 256 partial results per
- *    (batch element, KV head).  Other shapes, and fp32, run shape-agnostic scalar kernels: same results
- *    within rounding, far lower speed; their decode is limited to n <= 16384 (KVC_ERR_UNSUPPORTED beyond).
+ *  - The matrix-core (MFMA) kernels cover bf16 with d = 128: compression for n >= 8; the first layer of the
+ *    two-layer key reconstructor for m >= 8; decode for n in {256, 576, 1024}, G in {1, 2, 4, 6, 7, 8} and
+ *    at most 256 partial results per (batch element, KV head).  Other shapes, and fp32, run shape-agnostic
+ *    scalar kernels: same results within rounding, far lower speed; their decode is limited to n <= 16384
+ *    (KVC_ERR_UNSUPPORTED beyond).
  */
 #ifndef KVCAPSULE_H
 #define KVCAPSULE_H
@@ -229,7 +230,7 @@ kvc_status kvc_reconstruct_attend_decode_ragged(const kvc_shape *shape, const kv
  * the linear reconstruction).  With KVC_ACT_IDENTITY this is the linear form with theta = W1 W2.
  *  W1 in : [H_kv][m][m] (row j, column r), element type of the shape;  Kc in, H out: [B][H_kv][I][m][d],
  *          different buffers.
- * Runs on a scalar kernel (a one-off step of the prefill).
+ * bf16 with d = 128 and m >= 8 runs on the matrix cores (the kernel of kvc_compress), the rest on a scalar kernel.
  * Errors: NULL pointers, bad shape / activation, Kc == H, misalignment. */
 typedef enum { KVC_ACT_IDENTITY = 0, KVC_ACT_RELU = 1, KVC_ACT_GELU = 2 /* 0.5 x (1 + erf(x / sqrt 2)) */ } kvc_activation;
 kvc_status kvc_mlp_hidden(const kvc_shape *shape, const void *W1, int32_t activation,

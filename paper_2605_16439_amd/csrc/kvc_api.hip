@@ -303,6 +303,7 @@ kvc_status kvc_mlp_hidden(const kvc_shape *shape, const void *W1, int32_t activa
     if (shape->n_images > 0 && (!Kc || !H)) return KVC_ERR_NULL;
     if (Kc == H) return KVC_ERR_SHAPE;                       // every output row reads all input rows
     if (!aligned16(W1) || !aligned16(Kc) || !aligned16(H)) return KVC_ERR_ALIGN;
+    if (fast_mlp_hidden_supported(*shape)) return fast_mlp_hidden(*shape, W1, activation, Kc, H, static_cast<hipStream_t>(stream));
     return generic_mlp_hidden(*shape, W1, activation, Kc, H, static_cast<hipStream_t>(stream));
 }
 

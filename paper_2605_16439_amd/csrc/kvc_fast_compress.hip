@@ -18,6 +18,10 @@
 // the paper's workloads the kernel is bound by what the L2s deliver to the compute units (every
 // workgroup streams its rows of U and its block of V once), not by the matrix cores.
 //
+// The first layer of the two-layer key reconstructor, H = act(W1^T K_tilde) (kvc_mlp_hidden), is the same
+// product with W1 in the place of U and the compressed keys in the place of V, so it runs on the same
+// kernel (FORM 2).
+//
 // Keys (Sec. 3.1, "Selective Retention and Reconstruction for Keys"): every workgroup copies the
 // key rows that the mask selects for its own rows j, 16 bytes per lane, one pass of rows per step
 // of the projection, so the copy (and its writes) overlap the projection instead of preceding it.
@@ -29,6 +33,8 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));     // a 16-byte access at an element-aligned address
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int D = 128;
 constexpr int kKT = 64;        // positions per LDS tile
@@ -44,6 +50,7 @@ struct CPlan {
     int tiles, TPW, JT;         // 16-row tiles of U, tiles per workgroup, workgroups per image block
     int nproj;
     int per_xcd;                // workgroups per XCD when they divide evenly over the 8 XCDs, else 0
+    int act;                    // FORM 2: kvc_activation
     int64_t sb, sh, ss;
 #if defined(KVC_TIMELINE)
     unsigned long long *tl;     // timeline slots, see TSC()
@@ -70,7 +77,37 @@ template <int LD> __device__ inline int sv_index(int c, int p) { return c * LD +
 
 // NW wavefronts, MT tiles per wavefront: a workgroup covers up to 16 NW MT rows of U, so V is read
 // ceil(m / (16 NW MT)) times per image block and every LDS fragment of V feeds MT MFMAs.
-template <int NW, int MT>
+// FORM 0: compress, n a multiple of 64.
+// FORM 1: compress, any n >= 8.  Rows of U start at any 2-byte address and the last tile is partial: a 16-byte
+//         piece that would leave its row is read from the row's last 8 columns instead and shifted into place
+//         with register moves when it is stored to LDS (zeros come in behind it); rows of V past the end repeat
+//         the last one and meet those zeros.
+// FORM 2: first layer of the two-layer key reconstructor, p.n = m.  W1 [m][m] is stored with the contraction
+//         index slow, so its tile is transposed on its way into LDS as V's is; the same treatment of the edges.
+//         The operands of the matrix instruction trade places, so that a lane ends up with four consecutive
+//         channels of one row: the result is row-major.
+// The scalar kernels that FORM 1 and 2 replace run one multiply-add per lane and load; the same two shapes here
+// (n = 729, m = 292, 12 image blocks: 595 -> 13.5 us; m = 410, 128 image blocks, GELU: 1011 -> 23 us) are
+// bound as FORM 0 is, by the latency of a tile step and, when few workgroups are resident, by their number.
+// 16-byte register image of 8 elements, shifted down by `sh` elements (sh >= 8: nothing is left)
+__device__ inline u32x4 drop_elems(u32x4 v, int sh)
+{
+    const int dw = sh >> 1;
+    const uint32_t bits = (sh & 1) * 16u;
+    const uint32_t y0 = dw & 1 ? v.y : v.x, y1 = dw & 1 ? v.z : v.y, y2 = dw & 1 ? v.w : v.z, y3 = dw & 1 ? 0u : v.w;
+    const uint32_t x0 = dw & 2 ? y2 : y0, x1 = dw & 2 ? y3 : y1, x2 = dw & 2 ? 0u : y2, x3 = dw & 2 ? 0u : y3;
+    const uint32_t keep = sh >= 8 ? 0u : 0xffffffffu;
+    return u32x4{__builtin_amdgcn_alignbit(x1, x0, bits) & keep, __builtin_amdgcn_alignbit(x2, x1, bits) & keep,
+                 __builtin_amdgcn_alignbit(x3, x2, bits) & keep, (x3 >> bits) & keep};
+}
+__device__ inline float activate(float x, int act)
+{
+    if (act == 1) return fmaxf(x, 0.f);
+    if (act == 2) return 0.5f * x * (1.f + erff(x * 0.70710678118654752f));     // GELU, erf form
+    return x;
+}
+
+template <int NW, int MT, int FORM>
 __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *__restrict__ K,
                                                        const uint16_t *__restrict__ V,
                                                        const int32_t *__restrict__ idx,
@@ -107,14 +144,70 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
     int j0[MT];
 #pragma unroll
     for (int q = 0; q < MT; ++q) j0[q] = 16 * (tile0 + wave + NW * q);
+    const int NK = (p.n + kKT - 1) / kKT;
     // U loads: item = (row of the workgroup, 16-byte piece of its 64 positions); 2 MT per thread
+    const int ucol = 8 * (threadIdx.x & 7);
     const uint16_t *usrc[2 * MT];
+    if constexpr (FORM != 2) {
 #pragma unroll
-    for (int k = 0; k < 2 * MT; ++k) {
-        const int row = (static_cast<int>(threadIdx.x) + NT * k) >> 3;
-        usrc[k] = U + (static_cast<size_t>(h) * p.m + min(16 * tile0 + row, p.m - 1)) * p.n + 8 * (threadIdx.x & 7);
+        for (int k = 0; k < 2 * MT; ++k) {
+            const int row = (static_cast<int>(threadIdx.x) + NT * k) >> 3;
+            usrc[k] = U + (static_cast<size_t>(h) * p.m + min(16 * tile0 + row, p.m - 1)) * p.n + (FORM == 0 ? ucol : 0);
+        }
     }
-    const int64_t blk = b * p.sb + h * p.sh + (static_cast<int64_t>(p.vis0) + static_cast<int64_t>(i) * p.n) * p.ss;
+    // W1 loads: item q of MT = (pair of rows j, 8 columns r), 2 loads each; 16 lanes take consecutive pieces
+    int wcol[MT], wsh[MT];
+    if constexpr (FORM == 2) {
+#pragma unroll
+        for (int q = 0; q < MT; ++q) {
+            const int pg = (static_cast<int>(threadIdx.x) + NT * q) >> 9;
+            const int c = 16 * tile0 + 8 * ((threadIdx.x & 15) + 16 * pg);
+            wcol[q] = min(c, p.m - 8);
+            wsh[q] = min(c - wcol[q], 8);
+        }
+    }
+    // The load of item k of U (or W1) for tile kt.
+    auto load_u = [&](int kt, int k) -> u32x4 {
+        if constexpr (FORM == 0) {
+            return *reinterpret_cast<const u32x4 *>(usrc[k] + kt * kKT);
+        } else if constexpr (FORM == 1) {
+            return *reinterpret_cast<const u32x4_a2 *>(usrc[k] + min(kt * kKT + ucol, p.n - 8));
+        } else {
+            const int q = k >> 1, pr = ((static_cast<int>(threadIdx.x) + NT * q) >> 4) & 31;
+            const int j = min(kt * kKT + 2 * pr + (k & 1), p.n - 1);
+            return *reinterpret_cast<const u32x4_a2 *>(U + (static_cast<size_t>(h) * p.n + j) * p.m + wcol[q]);
+        }
+    };
+    // Its store piece k of 2 MT into the LDS tile of tile kt.
+    auto store_u = [&](int kt, const u32x4 (&ua)[2 * MT], int k) {
+        uint16_t *ubuf = sU + (kt & 1) * (R * kLD);
+        if constexpr (FORM == 2) {
+            // half k & 1 (channels 4 (k & 1) ... + 3 of the 8) of item k >> 1, rows j, j + 1 in one 32-bit word
+            const int q = k >> 1, idx = static_cast<int>(threadIdx.x) + NT * q;
+            const int pr = (idx >> 4) & 31, r = 8 * ((idx & 15) + 16 * (idx >> 9));
+            const int j = kt * kKT + 2 * pr;
+            const uint32_t ka = j < p.n ? 0xffffffffu : 0u, kc = j + 1 < p.n ? 0xffffffffu : 0u;
+            const u32x4 va = drop_elems(ua[2 * q], wsh[q]), vc = drop_elems(ua[2 * q + 1], wsh[q]);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int i = 2 * (k & 1) + e;
+                const uint32_t a = va[i] & ka, c2 = vc[i] & kc;
+                *reinterpret_cast<uint32_t *>(ubuf + sv_index<kLD>(r + 2 * i, 2 * pr)) = (a & 0xffffu) | (c2 << 16);
+                *reinterpret_cast<uint32_t *>(ubuf + sv_index<kLD>(r + 2 * i + 1, 2 * pr)) = (a >> 16) | (c2 & 0xffff0000u);
+            }
+        } else {
+            const int row = (static_cast<int>(threadIdx.x) + NT * k) >> 3;
+            u32x4 v = ua[k];
+            if constexpr (FORM == 1) {
+                if (kt >= NK - 1) v = drop_elems(v, min(max(kt * kKT + ucol - (p.n - 8), 0), 8));      // registers only
+            }
+            *reinterpret_cast<u32x4 *>(ubuf + row * kLD + ucol) = v;
+        }
+    };
+    // Row of V (or of the compressed keys) at position pp
+    auto v_row = [&](int pp) { return FORM == 0 ? pp : min(pp, p.n - 1); };
+    const int64_t blk = FORM == 2 ? static_cast<int64_t>(u) * p.n * D
+                                  : b * p.sb + h * p.sh + (static_cast<int64_t>(p.vis0) + static_cast<int64_t>(i) * p.n) * p.ss;
     const uint16_t *vsrc = V + blk;
     // V tile loads: item = (pair of positions, 8 channels); 512 items
     const int pair0 = threadIdx.x >> 4, cs = threadIdx.x & 15;      // further items: pair0 + RP q
@@ -135,21 +228,19 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
     // matrix work of the same wave instead of preceding it.  Two register stages rotate by name (the
     // loop is unrolled by two); X holds even tiles, Y odd ones.
     u32x4 vaX[NV][2], uaX[2 * MT], vaY[NV][2], uaY[2 * MT];
-    const int NK = p.n / kKT;
     auto load_tile = [&](int kt, u32x4 (&va)[NV][2], u32x4 (&ua)[2 * MT]) {
 #pragma unroll
         for (int q = 0; q < NV; ++q)
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
-                const int pp = kt * kKT + 2 * (pair0 + RP * q) + e;
+                const int pp = v_row(kt * kKT + 2 * (pair0 + RP * q) + e);
                 va[q][e] = *(reinterpret_cast<const u32x4 *>(vsrc + static_cast<int64_t>(pp) * p.ss) + cs);
             }
 #pragma unroll
-        for (int k = 0; k < 2 * MT; ++k) ua[k] = *reinterpret_cast<const u32x4 *>(usrc[k] + kt * kKT);
+        for (int k = 0; k < 2 * MT; ++k) ua[k] = load_u(kt, k);
     };
     auto store_tile = [&](int kt, const u32x4 (&va)[NV][2], const u32x4 (&ua)[2 * MT]) {
         uint16_t *buf = sVt + (kt & 1) * (D * kLD);
-        uint16_t *ubuf = sU + (kt & 1) * (R * kLD);
         // transposed store: positions (2 pair, 2 pair + 1) of channel c share one 32-bit word
 #pragma unroll
         for (int q = 0; q < NV; ++q) {
@@ -163,10 +254,7 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
             }
         }
 #pragma unroll
-        for (int k = 0; k < 2 * MT; ++k) {
-            const int row = (static_cast<int>(threadIdx.x) + NT * k) >> 3;
-            *reinterpret_cast<u32x4 *>(ubuf + row * kLD + 8 * (threadIdx.x & 7)) = ua[k];
-        }
+        for (int k = 0; k < 2 * MT; ++k) store_u(kt, ua, k);
     };
     // The same work in pieces, for spreading it over the MFMA groups of a step: 4 + 2 MT store pieces
     // (piece e < 4: channels 8 cs + 2 e, 8 cs + 2 e + 1 of the V items; piece 4 + k: row item k of U) and
@@ -174,7 +262,6 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
     constexpr int NP = 4 + 2 * MT, NL = 2 * NV + 2 * MT;
     auto store_piece = [&](int kt, const u32x4 (&va)[NV][2], const u32x4 (&ua)[2 * MT], int i) {
         uint16_t *buf = sVt + (kt & 1) * (D * kLD);
-        uint16_t *ubuf = sU + (kt & 1) * (R * kLD);
         if (i < 4) {
 #pragma unroll
             for (int q = 0; q < NV; ++q) {
@@ -184,19 +271,16 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
                 *reinterpret_cast<uint32_t *>(buf + sv_index<kLD>(8 * cs + 2 * i + 1, pl)) = (a >> 16) | (c2 & 0xffff0000u);
             }
         } else {
-            const int k = i - 4;
-            const int row = (static_cast<int>(threadIdx.x) + NT * k) >> 3;
-            *reinterpret_cast<u32x4 *>(ubuf + row * kLD + 8 * (threadIdx.x & 7)) = ua[k];
+            store_u(kt, ua, i - 4);
         }
     };
     auto load_item = [&](int kt, u32x4 (&va)[NV][2], u32x4 (&ua)[2 * MT], int i) {
         if (i < 2 * NV) {
             const int q = i >> 1, e = i & 1;
-            const int pp = kt * kKT + 2 * (pair0 + RP * q) + e;
+            const int pp = v_row(kt * kKT + 2 * (pair0 + RP * q) + e);
             va[q][e] = *(reinterpret_cast<const u32x4 *>(vsrc + static_cast<int64_t>(pp) * p.ss) + cs);
         } else {
-            const int k = i - 2 * NV;
-            ua[k] = *reinterpret_cast<const u32x4 *>(usrc[k] + kt * kKT);
+            ua[i - 2 * NV] = load_u(kt, i - 2 * NV);
         }
     };
     TSC(0);
@@ -213,10 +297,14 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
     constexpr int P = 4 * MT;
     const int rl = threadIdx.x >> 4;
     const int jlast = min(16 * (tile0 + ntile), p.m) - 1;
+    u32x4 kvrow;
+    if constexpr (FORM != 2) {
     for (int r = threadIdx.x; r < R; r += NT)
         sIdx[r] = min(max(idx[min(16 * tile0 + r, jlast)], 0), p.n - 1);      // an index outside the block must not leave it
-    u32x4 kvrow = *(reinterpret_cast<const u32x4 *>(K + blk + static_cast<int64_t>(min(max(idx[min(16 * tile0 + rl, jlast)], 0), p.n - 1)) * p.ss) + cs);
+    kvrow = *(reinterpret_cast<const u32x4 *>(K + blk + static_cast<int64_t>(min(max(idx[min(16 * tile0 + rl, jlast)], 0), p.n - 1)) * p.ss) + cs);
+    }
     auto keys_tick = [&](int t) {
+        if constexpr (FORM == 2) return;
         const int ps = min(t, P - 1), pl = min(t + 1, P - 1);
         const int j = min(16 * tile0 + RP * ps + rl, jlast);
         *(reinterpret_cast<u32x4 *>(Kc + (static_cast<size_t>(u) * p.m + j) * D) + cs) = kvrow;
@@ -242,6 +330,7 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
     bf16x8 af[2][MT], bq[16];
     auto frag_u = [&](int kt, int ks, int q) {
         const uint16_t *ubuf = sU + (kt & 1) * (R * kLD);
+        if constexpr (FORM == 2) return *reinterpret_cast<const bf16x8 *>(ubuf + sv_index<kLD>(16 * (wave + NW * q) + r16, 32 * ks + 8 * kg));
         return *reinterpret_cast<const bf16x8 *>(ubuf + (16 * (wave + NW * q) + r16) * kLD + 32 * ks + 8 * kg);
     };
     auto frag_v = [&](int kt, int f) {       // fragment f = 8 ks + nt
@@ -270,8 +359,9 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int q = 0; q < MT; ++q)
-                acc[q][f & 7] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[f >> 3][q], bq[f], acc[q][f & 7], 0, 0, 0);
-            if ((f & 7) == 7) {
+                acc[q][f & 7] = FORM == 2 ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(bq[f], af[f >> 3][q], acc[q][f & 7], 0, 0, 0)
+                                          : __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[f >> 3][q], bq[f], acc[q][f & 7], 0, 0, 0);
+            if (FORM != 2 && (f & 7) == 7) {
 #pragma unroll
                 for (int q = 0; q < MT; ++q)
                     accs[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[f >> 3][q], ones, accs[q], 0, 0, 0);
@@ -294,7 +384,7 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
     load_tile(min(2, NK - 1), vaX, uaX);
     uint16_t mur[8];                                     // the channel means the epilogue needs, requested early
 #pragma unroll
-    for (int nt = 0; nt < 8; ++nt) mur[nt] = mu[static_cast<size_t>(h) * D + 16 * nt + r16];
+    for (int nt = 0; nt < 8; ++nt) mur[nt] = FORM == 2 ? 0 : mu[static_cast<size_t>(h) * D + 16 * nt + r16];
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     first_fragments(0);
 #pragma unroll
@@ -310,7 +400,26 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
         ++kt;
     }
     TSC(4);
-    for (; kt < P; ++kt) keys_tick(kt);                  // passes a short block left over
+    if constexpr (FORM != 2)
+        for (; kt < P; ++kt) keys_tick(kt);              // passes a short block left over
+
+    if constexpr (FORM == 2) {
+        // row j0 + r16, channels 16 nt + 4 kg ... + 3
+#pragma unroll
+        for (int q = 0; q < MT; ++q) {
+            const int r = j0[q] + r16;
+            if (wave + NW * q >= ntile || r >= p.m) continue;
+            uint16_t *hout = Kc + (static_cast<size_t>(u) * p.m + r) * D + 4 * kg;
+#pragma unroll
+            for (int nt = 0; nt < 8; ++nt) {
+                uint32_t o[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = f32_to_bf16_bits(activate(acc[q][nt][e], p.act));
+                *reinterpret_cast<u32x2 *>(hout + 16 * nt) = u32x2{o[0] | (o[1] << 16), o[2] | (o[3] << 16)};
+            }
+        }
+        return;
+    }
 
     // ---- epilogue: centre, round once, store in the blocked layout -----------------------------------
     // lane holds rows j = j0 + 4 kg + e (e = 0..3) of channel c = 16 nt + r16; accs[e] = sum_p U[j][p]
@@ -341,16 +450,15 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
     TSC(5);
 }
 
-template <int NW, int MT> bool launch(const CPlan &p, const CompressCall &c)
+template <int NW, int MT, int FORM>
+bool launch(const CPlan &p, const uint16_t *K, const uint16_t *V, const int32_t *idx, const uint16_t *U, const uint16_t *mu,
+            uint16_t *Kc, uint16_t *Vc, hipStream_t stream)
 {
     static_assert(16 * NW * MT <= kMaxRows, "rows of U per workgroup");
     const size_t lds = static_cast<size_t>(2) * (D + 16 * NW * MT) * ld_of(16 * NW * MT) * sizeof(uint16_t);
     static bool attr_set[kMaxDevices] = {};
-    if (!allow_lds(reinterpret_cast<const void *>(fk_compress<NW, MT>), lds, attr_set)) return false;
-    fk_compress<NW, MT><<<p.nproj, 64 * NW, lds, c.stream>>>(
-        p, static_cast<const uint16_t *>(c.K), static_cast<const uint16_t *>(c.V), c.key_idx,
-        static_cast<const uint16_t *>(c.U), static_cast<const uint16_t *>(c.mu),
-        static_cast<uint16_t *>(c.Kc), static_cast<uint16_t *>(c.Vc));
+    if (!allow_lds(reinterpret_cast<const void *>(fk_compress<NW, MT, FORM>), lds, attr_set)) return false;
+    fk_compress<NW, MT, FORM><<<p.nproj, 64 * NW, lds, stream>>>(p, K, V, idx, U, mu, Kc, Vc);
     return true;
 }
 
@@ -379,9 +487,50 @@ void fast_compress_knobs(int nw, int jt)
     if (jt >= 0) g_force_jt = jt;
 }
 
+// How the 16-row tiles of U are shared out: JT workgroups per image block, at most 16 tiles each.  A
+// workgroup's time has a part that does not depend on its share (it streams the whole block of V) and a part
+// that grows with it, about 20 : 1 per tile on MI355X; JT minimises rounds of resident workgroups (one per
+// compute unit) times that cost, which at the paper's shapes is the smallest JT the kernel supports.
+static void share_tiles(CPlan &p)
+{
+    p.tiles = (p.m + 15) / 16;
+    const int units = p.B * p.Hkv * p.I;
+    const int max_tpw = kMaxRows / 16;
+    const int cus = device_cus();
+    const int jt_min = (p.tiles + max_tpw - 1) / max_tpw, jt_max = (p.tiles + 3) / 4;
+    long best = -1;
+    for (int jt = jt_min; jt <= jt_max; ++jt) {
+        const int tpw = (p.tiles + jt - 1) / jt;
+        const long rounds = (static_cast<long>(units) * jt + cus - 1) / cus;
+        const long cost = rounds * (20 + tpw);
+        if (best < 0 || cost < best) { best = cost; p.JT = jt; }
+    }
+    if (g_force_jt > 0) p.JT = std::min(std::max(g_force_jt, jt_min), p.tiles);
+    p.TPW = (p.tiles + p.JT - 1) / p.JT;
+    p.nproj = units * p.JT;
+    p.per_xcd = p.nproj % 8 == 0 ? p.nproj / 8 : 0;
+}
+
+template <int FORM> static bool launch_compress(const CPlan &p, const CompressCall &c)
+{
+    const uint16_t *K = static_cast<const uint16_t *>(c.K), *V = static_cast<const uint16_t *>(c.V);
+    const uint16_t *U = static_cast<const uint16_t *>(c.U), *mu = static_cast<const uint16_t *>(c.mu);
+    uint16_t *Kc = static_cast<uint16_t *>(c.Kc), *Vc = static_cast<uint16_t *>(c.Vc);
+    const int nw = g_force_nw == 4 || g_force_nw == 8 ? g_force_nw : (p.TPW > 4 ? 8 : 4);
+    if (nw == 8)
+        return p.TPW > 8 ? launch<8, 2, FORM>(p, K, V, c.key_idx, U, mu, Kc, Vc, c.stream)
+                         : launch<8, 1, FORM>(p, K, V, c.key_idx, U, mu, Kc, Vc, c.stream);
+    switch ((p.TPW + 3) / 4) {
+    case 1: return launch<4, 1, FORM>(p, K, V, c.key_idx, U, mu, Kc, Vc, c.stream);
+    case 2: return launch<4, 2, FORM>(p, K, V, c.key_idx, U, mu, Kc, Vc, c.stream);
+    case 3: return launch<4, 3, FORM>(p, K, V, c.key_idx, U, mu, Kc, Vc, c.stream);
+    default: return launch<4, 4, FORM>(p, K, V, c.key_idx, U, mu, Kc, Vc, c.stream);
+    }
+}
+
 bool fast_compress_supported(const kvc_shape &s)
 {
-    return s.dtype == KVC_BF16 && s.head_dim == D && s.n_img_tokens % kKT == 0;
+    return s.dtype == KVC_BF16 && s.head_dim == D && s.n_img_tokens >= 8;      // a 16-byte piece of a row of U
 }
 
 size_t fast_compress_ws_bytes(const kvc_shape &) { return 0; }
@@ -393,47 +542,35 @@ kvc_status fast_compress(const CompressCall &c)
     CPlan p;
     p.B = s.batch; p.Hkv = s.n_kv_heads; p.n = s.n_img_tokens; p.I = s.n_images; p.m = s.m;
     p.vis0 = c.vis_start;
-    // The 16-row tiles of U are shared out evenly over JT workgroups per image block, at most 16 per
-    // workgroup.  A workgroup's time has a part that does not depend on its share (it streams the
-    // whole block of V) and a part that grows with it, about 20 : 1 per tile on MI355X; JT minimises
-    // rounds of resident workgroups (one per compute unit) times that cost, which at the paper's shapes
-    // is the smallest JT the kernel supports.
-    p.tiles = (s.m + 15) / 16;
-    const int units = p.B * p.Hkv * p.I;
-    const int max_tpw = kMaxRows / 16;
-    {
-        const int cus = device_cus();
-        const int jt_min = (p.tiles + max_tpw - 1) / max_tpw, jt_max = (p.tiles + 3) / 4;
-        long best = -1;
-        for (int jt = jt_min; jt <= jt_max; ++jt) {
-            const int tpw = (p.tiles + jt - 1) / jt;
-            const long rounds = (static_cast<long>(units) * jt + cus - 1) / cus;
-            const long cost = rounds * (20 + tpw);
-            if (best < 0 || cost < best) { best = cost; p.JT = jt; }
-        }
-        if (g_force_jt > 0) p.JT = std::min(std::max(g_force_jt, jt_min), p.tiles);
-    }
-    p.TPW = (p.tiles + p.JT - 1) / p.JT;
-    p.nproj = units * p.JT;
-    p.per_xcd = p.nproj % 8 == 0 ? p.nproj / 8 : 0;
+    p.act = 0;
+    share_tiles(p);
     p.sb = c.stride_b; p.sh = c.stride_h; p.ss = c.stride_s;
 #if defined(KVC_TIMELINE)
     p.tl = (c.ws && c.ws_bytes >= (2u << 20))
                ? reinterpret_cast<unsigned long long *>((reinterpret_cast<uintptr_t>(c.ws) + c.ws_bytes - (1u << 20)) & ~uintptr_t(7))
                : nullptr;
 #endif
-    const int nw = g_force_nw == 4 || g_force_nw == 8 ? g_force_nw : (p.TPW > 4 ? 8 : 4);
-    bool ok;
-    if (nw == 8) {
-        ok = p.TPW > 8 ? launch<8, 2>(p, c) : launch<8, 1>(p, c);
-    } else {
-        switch ((p.TPW + 3) / 4) {
-        case 1: ok = launch<4, 1>(p, c); break;
-        case 2: ok = launch<4, 2>(p, c); break;
-        case 3: ok = launch<4, 3>(p, c); break;
-        default: ok = launch<4, 4>(p, c); break;
-        }
-    }
+    const bool ok = p.n % kKT == 0 ? launch_compress<0>(p, c) : launch_compress<1>(p, c);
+    return ok && hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_HIP;
+}
+
+bool fast_mlp_hidden_supported(const kvc_shape &s) { return s.dtype == KVC_BF16 && s.head_dim == D && s.m >= 8; }
+
+kvc_status fast_mlp_hidden(const kvc_shape &s, const void *W1, int act, const void *Kc, void *H, hipStream_t stream)
+{
+    if (s.n_images == 0) return KVC_OK;
+    CPlan p;
+    p.B = s.batch; p.Hkv = s.n_kv_heads; p.n = s.m; p.I = s.n_images; p.m = s.m;
+    p.vis0 = 0; p.sb = p.sh = 0; p.ss = D;
+    p.act = act;
+    share_tiles(p);
+#if defined(KVC_TIMELINE)
+    p.tl = nullptr;
+#endif
+    const uint16_t *k = static_cast<const uint16_t *>(Kc), *w = static_cast<const uint16_t *>(W1);
+    uint16_t *out = static_cast<uint16_t *>(H);
+    const bool ok = p.TPW > 8 ? launch<8, 2, 2>(p, nullptr, k, nullptr, w, nullptr, out, nullptr, stream)
+                              : launch<8, 1, 2>(p, nullptr, k, nullptr, w, nullptr, out, nullptr, stream);
     return ok && hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_HIP;
 }
 

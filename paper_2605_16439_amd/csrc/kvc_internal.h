@@ -161,6 +161,9 @@ void full_decode_set_chunk_steps(int steps);
 bool fast_compress_supported(const kvc_shape &s);
 size_t fast_compress_ws_bytes(const kvc_shape &s);
 kvc_status fast_compress(const CompressCall &c);
+// first layer of the two-layer key reconstructor on the same kernel
+bool fast_mlp_hidden_supported(const kvc_shape &s);
+kvc_status fast_mlp_hidden(const kvc_shape &s, const void *W1, int act, const void *Kc, void *H, hipStream_t stream);
 void fast_compress_knobs(int waves, int jt);
 
 }  // namespace kvc
