@@ -241,7 +241,8 @@ kvc_status kvc_mlp_hidden(const kvc_shape *shape, const void *W1, int32_t activa
  * the I*m compressed rows of each (batch element, KV head) and the text rows,
  *     out[b,g,:] = softmax(scale * q[b,g] . [Kc[b,g/G] ; K_text]^T) [Vc[b,g/G] ; V_text],
  * no theta, no U^T, no mu.  Arguments as in kvc_reconstruct_attend_decode (Vc in its blocked layout;
- * shape->n_img_tokens is not used).  Runs on the shape-agnostic scalar kernels. */
+ * shape->n_img_tokens is not used).  bf16 with d = 128 and G <= 16 runs on the matrix cores (weights kept at
+ * float32 precision), the rest on the shape-agnostic scalar kernels. */
 kvc_status kvc_static_attend_decode(const kvc_shape *shape, const void *q, const void *Kc, const void *Vc,
                                     void *K_text, void *V_text, int32_t text_len, int32_t text_cap,
                                     const void *k_new, const void *v_new, float softmax_scale,

@@ -178,6 +178,7 @@ size_t kvc_workspace_bytes(const kvc_shape *shape, int32_t max_text_len)
         if (f > need) need = f;
     }
     need = std::max(need, stream_decode_ws_bytes(*shape, max_text_len));
+    if (fast_static_supported(*shape)) need = std::max(need, fast_static_ws_bytes(*shape));
     return need;
 }
 
@@ -290,7 +291,7 @@ kvc_status kvc_static_attend_decode(const kvc_shape *shape, const void *q, const
                                    softmax_scale, out, lse_out, workspace, workspace_bytes, stream);
     if (st != KVC_OK) return st;
     c.static_variant = true;
-    return generic_decode(c);
+    return fast_static_supported(c.s) ? fast_static_decode(c) : generic_decode(c);
 }
 
 kvc_status kvc_mlp_hidden(const kvc_shape *shape, const void *W1, int32_t activation, const void *Kc, void *H,

@@ -134,6 +134,16 @@ __device__ inline float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff000
 // spread over the banks and the operand reads of one tile stay conflict-free
 __device__ inline int vt_index(int c, int x) { return c * kLDV + ((((x >> 3) ^ (c >> 4)) & (kXC / 8 - 1)) << 3) + (x & 7); }
 
+// 128-bit right shift by ds dwords and bs bits (registers only; identity for ds = bs = 0)
+__device__ __forceinline__ u32x4 shift_window(u32x4 wv, int ds, uint32_t bs)
+{
+    const bool d1 = ds & 1, d2 = ds & 2;
+    const uint32_t y0 = d1 ? wv.y : wv.x, y1 = d1 ? wv.z : wv.y, y2 = d1 ? wv.w : wv.z, y3 = d1 ? 0u : wv.w;
+    const uint32_t x0 = d2 ? y2 : y0, x1 = d2 ? y3 : y1, x2 = d2 ? 0u : y2, x3 = d2 ? 0u : y3;
+    return u32x4_mk(__builtin_amdgcn_alignbit(x1, x0, bs), __builtin_amdgcn_alignbit(x2, x1, bs),
+                    __builtin_amdgcn_alignbit(x3, x2, bs), x3 >> bs);
+}
+
 // first query row of image block ub (b*I + i) of a KV head
 __host__ __device__ inline int unit_row(int ub, int UPBs, int G) { return ((ub >> UPBs) << 6) + (ub & ((1 << UPBs) - 1)) * G; }
 // rows of a 64-row block beyond its image blocks, and rows beyond the last image block, hold nothing

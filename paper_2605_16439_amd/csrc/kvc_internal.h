@@ -158,6 +158,10 @@ bool fast_full_supported(int dtype, int head_dim, int G);
 size_t fast_full_ws_bytes(int B, int Hq, int Hkv);
 kvc_status fast_full_decode(const FullCall &c);
 void full_decode_set_chunk_steps(int steps);
+// static variant (attention over the compressed rows themselves), bf16, head_dim 128
+bool fast_static_supported(const kvc_shape &s);
+size_t fast_static_ws_bytes(const kvc_shape &s);
+kvc_status fast_static_decode(const DecodeCall &c);
 bool fast_compress_supported(const kvc_shape &s);
 size_t fast_compress_ws_bytes(const kvc_shape &s);
 kvc_status fast_compress(const CompressCall &c);

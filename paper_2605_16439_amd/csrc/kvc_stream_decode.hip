@@ -84,16 +84,6 @@ __device__ __forceinline__ LastStep last_step(int rows, int X, int x, int kg, in
     r.bs = mine ? (sh & 2) * 8u : 0u;
     return r;
 }
-// 128-bit right shift by ds dwords and bs bits (registers only; identity for ds = bs = 0)
-__device__ __forceinline__ u32x4 shift_window(u32x4 wv, int ds, uint32_t bs)
-{
-    const bool d1 = ds & 1, d2 = ds & 2;
-    const uint32_t y0 = d1 ? wv.y : wv.x, y1 = d1 ? wv.z : wv.y, y2 = d1 ? wv.w : wv.z, y3 = d1 ? 0u : wv.w;
-    const uint32_t x0 = d2 ? y2 : y0, x1 = d2 ? y3 : y1, x2 = d2 ? 0u : y2, x3 = d2 ? 0u : y3;
-    return u32x4_mk(__builtin_amdgcn_alignbit(x1, x0, bs), __builtin_amdgcn_alignbit(x2, x1, bs),
-                    __builtin_amdgcn_alignbit(x3, x2, bs), x3 >> bs);
-}
-
 constexpr size_t stream_lds_bytes(int KS, int PS)
 {
     return static_cast<size_t>(2 * 16 * (32 * KS + 16) + 16 * (PS + 16)) * 2 +

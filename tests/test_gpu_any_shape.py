@@ -52,3 +52,37 @@ def test_hidden_rows_any_length(m, act):
     kv.kvc_mlp_hidden(kv.make_shape(B, 4, hkv, 128, 1024, I, m, torch.bfloat16), W1.to(DEV), act, Kc.to(DEV), H)
     torch.cuda.synchronize()
     assert block_rel_err(f64(H), orc.mlp_hidden(f64(Kc), f64(W1), act, orc.STORE_BF16)) <= ONE_ROUNDING
+
+
+# Attention results whose scores, weights and sums are float32 differ from the exact result by the rounding of the
+# output alone: at most half a bf16 step, 2^-9 of the value, so 2^-9 of a row's norm; float32 adds about 1e-5.
+OUT_ROUNDING = 2.0 ** -9 + 1e-4
+
+
+def check_rows(out, ref):
+    assert np.all(np.isfinite(out))
+    e = np.linalg.norm(out - ref, axis=-1) / np.maximum(np.linalg.norm(ref, axis=-1), 1e-30)
+    print(f"[any]   row rel err {e.max():.3e}", flush=True)
+    assert e.max() <= OUT_ROUNDING
+
+
+# m around the 8-row block and the 32-row step (record shorter than a block included), text around the 128-row
+# workgroup step, runs of several steps, every kind of group size, no image, no text
+@pytest.mark.parametrize("hq,hkv,I,m,t", [(4, 4, 1, 1, 0), (7, 1, 2, 7, 1), (6, 2, 3, 8, 127), (24, 2, 1, 31, 128), (16, 1, 3, 33, 129),
+                                          (14, 2, 5, 41, 300), (8, 8, 70, 64, 5), (2, 2, 0, 20, 260), (28, 4, 64, 103, 40)])
+def test_static_variant_any_shape(hq, hkv, I, m, t):
+    w = wl(128, I, B=2, hq=hq, hkv=hkv, t=t)
+    L = Layer(w, m)
+    g = torch.Generator().manual_seed(m)
+    L.gKc = torch.randn(L.gKc.shape, generator=g).to(torch.bfloat16).to(DEV)
+    L.gVc = torch.randn(L.gVc.shape, generator=g).to(torch.bfloat16).to(DEV)
+    q, kn, vn = synth.make_step_inputs(w, 0, 0)
+    print(f"[any] static hq={hq} hkv={hkv} I={I} m={m} t={t}", flush=True)
+    kv.kvc_static_attend_decode(L.shape, q.to(DEV), L.gKc, L.gVc, L.gKt, L.gVt, t, w.text_cap, kn.to(DEV), vn.to(DEV), 0.0, L.out,
+                                L.lse, L.ws)
+    torch.cuda.synchronize()
+    Kt, Vt = f64(L.Kt).copy(), f64(L.Vt).copy()
+    ref, lref = orc.static_attend_decode(f64(q), f64(L.gKc), unpack_vc(L.gVc, m, 128), Kt, Vt, t, f64(kn), f64(vn))
+    check_rows(f64(L.out), ref)
+    assert np.abs(f64(L.lse) - lref).max() <= 1e-4
+    assert np.array_equal(f64(L.gKt), Kt) and np.array_equal(f64(L.gVt), Vt)
