@@ -38,10 +38,11 @@
  *    element), m = ceil((1 - c) n) compressed length for compression ratio c,
  *    t text tokens in the cache.
  *  - The matrix-core (MFMA) kernels cover bf16 with d = 128: compression for n >= 8; the first layer of the
- *    two-layer key reconstructor for m >= 8; decode for n in {256, 576, 1024}, G in {1, 2, 4, 6, 7, 8} and
- *    at most 256 partial results per (batch element, KV head).  Other shapes, and fp32, run shape-agnostic
- *    scalar kernels: same results within rounding, far lower speed; their decode is limited to n <= 16384
- *    (KVC_ERR_UNSUPPORTED beyond).
+ *    two-layer key reconstructor for m >= 8; decode for n >= 8 and G <= 16.  Decode kernels tuned further, with
+ *    scores and weights rounded to bf16 between the steps, serve n in {256, 576, 1024}, G in {1, 2, 4, 6, 7, 8}
+ *    and at most 256 partial results per (batch element, KV head); every other decode keeps them at float32
+ *    precision.  Other shapes, and fp32, run shape-agnostic scalar kernels: same results within rounding, far
+ *    lower speed; their decode is limited to n <= 16384 (KVC_ERR_UNSUPPORTED beyond).
  */
 #ifndef KVCAPSULE_H
 #define KVCAPSULE_H

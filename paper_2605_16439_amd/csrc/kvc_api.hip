@@ -136,7 +136,15 @@ kvc_status dispatch_decode(const DecodeCall &c)
     kvc_status st = KVC_OK;
     if (stream_decode(c, &st)) return st;
     if (fast_decode_supported(c.s)) return fast_decode(c);
-    return generic_decode(c);
+    return other_decode(c);
+}
+
+// scratch without which no kernel serves the shape (kvc_workspace_bytes also covers kernels that have a fallback)
+size_t least_decode_ws_bytes(const kvc_shape &s, int32_t max_text)
+{
+    size_t need = generic_decode_ws_bytes(s, max_text);
+    if (fast_decode_supported(s)) need = std::max(need, fast_decode_ws_bytes(s, max_text));
+    return std::max(need, stream_decode_ws_bytes(s, max_text));
 }
 
 template <class T>
@@ -151,6 +159,14 @@ __global__ __launch_bounds__(256) void unpack_values(const T *__restrict__ Vc, T
 }
 
 }  // namespace
+
+namespace kvc {
+kvc_status other_decode(const DecodeCall &c)
+{
+    kvc_status st = KVC_OK;
+    return any_decode(c, &st) ? st : generic_decode(c);
+}
+}  // namespace kvc
 
 extern "C" {
 
@@ -168,16 +184,12 @@ int32_t kvc_compressed_len(int32_t n, double compression_ratio)
 size_t kvc_workspace_bytes(const kvc_shape *shape, int32_t max_text_len)
 {
     if (check_shape(shape) != KVC_OK || max_text_len < 0) return 0;
-    size_t need = generic_decode_ws_bytes(*shape, max_text_len);
-    if (fast_decode_supported(*shape)) {
-        size_t f = fast_decode_ws_bytes(*shape, max_text_len);
-        if (f > need) need = f;
-    }
+    size_t need = least_decode_ws_bytes(*shape, max_text_len);
     if (fast_compress_supported(*shape)) {
         size_t f = fast_compress_ws_bytes(*shape);
         if (f > need) need = f;
     }
-    need = std::max(need, stream_decode_ws_bytes(*shape, max_text_len));
+    if (any_decode_supported(*shape)) need = std::max(need, any_decode_ws_bytes(*shape, max_text_len));
     if (fast_static_supported(*shape)) need = std::max(need, fast_static_ws_bytes(*shape));
     return need;
 }
@@ -395,7 +407,7 @@ kvc_status kvc_reconstruct_attend_decode_static(const kvc_shape *shape, const kv
                                    k_new, v_new, softmax_scale, out, lse_out,
                                    reinterpret_cast<void *>(static_cast<uintptr_t>(256)), kStaticScratchBytes, stream);
     if (st != KVC_OK) return st;
-    if (kvc_workspace_bytes(shape, text_cap) > kStaticScratchBytes) return KVC_ERR_WORKSPACE;
+    if (least_decode_ws_bytes(*shape, text_cap) > kStaticScratchBytes) return KVC_ERR_WORKSPACE;
     c.ws = static_scratch_ptr();
     if (!c.ws) return KVC_ERR_HIP;
     return dispatch_decode(c);

@@ -1415,7 +1415,7 @@ size_t fast_decode_ws_bytes(const kvc_shape &s, int32_t max_text)
 kvc_status fast_decode(const DecodeCall &c)
 {
     Plan p = make_plan(c.s, c.t, c.t_in, c.cap, c.scale, c.ws);
-    if (p.nparts > kMaxParts) return generic_decode(c);
+    if (p.nparts > kMaxParts) return other_decode(c);
     // quot(): every dividend is a workgroup, tile or image-block index, every divisor one of these
     {
         const long args[] = {static_cast<long>(p.nvis_a) * 4 * kTPW, static_cast<long>(p.B) * p.Hkv * p.NXC, p.nvis_b, p.nvis_c,
@@ -1424,7 +1424,7 @@ kvc_status fast_decode(const DecodeCall &c)
         long amax = 0, dmax = 1;
         for (long a : args) amax = a > amax ? a : amax;
         for (int d : divs) dmax = d > dmax ? d : dmax;
-        if (amax * dmax >= (1ll << 32)) return generic_decode(c);
+        if (amax * dmax >= (1ll << 32)) return other_decode(c);
     }
     if (p.bytes > c.ws_bytes) return KVC_ERR_WORKSPACE;
     if (c.n_images_dev && c.text_len_dev) { p.n_img = c.n_images_dev; p.tlen = c.text_len_dev; }

@@ -158,6 +158,12 @@ bool fast_full_supported(int dtype, int head_dim, int G);
 size_t fast_full_ws_bytes(int B, int Hq, int Hkv);
 kvc_status fast_full_decode(const FullCall &c);
 void full_decode_set_chunk_steps(int steps);
+// decode for the shapes the tuned kernels are not compiled for, bf16, head_dim 128: true when the call was taken
+bool any_decode_supported(const kvc_shape &s);
+size_t any_decode_ws_bytes(const kvc_shape &s, int32_t max_text);
+bool any_decode(const DecodeCall &c, kvc_status *st);
+// that, or the scalar kernels
+kvc_status other_decode(const DecodeCall &c);
 // static variant (attention over the compressed rows themselves), bf16, head_dim 128
 bool fast_static_supported(const kvc_shape &s);
 size_t fast_static_ws_bytes(const kvc_shape &s);

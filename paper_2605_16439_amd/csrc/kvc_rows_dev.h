@@ -1,0 +1,228 @@
+// Device code shared by the decode kernels that keep scores and weights at float32 precision
+// (kvc_static_decode.hip, kvc_any_decode.hip): a float as three bf16 terms, and one wavefront's pass over rows
+// that are attended as they are -- compressed rows or rows of the text cache.
+#pragma once
+#include "kvc_decode_dev.h"
+
+namespace kvc {
+namespace rows {
+
+using namespace dd;
+
+constexpr int kSW = 4;                // wavefronts
+constexpr int kSR = 32;               // rows per wavefront and step
+constexpr int kLDX = 24;              // 32-bit words per channel of the transposed value tile (16 row pairs; 96 bytes: no bank conflicts)
+constexpr int kLDO = D + 4;           // floats per head row of a wavefront's output in LDS
+
+// what walk() needs to know of a sequence's rows
+struct Rows {
+    int I, m, KS, SV;                 // compressed rows: blocks of m rows, KS 32-row steps each, SV = I KS steps
+    int t;                            // rows of the text cache
+    int cs;                           // steps per wavefront and run
+    unsigned qKS;
+    float scale;
+};
+
+// p = p1 + p2 + p3, each a bf16: the high parts are exact remainders
+struct Split3 {
+    bf16x8 a, b, c;
+};
+__device__ __forceinline__ Split3 split3(const float (&p)[8])
+{
+    uint32_t w[3][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float x0 = p[2 * i], x1 = p[2 * i + 1];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const uint32_t h0 = f32_to_bf16_bits(x0), h1 = f32_to_bf16_bits(x1);
+            w[k][i] = h0 | (h1 << 16);
+            x0 -= __uint_as_float(h0 << 16);
+            x1 -= __uint_as_float(h1 << 16);
+        }
+    }
+    Split3 r;
+    r.a = as_bf16x8(u32x4_mk(w[0][0], w[0][1], w[0][2], w[0][3]));
+    r.b = as_bf16x8(u32x4_mk(w[1][0], w[1][1], w[1][2], w[1][3]));
+    r.c = as_bf16x8(u32x4_mk(w[2][0], w[2][1], w[2][2], w[2][3]));
+    return r;
+}
+
+// One wavefront's pass over its steps of a run.  TEXT: rows of the text cache, else compressed rows.
+template <bool TEXT>
+__device__ __forceinline__ void walk(const Rows &p, const uint16_t *__restrict__ Kb, const uint16_t *__restrict__ Vb,
+                                     const uint16_t *__restrict__ kn, const uint16_t *__restrict__ vn, int t_new,
+                                     const u32x4 (&qf)[4], int s0, uint32_t *vt, float &m_run, float &l_run, f32x4 (&acc)[8])
+{
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int r16 = lane & 15, kg = lane >> 4;
+    const int nfull = p.m >> 3, wt = p.m & 7;
+    // key rows of a tile are permuted (see the top of the file)
+    const int krow = 8 * (r16 >> 2) + (r16 & 3);
+
+    // step s: first row, and how many rows from there on exist (at most 32 count)
+    auto rows_of = [&](int s, int &base, int &left, int &i, int &ks) {
+        if constexpr (TEXT) {
+            i = 0; ks = s;
+            base = kSR * s; left = p.t - base;
+        } else {
+            const int sc = min(s, p.SV - 1);
+            i = quot(sc, p.qKS); ks = sc - i * p.KS;
+            base = i * p.m + kSR * ks; left = s < p.SV ? p.m - kSR * ks : 0;
+        }
+    };
+    // loads of step s; a step past the end reads valid rows again and is masked
+    auto load = [&](int s, u32x4 (&kf)[2][4], u32x4 (&vf)[8]) {
+        int base, left, i, ks;
+        rows_of(s, base, left, i, ks);
+        const int last = TEXT ? max(p.t - 1, 0) : (i + 1) * p.m - 1;
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt) {
+            const int x = min(base + krow + 4 * tt, last);
+            const u32x4 *kp = reinterpret_cast<const u32x4 *>((TEXT && x == t_new) ? kn : Kb + static_cast<size_t>(x) * D) + kg;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) kf[tt][k] = kp[4 * k];
+        }
+        if constexpr (TEXT) {
+            // rows base + 2 (kg + 4 k) + e, 16 lanes per row
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const int x = min(base + 2 * (kg + 4 * k) + e, last);
+                    vf[2 * k + e] = *(reinterpret_cast<const u32x4 *>(x == t_new ? vn : Vb + static_cast<size_t>(x) * D) + r16);
+                }
+        } else {
+            // 8-row block 4 ks + kg of the record; the record's shorter last block [D][wt] is read as a dword-aligned
+            // window around the lane's values (shifted into place in compute()), a block past it reads a valid one
+            const char *rec = reinterpret_cast<const char *>(Vb + static_cast<size_t>(i) * p.m * D);
+            const int jb = 4 * ks + kg;
+            const bool tail = wt != 0 && jb == nfull;
+            const uint32_t full = static_cast<uint32_t>(max(min(jb, nfull - 1), 0) * (8 * D * 2));
+#pragma unroll
+            for (int ct = 0; ct < 8; ++ct) {
+                const int c = 16 * ct + r16;
+                const uint32_t a0 = static_cast<uint32_t>(max(min(c * 2 * wt & ~3, D * 2 * wt - 16), 0));
+                const uint32_t off = tail ? static_cast<uint32_t>(nfull * 8 * D * 2) + a0 : nfull ? full + c * 16 : 0u;
+                vf[ct] = *reinterpret_cast<const u32x4_a4 *>(rec + off);
+            }
+        }
+    };
+    auto compute = [&](int s, const u32x4 (&kf)[2][4], const u32x4 (&vf)[8]) {
+        int base, left, i, ks;
+        rows_of(s, base, left, i, ks);
+        if constexpr (TEXT) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t a = vf[2 * k][j], c2 = vf[2 * k + 1][j];
+                    vt[(8 * r16 + 2 * j) * kLDX + kg + 4 * k] = (a & 0xffffu) | (c2 << 16);
+                    vt[(8 * r16 + 2 * j + 1) * kLDX + kg + 4 * k] = (a >> 16) | (c2 & 0xffff0000u);
+                }
+        }
+        // logits of rows base + 8 kg + 4 tt + e for head r16
+        float sc[8];
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt) {
+            f32x4 a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kf[tt][k]), as_bf16x8(qf[k]), a, 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sc[4 * tt + e] = 8 * kg + 4 * tt + e < left ? a[e] * p.scale : -INFINITY;
+        }
+        float mx = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])), fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float m_new = fmaxf(m_run, mx);
+        const float mref = m_new == -INFINITY ? 0.f : m_new;     // nothing valid so far: exp(-inf - 0) = 0
+        const float alpha = __expf(m_run - mref);
+        m_run = m_new;
+        float pr[8], ls = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            pr[e] = __expf(sc[e] - mref);
+            ls += pr[e];
+        }
+        l_run = l_run * alpha + ls;
+        const Split3 pf = split3(pr);
+        if constexpr (TEXT) {
+            // the wavefront reads back what its own lanes stored: LDS works through its requests in order
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_wave_barrier();
+        }
+        const bool tail = !TEXT && wt != 0 && 4 * ks + kg == nfull;
+#pragma unroll
+        for (int ct = 0; ct < 8; ++ct) {
+            u32x4 v;
+            if constexpr (TEXT) {
+                v = *reinterpret_cast<const u32x4 *>(vt + (16 * ct + r16) * kLDX + 4 * kg);
+            } else {
+                v = vf[ct];
+                if (wt != 0 && ks == p.KS - 1) {                 // uniform, registers only
+                    const int to = (16 * ct + r16) * 2 * wt, sh = tail ? to - max(min(to & ~3, D * 2 * wt - 16), 0) : 0;
+                    v = shift_window(v, sh >> 2, (sh & 2) * 8u);
+                }
+            }
+            f32x4 o = acc[ct];
+            o[0] *= alpha; o[1] *= alpha; o[2] *= alpha; o[3] *= alpha;
+            o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(v), pf.c, o, 0, 0, 0);
+            o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(v), pf.b, o, 0, 0, 0);
+            acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(v), pf.a, o, 0, 0, 0);
+        }
+        if constexpr (TEXT) __builtin_amdgcn_wave_barrier();
+    };
+
+    u32x4 kA[2][4], vA[8], kB[2][4], vB[8];
+    load(s0 + wave, kA, vA);
+    for (int it = 0; it < p.cs; it += 2) {
+        load(s0 + wave + kSW * (it + 1), kB, vB);
+        compute(s0 + wave + kSW * it, kA, vA);
+        if (it + 1 >= p.cs) break;
+        load(s0 + wave + kSW * (it + 2), kA, vA);
+        compute(s0 + wave + kSW * (it + 1), kB, vB);
+    }
+}
+
+// The kSW wavefronts of a run merge into one part record: [G][D] un-normalised output, [G] maxima, [G] sums.
+// Every thread of the workgroup calls this; those beyond the kSW wavefronts only meet the barrier.
+__device__ __forceinline__ void merge_waves(uint32_t (*sVt)[D * kLDX], float (*sM)[16], float (*sL)[16], float m_run, float l_run,
+                                            const f32x4 (&acc)[8], int G, float *yp)
+{
+    static_assert(D * kLDX >= 16 * kLDO, "a wavefront's output rows reuse its value tile");
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int r16 = lane & 15, kg = lane >> 4;
+    if (wave < kSW) {
+        l_run += __shfl_xor(l_run, 16, 64);
+        l_run += __shfl_xor(l_run, 32, 64);
+        float *fo = reinterpret_cast<float *>(sVt[wave]);         // [16 heads][kLDO]
+#pragma unroll
+        for (int ct = 0; ct < 8; ++ct) *reinterpret_cast<f32x4 *>(fo + r16 * kLDO + 16 * ct + 4 * kg) = acc[ct];
+        if (kg == 0) { sM[wave][r16] = m_run; sL[wave][r16] = l_run; }
+    }
+    __syncthreads();
+    if (wave >= kSW) return;
+    for (int idx = threadIdx.x; idx < G * (D / 4); idx += 64 * kSW) {
+        const int g = idx / (D / 4), c4 = (idx - g * (D / 4)) * 4;
+        const float M = fmaxf(fmaxf(sM[0][g], sM[1][g]), fmaxf(sM[2][g], sM[3][g]));
+        const float mref = M == -INFINITY ? 0.f : M;
+        f32x4 y = {0.f, 0.f, 0.f, 0.f};
+        float l = 0.f;
+#pragma unroll
+        for (int w = 0; w < kSW; ++w) {
+            const float a = __expf(sM[w][g] - mref);
+            const f32x4 o = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(sVt[w]) + g * kLDO + c4);
+            y[0] += a * o[0]; y[1] += a * o[1]; y[2] += a * o[2]; y[3] += a * o[3];
+            l += a * sL[w][g];
+        }
+        *reinterpret_cast<f32x4 *>(yp + g * D + c4) = y;
+        if (c4 == 0) {
+            yp[G * D + g] = M;
+            yp[G * D + G + g] = l;
+        }
+    }
+}
+
+}  // namespace rows
+}  // namespace kvc

@@ -55,8 +55,9 @@ def test_hidden_rows_any_length(m, act):
 
 
 # Attention results whose scores, weights and sums are float32 differ from the exact result by the rounding of the
-# output alone: at most half a bf16 step, 2^-9 of the value, so 2^-9 of a row's norm; float32 adds about 1e-5.
-OUT_ROUNDING = 2.0 ** -9 + 1e-4
+# output alone.  bf16 keeps 8 significant bits: neighbours are 2^-7 apart at 1.0, so rounding to nearest moves a value
+# by at most 2^-8 of itself, and a row by at most 2^-8 of its norm; float32 adds about 1e-5.
+OUT_ROUNDING = 2.0 ** -8 + 1e-4
 
 
 def check_rows(out, ref):
@@ -86,3 +87,63 @@ def test_static_variant_any_shape(hq, hkv, I, m, t):
     check_rows(f64(L.out), ref)
     assert np.abs(f64(L.lse) - lref).max() <= 1e-4
     assert np.array_equal(f64(L.gKt), Kt) and np.array_equal(f64(L.gVt), Vt)
+
+
+def decode_case(w, m, ragged=None, packed=False):
+    """One step on random capsules against the oracle; ragged: (image counts, text counts) with NaNs in the capsule
+    slots and text rows that a sequence does not own."""
+    L = Layer(w, m)
+    g = torch.Generator().manual_seed(m)
+    L.gKc = torch.randn(L.gKc.shape, generator=g).to(torch.bfloat16).to(DEV)
+    L.gVc = torch.randn(L.gVc.shape, generator=g).to(torch.bfloat16).to(DEV)
+    if packed:
+        thp, up = kv.kvc_pack_theta(L.shape, L.g["theta"]), kv.kvc_pack_u(L.shape, L.g["U"])
+        L.params = kv.make_params(L.g["key_idx"], L.g["theta"], L.g["U"], L.g["mu"], thp, up)
+    q, kn, vn = synth.make_step_inputs(w, 0, 0)
+    th, U, mu = f64(L.p["theta"]), f64(L.p["U"]), f64(L.p["mu"])
+    Kt, Vt = f64(L.Kt).copy(), f64(L.Vt).copy()
+    Kc, Vc = f64(L.gKc), unpack_vc(L.gVc, m, 128)
+    print(f"[any] decode {w.n_q_heads}/{w.n_kv_heads} n={w.n_img_tokens} m={m} I={w.n_images} t={w.text_len} packed={packed} {ragged}", flush=True)
+    if ragged is None:
+        out, lse = L.decode(q.to(DEV), w.text_len, kn.to(DEV), vn.to(DEV))
+        ref, lref = orc.reconstruct_attend_decode(f64(q), Kc, Vc, th, U, mu, w.n_img_tokens, Kt, Vt, w.text_len, f64(kn), f64(vn))
+        assert np.array_equal(f64(L.gKt), Kt) and np.array_equal(f64(L.gVt), Vt)
+    else:
+        ni, tl = ragged
+        for b in range(w.batch):
+            L.gKc[b, :, ni[b]:] = float("nan")
+            L.gVc[b, :, ni[b]:] = float("nan")
+            L.gKt[b, :, tl[b] + 1:] = float("nan")
+            L.gVt[b, :, tl[b] + 1:] = float("nan")
+        dev = [torch.tensor(x, dtype=torch.int32, device=DEV) for x in ragged]
+        kv.kvc_reconstruct_attend_decode_ragged(L.shape, L.params, q.to(DEV), L.gKc, L.gVc, L.gKt, L.gVt, *dev, w.text_cap, kn.to(DEV),
+                                                vn.to(DEV), 0.0, L.out, L.lse, L.ws)
+        torch.cuda.synchronize()
+        out, lse = f64(L.out), f64(L.lse)
+        ref, lref = orc.reconstruct_attend_decode_ragged(f64(q), Kc, Vc, th, U, mu, w.n_img_tokens, ni, tl, Kt, Vt, f64(kn), f64(vn))
+    check_rows(out, ref)
+    assert np.abs(lse - lref).max() <= 1e-4
+
+
+# n around the 8-column piece and the slices of 128 / 256 / 512 positions; m around 8, 16 and 32 rows; tiles with fewer
+# image blocks than they hold; several tiles per workgroup; group sizes without a tuned kernel; batches that select
+# each slice width
+@pytest.mark.parametrize("hq,hkv,B,I,n,m,t", [
+    (4, 4, 1, 1, 8, 3, 0), (7, 1, 1, 3, 9, 9, 1), (6, 2, 2, 1, 127, 8, 5), (3, 1, 1, 5, 128, 128, 127), (14, 2, 1, 2, 129, 31, 128),
+    (28, 4, 1, 3, 729, 292, 200), (16, 1, 1, 2, 333, 33, 130), (5, 1, 2, 7, 257, 103, 300), (12, 1, 1, 4, 511, 64, 20),
+    (9, 1, 1, 1, 1023, 640, 3), (4, 2, 2, 9, 100, 41, 2500), (64, 32, 8, 3, 200, 40, 10), (32, 8, 16, 2, 300, 90, 33),
+    (32, 32, 8, 17, 65, 17, 4), (2, 1, 1, 64, 515, 65, 9), (8, 8, 32, 3, 520, 40, 7), (2, 2, 1, 0, 50, 20, 40),
+    (10, 2, 1, 2, 1024, 1024, 6)])
+def test_decode_any_shape(hq, hkv, B, I, n, m, t):
+    decode_case(wl(n, I, B=B, hq=hq, hkv=hkv, t=t), m)
+
+
+@pytest.mark.parametrize("hq,hkv,B,I,n,m,t", [(4, 4, 1, 1, 8, 3, 0), (14, 2, 1, 3, 136, 29, 9), (28, 4, 1, 3, 728, 292, 200),
+                                              (64, 32, 8, 3, 200, 43, 10), (32, 8, 16, 2, 304, 90, 33), (8, 8, 32, 3, 520, 47, 7)])
+def test_decode_any_shape_packed_parameters(hq, hkv, B, I, n, m, t):
+    decode_case(wl(n, I, B=B, hq=hq, hkv=hkv, t=t), m, packed=True)
+
+
+@pytest.mark.parametrize("n,m,packed", [(137, 41, False), (136, 41, True), (600, 100, False), (600, 100, True)])
+def test_ragged_batch_any_shape(n, m, packed):
+    decode_case(wl(n, 5, B=5, hq=14, hkv=2, t=140), m, ragged=([5, 0, 1, 3, 4], [139, 0, 5, 128, 127]), packed=packed)
