@@ -41,7 +41,8 @@
  *    two-layer key reconstructor for m >= 8; decode for n >= 8 and G <= 16.  Decode kernels tuned further, with
  *    scores and weights rounded to bf16 between the steps, serve n in {256, 576, 1024}, G in {1, 2, 4, 6, 7, 8}
  *    and at most 256 partial results per (batch element, KV head); every other decode keeps them at float32
- *    precision.  Other shapes, and fp32, run shape-agnostic scalar kernels: same results within rounding, far
+ *    precision.  fp32, and bf16 with another d, run compression and decode on the fp32 matrix instruction
+ *    (n >= 4, G <= 16).  What is left runs shape-agnostic scalar kernels: same results within rounding, far
  *    lower speed; their decode is limited to n <= 16384 (KVC_ERR_UNSUPPORTED beyond).
  */
 #ifndef KVCAPSULE_H

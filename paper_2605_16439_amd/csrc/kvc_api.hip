@@ -164,7 +164,7 @@ namespace kvc {
 kvc_status other_decode(const DecodeCall &c)
 {
     kvc_status st = KVC_OK;
-    return any_decode(c, &st) ? st : generic_decode(c);
+    return any_decode(c, &st) || float_decode(c, &st) ? st : generic_decode(c);
 }
 }  // namespace kvc
 
@@ -189,6 +189,7 @@ size_t kvc_workspace_bytes(const kvc_shape *shape, int32_t max_text_len)
         size_t f = fast_compress_ws_bytes(*shape);
         if (f > need) need = f;
     }
+    need = std::max(need, float_decode_ws_bytes(*shape, max_text_len));
     if (any_decode_supported(*shape)) need = std::max(need, any_decode_ws_bytes(*shape, max_text_len));
     if (fast_static_supported(*shape)) need = std::max(need, fast_static_ws_bytes(*shape));
     return need;
@@ -221,7 +222,7 @@ kvc_status kvc_compress(const kvc_shape *shape, const kvc_params *params, const 
                                      vis_start, seq_len, Kc, Vc, workspace, workspace_bytes, stream);
     if (st != KVC_OK) return st;
     if (fast_compress_supported(c.s)) return fast_compress(c);
-    return generic_compress(c);
+    return float_compress(c, &st) ? st : generic_compress(c);
 }
 
 kvc_status kvc_compress_generic(const kvc_shape *shape, const kvc_params *params, const void *K,

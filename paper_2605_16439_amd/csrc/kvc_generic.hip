@@ -4,7 +4,9 @@
 // text keys (Sec. 3.2):
 //     S = sigma q Kc^T  ->  L = S theta  ->  P = softmax([L ; text logits])
 //     W = P_vis U^T     ->  out = sum_blocks W Vc + (sum P_vis) mu + P_txt V_text
-// The fp32 configuration and every shape outside the matrix-core kernels runs here.
+// What the matrix-core kernels do not cover runs here: block lengths below four, more than 16 query heads per KV head,
+// the static variant, the full-cache comparison and the first layer of the two-layer reconstructor outside bf16 with
+// d = 128 -- and, through the forced entry points, anything, as a second implementation to check against.
 #include "kvc_internal.h"
 
 namespace kvc {

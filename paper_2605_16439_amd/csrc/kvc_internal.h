@@ -162,7 +162,11 @@ void full_decode_set_chunk_steps(int steps);
 bool any_decode_supported(const kvc_shape &s);
 size_t any_decode_ws_bytes(const kvc_shape &s, int32_t max_text);
 bool any_decode(const DecodeCall &c, kvc_status *st);
-// that, or the scalar kernels
+// fp32, and bf16 with any head_dim, on the fp32 matrix instruction: true when the call was taken
+bool float_compress(const CompressCall &c, kvc_status *st);
+size_t float_decode_ws_bytes(const kvc_shape &s, int32_t max_text);
+bool float_decode(const DecodeCall &c, kvc_status *st);
+// those, or the scalar kernels
 kvc_status other_decode(const DecodeCall &c);
 // static variant (attention over the compressed rows themselves), bf16, head_dim 128
 bool fast_static_supported(const kvc_shape &s);

@@ -147,3 +147,58 @@ def test_decode_any_shape_packed_parameters(hq, hkv, B, I, n, m, t):
 @pytest.mark.parametrize("n,m,packed", [(137, 41, False), (136, 41, True), (600, 100, False), (600, 100, True)])
 def test_ragged_batch_any_shape(n, m, packed):
     decode_case(wl(n, 5, B=5, hq=14, hkv=2, t=140), m, ragged=([5, 0, 1, 3, 4], [139, 0, 5, 128, 127]), packed=packed)
+
+
+# fp32, and bf16 with other head dimensions: d around the 16-channel tile, n around 4 and the slices of 64 and 256
+# positions, m around 16 and 32 rows, text around the 128-row step, few and many image blocks
+FLOAT_CASES = [(2, 1, 1, 1, 4, 1, 0, 8), (8, 2, 1, 1, 576, 231, 64, 64), (3, 3, 2, 3, 63, 15, 127, 24), (16, 1, 1, 2, 65, 16, 128, 72),
+               (14, 2, 2, 5, 130, 33, 300, 128), (4, 4, 2, 3, 257, 129, 1, 136), (10, 2, 1, 4, 1023, 410, 9, 256),
+               (32, 32, 16, 2, 260, 17, 5, 40), (1, 1, 1, 0, 10, 4, 2500, 64), (6, 2, 1, 60, 300, 70, 3, 64)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("hq,hkv,B,I,n,m,t,d", FLOAT_CASES)
+def test_layer_on_the_fp32_matrix_instruction(hq, hkv, B, I, n, m, t, d, dtype):
+    w = synth.Workload(f"float_n{n}", 93, 1, B, hq, hkv, d, dtype, n, I, 0.6, t, 1)
+    L = Layer(w, m, pre=3, post=2)
+    print(f"[float] {dtype} {hq}/{hkv} B={B} I={I} n={n} m={m} t={t} d={d}", flush=True)
+    th, U, mu = f64(L.p["theta"]), f64(L.p["U"]), f64(L.p["mu"])
+    if I > 0:
+        L.compress()
+        Kc_ref, Vc_ref = orc.compress(f64(L.K), f64(L.V), L.p["key_idx"].numpy(), U, mu, n, I, 3, store_code(w))
+        assert np.array_equal(f64(L.gKc), Kc_ref)
+        assert block_rel_err(unpack_vc(L.gVc, m, d), Vc_ref) <= (1e-5 if dtype == "f32" else ONE_ROUNDING)
+    q, kn, vn = synth.make_step_inputs(w, 0, 0)
+    Kt, Vt = f64(L.Kt).copy(), f64(L.Vt).copy()
+    out, lse = L.decode(q.to(DEV), t, kn.to(DEV), vn.to(DEV))
+    ref, lref = orc.reconstruct_attend_decode(f64(q), f64(L.gKc), unpack_vc(L.gVc, m, d), th, U, mu, n, Kt, Vt, t, f64(kn), f64(vn))
+    assert np.array_equal(f64(L.gKt), Kt) and np.array_equal(f64(L.gVt), Vt)
+    if dtype == "f32":
+        e = np.linalg.norm(out - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
+        print(f"[float]   row rel err {e.max():.3e}", flush=True)
+        assert e.max() <= 1e-5
+    else:
+        check_rows(out, ref)
+    assert np.abs(lse - lref).max() <= 1e-4
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_ragged_batch_fp32(d):
+    w = synth.Workload("float_ragged", 94, 1, 4, 14, 2, d, "f32", 150, 5, 0.6, 140, 1)
+    m = 41
+    L = Layer(w, m)
+    g = torch.Generator().manual_seed(m)
+    L.gKc, L.gVc = (torch.randn(L.gKc.shape, generator=g).to(DEV) for _ in range(2))
+    ni, tl = [5, 0, 1, 3], [139, 0, 5, 128]
+    Kc, Vc, Kt, Vt = f64(L.gKc), unpack_vc(L.gVc, m, d), f64(L.Kt).copy(), f64(L.Vt).copy()
+    for b in range(w.batch):
+        L.gKc[b, :, ni[b]:], L.gVc[b, :, ni[b]:], L.gKt[b, :, tl[b] + 1:], L.gVt[b, :, tl[b] + 1:] = (float("nan"),) * 4
+    q, kn, vn = synth.make_step_inputs(w, 0, 0)
+    dev = [torch.tensor(x, dtype=torch.int32, device=DEV) for x in (ni, tl)]
+    kv.kvc_reconstruct_attend_decode_ragged(L.shape, L.params, q.to(DEV), L.gKc, L.gVc, L.gKt, L.gVt, *dev, w.text_cap, kn.to(DEV),
+                                            vn.to(DEV), 0.0, L.out, L.lse, L.ws)
+    torch.cuda.synchronize()
+    ref, lref = orc.reconstruct_attend_decode_ragged(f64(q), Kc, Vc, f64(L.p["theta"]), f64(L.p["U"]), f64(L.p["mu"]), 150, ni, tl, Kt, Vt,
+                                                     f64(kn), f64(vn))
+    e = np.linalg.norm(f64(L.out) - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
+    assert e.max() <= 1e-5 and np.abs(f64(L.lse) - lref).max() <= 1e-4
