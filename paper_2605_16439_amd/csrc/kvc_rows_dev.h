@@ -174,15 +174,24 @@ __device__ __forceinline__ void walk(const Rows &p, const uint16_t *__restrict__
         if constexpr (TEXT) __builtin_amdgcn_wave_barrier();
     };
 
-    u32x4 kA[2][4], vA[8], kB[2][4], vB[8];
-    load(s0 + wave, kA, vA);
-    for (int it = 0; it < p.cs; it += 2) {
-        load(s0 + wave + kSW * (it + 1), kB, vB);
-        compute(s0 + wave + kSW * it, kA, vA);
-        if (it + 1 >= p.cs) break;
-        load(s0 + wave + kSW * (it + 2), kA, vA);
-        compute(s0 + wave + kSW * (it + 1), kB, vB);
+    // Two steps in flight in two register sets.  No step is requested that the run does not have: with runs of one or
+    // two steps a request ahead of the end would double what the kernel reads.
+    const int all = TEXT ? (p.t + kSR - 1) / kSR : p.SV;
+    const int left_w = min(all - s0, kSW * p.cs) - wave, N = left_w > 0 ? (left_w + kSW - 1) / kSW : 0;
+    if (N == 0) return;
+    const int sw = s0 + wave;
+    u32x4 kA[2][4], vA[8], kB[2][4] = {}, vB[8] = {};
+    load(sw, kA, vA);
+    if (N > 1) load(sw + kSW, kB, vB);
+    int it = 0;
+    for (; it + 2 < N; it += 2) {
+        compute(sw + kSW * it, kA, vA);
+        load(sw + kSW * (it + 2), kA, vA);
+        compute(sw + kSW * (it + 1), kB, vB);
+        load(sw + kSW * min(it + 3, N - 1), kB, vB);
     }
+    compute(sw + kSW * it, kA, vA);
+    if (it + 1 < N) compute(sw + kSW * (it + 1), kB, vB);
 }
 
 // The kSW wavefronts of a run merge into one part record: [G][D] un-normalised output, [G] maxima, [G] sums.
