@@ -12,13 +12,15 @@
 //                  from memory; P = exp(S - max) stays in registers and is the B operand of the
 //                  second product as it comes out of the first (the 32 rows of a step are numbered
 //                  the same way on both sides of the contraction); the value rows are transposed
-//                  through a wave-private LDS tile to become its A operand.  The next step's rows
-//                  are requested before the current step is multiplied.  The four waves merge
+//                  through a wave-private LDS tile to become its A operand.  Two steps are in flight;
+//                  none beyond the split is requested.  The four waves merge
 //                  through LDS into one part record.
 //   finalize       the parts of a (batch element, query head) are merged by the finalize kernel of
 //                  the capsule path (a lane per part, shuffles only).
 //
-// Bound: HBM (2 B H_kv (S + 1) d 2 bytes are read once; 4 flop per byte).
+// Bound: HBM (2 B H_kv (S + 1) d 2 bytes are read once; 4 flop per byte).  B = 4, 28 / 4 heads, 8705 rows, 71 MB:
+// 24.2 us per call with 368 workgroups and requests past a split's end, 20.5 us (3.5 TB/s, the merge launch included)
+// with one workgroup per CU (make_full_plan).
 #include "kvc_internal.h"
 
 #include <algorithm>
@@ -40,7 +42,7 @@ constexpr int kLDF = D + 4;       // floats per head row of a wave's output in L
 constexpr int kMaxSplits = 64;    // the finalize kernel keeps one part per lane
 
 struct FullPlan {
-    int Hq, Hkv, G, NS, chunk, nit, t, t_in, rec;
+    int Hq, Hkv, G, NS, chunk, t, t_in, rec;
     unsigned qNS, qHkv;
     long sb, sh, ss;              // element strides of the cache
     float scale;
@@ -91,8 +93,11 @@ __global__ __launch_bounds__(64 * kWaves) void full_split(const uint16_t *__rest
             }
     };
 
-    u32x4 kA[2][4], vA[4][2], kB[2][4], vB[4][2];
-    load_tile(0, kA, vA);
+    // steps of this wave
+    const int N = max((hi - lo - kRW * wave + kStep - 1) / kStep, 0);
+    u32x4 kA[2][4] = {}, vA[4][2] = {}, kB[2][4] = {}, vB[4][2] = {};
+    if (N > 0) load_tile(0, kA, vA);
+    if (N > 1) load_tile(1, kB, vB);
     u32x4 qf[4];
     {
         const u32x4 *qp = reinterpret_cast<const u32x4 *>(q + (static_cast<size_t>(b) * p.Hq + h * p.G + min(r16, p.G - 1)) * D) + kg;
@@ -167,13 +172,17 @@ __global__ __launch_bounds__(64 * kWaves) void full_split(const uint16_t *__rest
         __builtin_amdgcn_wave_barrier();
     };
 
-    // two steps per round, so that the two register sets swap by name; a step beyond the split is
-    // all masked (its loads repeat the split's last row)
-    for (int it = 0; it < p.nit; it += 2) {
-        load_tile(it + 1, kB, vB);
+    // Two steps in flight in two register sets; no step is requested that the split does not have.
+    if (N > 0) {
+        int it = 0;
+        for (; it + 2 < N; it += 2) {
+            compute(it, kA, vA);
+            load_tile(it + 2, kA, vA);
+            compute(it + 1, kB, vB);
+            load_tile(min(it + 3, N - 1), kB, vB);
+        }
         compute(it, kA, vA);
-        load_tile(it + 2, kA, vA);
-        compute(it + 1, kB, vB);
+        if (it + 1 < N) compute(it + 1, kB, vB);
     }
 
     // ---- the four waves merge into one part record ------------------------------------------------
@@ -222,19 +231,26 @@ FullPlan make_full_plan(const FullCall &c, void *ws)
     p.t = c.t; p.t_in = c.t_in;
     p.sb = c.sb; p.sh = c.sh; p.ss = c.ss;
     p.scale = c.scale;
-    // Rows per split: enough splits to give every CU about two workgroups (the rows of a split are
-    // read by one workgroup, 64 KB in flight per step), never more than the finalize kernel's 64 parts
-    const int steps_total = (c.t + kStep - 1) / kStep;
+    // Rows per split, in groups of 32, one wave's step: the choice that minimises rounds of workgroups (one per CU) times
+    // a split's groups plus 10 for its start and its part record.  At t = 8705, 16 (b, head) pairs: 18 groups,
+    // 16 splits, every CU one workgroup 20.5 us; 24 groups (192 workgroups) 21.3; 9 groups (two per CU) 24.5;
+    // 12 groups (368 workgroups, some CUs two) 25.3; 36 groups (128) 27.6; 17 groups (272: 16 CUs take two) 31.2.
+    // A split is at least a group per wave; the finalize kernel takes at most 64 parts.
+    const int groups = (c.t + kRW - 1) / kRW;
     const long bh = static_cast<long>(c.B) * c.Hkv;
-    int cs = g_chunk_steps;
-    if (cs <= 0) {
-        const long want = std::max(1L, (2L * c.cus + bh - 1) / bh);        // splits per (b, head)
-        cs = static_cast<int>((steps_total + want - 1) / want);
-        if (cs < 2) cs = steps_total >= 2 ? 2 : 1;
+    int cg = g_chunk_steps * kWaves;
+    if (cg <= 0) {
+        long best = -1;
+        const long first = (bh + c.cus - 1) / c.cus;
+        for (long rounds = first; rounds < first + 4; ++rounds) {          // as many splits as fit that many rounds
+            const int ns = static_cast<int>(std::min<long>(rounds * c.cus / bh, kMaxSplits));
+            const int g = std::max((groups + ns - 1) / ns, kWaves), used = (groups + g - 1) / g;
+            const long cost = (bh * used + c.cus - 1) / c.cus * (g + 10);
+            if (best < 0 || cost < best) { best = cost; cg = g; }
+        }
     }
-    while ((steps_total + cs - 1) / cs > kMaxSplits) ++cs;
-    p.chunk = cs * kStep;
-    p.nit = std::min(cs, steps_total);
+    while ((groups + cg - 1) / cg > kMaxSplits) ++cg;
+    p.chunk = cg * kRW;
     p.NS = (c.t + p.chunk - 1) / p.chunk;
     p.rec = static_cast<int>(align_up(static_cast<size_t>(p.G) * D + 2 * p.G, 4));
     p.qNS = quot_multiplier(p.NS);

@@ -113,6 +113,14 @@ def test_full_decode_split_sizes(chunk_steps):
     run_case(62 + chunk_steps, 2, 14, 2, 128, 1500, steps=1, chunk_steps=chunk_steps)
 
 
+# splits that leave wavefronts without a step, with one, with an odd and an even number of them; more (batch, head)
+# pairs than compute units
+@pytest.mark.parametrize("B,hq,hkv,kv_len", [(1, 2, 1, 20), (1, 8, 1, 8191), (4, 8, 4, 2047), (3, 15, 15, 700), (11, 24, 24, 160),
+                                             (5, 16, 16, 1290), (40, 8, 8, 97)])
+def test_full_decode_rows_per_split(B, hq, hkv, kv_len):
+    run_case(73, B, hq, hkv, 128, kv_len, steps=2)
+
+
 def test_full_decode_scalar_path_fp32_and_other_head_dim():
     run_case(70, 2, 6, 3, 64, 150, steps=2, dtype=torch.float32)
     run_case(71, 1, 4, 2, 64, 90, steps=1, dtype=torch.bfloat16)
