@@ -14,7 +14,9 @@
 // MFMA operands.
 //
 // With NW = 8 two wavefronts share a SIMD: while one waits for LDS or at the barrier the other
-// issues MFMAs, which a workgroup of four wavefronts (one per SIMD) cannot do.  At the shapes of
+// issues MFMAs, which a workgroup of four wavefronts (one per SIMD) cannot do.  (Rows of U straight from memory in the
+// operand layout, no LDS for them: 32.4 us against 28.3 at the headline shape -- half of each line per request, as
+// LDS is not the bound.)  At the shapes of
 // the paper's workloads the kernel is bound by what the L2s deliver to the compute units (every
 // workgroup streams its rows of U and its block of V once), not by the matrix cores.
 //
@@ -87,7 +89,7 @@ template <int LD> __device__ inline int sv_index(int c, int p) { return c * LD +
 //         The operands of the matrix instruction trade places, so that a lane ends up with four consecutive
 //         channels of one row: the result is row-major.
 // The scalar kernels that FORM 1 and 2 replace run one multiply-add per lane and load; the same two shapes here
-// (n = 729, m = 292, 12 image blocks: 595 -> 13.5 us; m = 410, 128 image blocks, GELU: 1011 -> 23 us) are
+// (n = 729, m = 292, 12 image blocks: 595 -> 13.5 us; m = 410, 128 image blocks, GELU: 1011 -> 20.8 us) are
 // bound as FORM 0 is, by the latency of a tile step and, when few workgroups are resident, by their number.
 // 16-byte register image of 8 elements, shifted down by `sh` elements (sh >= 8: nothing is left)
 __device__ inline u32x4 drop_elems(u32x4 v, int sh)
@@ -100,10 +102,31 @@ __device__ inline u32x4 drop_elems(u32x4 v, int sh)
     return u32x4{__builtin_amdgcn_alignbit(x1, x0, bits) & keep, __builtin_amdgcn_alignbit(x2, x1, bits) & keep,
                  __builtin_amdgcn_alignbit(x3, x2, bits) & keep, (x3 >> bits) & keep};
 }
+// GELU, erf form: x Phi(x) = max(x, 0) - |x| Q(|x|), Q(a) = erfc(a / sqrt 2) / 2 = exp(-a^2 / 2) t P(t) with
+// t = 1 / (1 + 0.21875 a).  P is a fit of degree 8 to the ratio over 0 <= a <= 14.5, largest relative error 6e-8.
+// Against float64 on N(0, 1) arguments: 3.6e-8 of the norm (0.5 x (1 + erff): 3.8e-8), and for negative x no
+// cancellation.  No branch: erff evaluates both of its ranges in a wavefront whose arguments straddle 1, which cost
+// 8 of 26 us at m = 410, 128 image blocks.
+__device__ inline float gelu(float x)
+{
+    const float a = fminf(fabsf(x), 15.f);               // Q underflows before; an infinite |x| must not meet Q = 0
+    const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.21875f, a, 1.f));
+    float r = -0.043066394f;
+    r = __builtin_fmaf(r, t, 0.126726424f);
+    r = __builtin_fmaf(r, t, -0.058756439f);
+    r = __builtin_fmaf(r, t, 0.082225485f);
+    r = __builtin_fmaf(r, t, 0.065257973f);
+    r = __builtin_fmaf(r, t, 0.067752807f);
+    r = __builtin_fmaf(r, t, 0.085734924f);
+    r = __builtin_fmaf(r, t, 0.086828119f);
+    r = __builtin_fmaf(r, t, 0.087297074f);
+    const float q = r * t * __builtin_amdgcn_exp2f(a * a * -0.72134752f);
+    return (x > 0.f ? x : x * 0.f) - a * q;              // (x * 0: a NaN stays one)
+}
 __device__ inline float activate(float x, int act)
 {
     if (act == 1) return fmaxf(x, 0.f);
-    if (act == 2) return 0.5f * x * (1.f + erff(x * 0.70710678118654752f));     // GELU, erf form
+    if (act == 2) return gelu(x);
     return x;
 }
 

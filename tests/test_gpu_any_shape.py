@@ -54,6 +54,22 @@ def test_hidden_rows_any_length(m, act):
     assert block_rel_err(f64(H), orc.mlp_hidden(f64(Kc), f64(W1), act, orc.STORE_BF16)) <= ONE_ROUNDING
 
 
+# GELU over its range: with W1 = I a hidden row is the activation of a key row, rounded once (2^-8 of the value at most;
+# 1e-5 for the float32 evaluation and for results below bf16's smallest normal number, which are left out)
+def test_gelu_over_its_range():
+    m, d = 128, 128
+    mag = torch.logspace(-6, 2, m * d // 2, dtype=torch.float64)
+    x = torch.cat([mag, -mag]).to(torch.bfloat16).reshape(1, 1, 1, m, d)
+    x[0, 0, 0, 0, :2] = torch.tensor([0.0, -0.0])
+    H = torch.full_like(x, float("nan")).to(DEV)
+    kv.kvc_mlp_hidden(kv.make_shape(1, 1, 1, d, 1024, 1, m, torch.bfloat16), torch.eye(m, dtype=torch.bfloat16)[None].to(DEV), kv.KVC_ACT_GELU,
+                      x.to(DEV), H)
+    ref = x.double() * 0.5 * torch.special.erfc(-x.double() / 2 ** 0.5)
+    got = H.cpu().double()
+    assert torch.isfinite(got).all()
+    assert ((got - ref).abs() <= (2.0 ** -8 + 1e-5) * ref.abs() + 2.0 ** -126).all()
+
+
 # Attention results whose scores, weights and sums are float32 differ from the exact result by the rounding of the
 # output alone.  bf16 keeps 8 significant bits: neighbours are 2^-7 apart at 1.0, so rounding to nearest moves a value
 # by at most 2^-8 of itself, and a row by at most 2^-8 of its norm; float32 adds about 1e-5.
