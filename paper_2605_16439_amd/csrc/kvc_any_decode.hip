@@ -1,5 +1,5 @@
-// Decode step for the shapes that the tuned kernels are not compiled for: bf16 storage, head_dim 128, any number
-// n >= 8 of tokens per image block, any compressed length, at most 16 query heads per KV head.  One launch in the
+// Decode step for the shapes that the tuned kernels are not compiled for, and for small calls of the others
+// (any_decode_preferred): bf16 storage, head_dim 128, any number n >= 8 of tokens per image block, any compressed length, at most 16 query heads per KV head.  One launch in the
 // score-space order of Alg. 1, then the merge of the part records:
 //
 //   ga_pass   a vision workgroup owns a slice of PS positions of one (batch element, KV head) and walks tiles of
@@ -643,6 +643,7 @@ __global__ __launch_bounds__(64 * kGW) void ga_pass(const uint16_t *__restrict__
 }
 
 constexpr size_t kPassLds = 156 * 1024;
+constexpr int kOneEach = 256;         // workgroups that find a compute unit each
 
 // false: no plan (slices or LDS beyond what the kernel holds)
 bool make_gplan(GPlan &p, const kvc_shape &s, int t, int t_in, int cap)
@@ -661,20 +662,24 @@ bool make_gplan(GPlan &p, const kvc_shape &s, int t, int t_in, int cap)
     p.UP = up_max;
     for (int w : {512, 256})
         if (p.n > w / 2 && groups(up_max) * ((p.n + w - 1) / w) >= 256 && pass_lds(p.m, w, false) <= kPassLds) { ps = w; break; }
-    if (ps == 128)
-        while (p.UP > 1 && groups(p.UP) * ((p.n + 127) / 128) < 256) p.UP = (p.UP + 1) / 2;
     p.PS = ps;
     p.F = (p.n + ps - 1) / ps;
     if (p.F > kMaxVisParts || pass_lds(p.m, ps, false) > kPassLds) return false;
+    const int steps = (t + kSR * kSW - 1) / (kSR * kSW);
+    p.cst = std::max(1, (steps + kMaxTextParts - 1) / kMaxTextParts);
+    p.NTX = (steps + p.cst - 1) / p.cst;
+    // smaller tiles as long as every workgroup, those of the text with them, still has a compute unit to itself and one
+    // tile: 12 blocks of n = 576, m = 346, B = 1, 12/2 heads, two tiles per workgroup 24.6 us, one twice as full 20.5
+    if (ps == 128)
+        for (int up = (p.UP + 1) / 2; p.UP > 1 && groups(up) * p.F + bh * p.NTX <= kOneEach && (p.I + up - 1) / up * p.F <= kMaxVisParts;
+             up = (p.UP + 1) / 2)
+            p.UP = up;
     const int tiles = (p.I + p.UP - 1) / p.UP, ug_max = kMaxVisParts / p.F;
     p.NUT = p.I > 0 ? (tiles + ug_max - 1) / ug_max : 1;
     p.NUG = p.I > 0 ? (tiles + p.NUT - 1) / p.NUT : 0;
     p.NGR = p.Hkv * p.B * p.NUG;
     p.chunk = (p.NGR + 7) / 8;
     p.nvis = 8 * p.chunk * p.F;
-    const int steps = (t + kSR * kSW - 1) / (kSR * kSW);
-    p.cst = std::max(1, (steps + kMaxTextParts - 1) / kMaxTextParts);
-    p.NTX = (steps + p.cst - 1) / p.cst;
     p.nparts = p.NUG * p.F + p.NTX;
     p.rec = static_cast<int>(align_up(p.G * D + 2 * p.G, 4));
     p.qF = quot_multiplier(p.F); p.qBU = quot_multiplier(p.B * p.NUG); p.qNUG = quot_multiplier(p.NUG);
@@ -717,11 +722,21 @@ bool any_decode_supported(const kvc_shape &s)
 
 size_t any_decode_ws_bytes(const kvc_shape &s, int32_t max_text)
 {
+    // (tiles, and with them the part records, are smallest and most where the text is short)
     GPlan p;
-    if (!make_gplan(p, s, std::max(max_text, 1), 0, max_text)) return 0;
+    if (!make_gplan(p, s, s.n_images > 0 ? 0 : 1, 0, max_text)) return 0;
     // (the number of text parts does not grow monotonically with the text length: its bound is taken)
     const int ntx = std::min((std::max(max_text, 1) + kSR * kSW - 1) / (kSR * kSW), kMaxTextParts);
     return static_cast<size_t>(p.B) * p.Hkv * (p.NUG * p.F + ntx) * p.rec * sizeof(float) + kTimelineBytes;
+}
+
+bool any_decode_preferred(const DecodeCall &c)
+{
+    GPlan p;
+    return c.theta_packed && c.U_packed && !c.static_variant && c.s.dtype == KVC_BF16 && c.s.head_dim == D &&
+           c.s.n_q_heads / c.s.n_kv_heads <= 16 && c.s.n_img_tokens >= 8 && c.s.n_images > 0 &&
+           make_gplan(p, c.s, c.t, c.t_in, c.cap) && p.NUT == 1 && p.UP * p.KS <= 10 &&
+           static_cast<long>(p.NGR) * p.F + static_cast<long>(p.B) * p.Hkv * p.NTX <= kOneEach;
 }
 
 bool any_decode(const DecodeCall &c, kvc_status *st)

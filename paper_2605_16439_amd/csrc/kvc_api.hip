@@ -134,6 +134,13 @@ kvc_status prepare_compress(CompressCall &c, const kvc_shape *shape, const kvc_p
 kvc_status dispatch_decode(const DecodeCall &c)
 {
     kvc_status st = KVC_OK;
+    // Small calls with packed parameters: one latency-bound pass, with float32 weights, instead of three or four launches.
+    // "Small": a compute unit for every workgroup of that pass, and at most 10 steps of 32 compressed rows per workgroup,
+    // whose chains are its time (us per layer, tuned kernels against this pass: n = 256, m = 154, 16 blocks, 28/4 heads 16.5 / 11.5,
+    // 32 blocks (10 steps) 16.6 / 14.0; n = 576, m = 144, 5 blocks 14.9 / 12.0, 12 blocks (10 steps) 14.9 / 13.1; n = 1024,
+    // m = 256, one block 14.6 / 12.6, 8 blocks (16 steps) 13.3 / 16.5; m = 615 (20 steps) 19.5 / 21.4).  With plain parameters
+    // these shapes stay on the tuned kernels.
+    if (fast_decode_default() && any_decode_preferred(c) && any_decode(c, &st)) return st;
     if (stream_decode(c, &st)) return st;
     if (fast_decode_supported(c.s)) return fast_decode(c);
     return other_decode(c);

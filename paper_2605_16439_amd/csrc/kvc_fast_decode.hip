@@ -62,7 +62,8 @@ using namespace dd;
 
 // developer knobs (kvc_dev_decode_knobs) and the call counter that numbers fab_fused's epochs
 std::atomic<unsigned> g_epoch{0};
-int g_wait_ticks = 2000;          // 20 us: a few launch latencies; a workgroup that waits longer computes alone
+constexpr int kWaitTicks = 2000;
+int g_wait_ticks = kWaitTicks;        // 20 us: a few launch latencies; a workgroup that waits longer computes alone
 int g_force_nt = 0;               // row tiles per fc_fused workgroup (0: rule in make_plan_layout)
 int g_use_packed_u = 1;           // developer switch: 0 reads the plain U even where the packed form is given
 int g_separate = 0;               // 1: fa_scores and fb_probs as separate launches
@@ -1388,6 +1389,8 @@ void fast_decode_knobs(int row_tiles, int separate, int wait_ticks)
     if (separate >= 0) g_separate = separate;
     if (wait_ticks >= 0) g_wait_ticks = wait_ticks;
 }
+
+bool fast_decode_default() { return g_force_nt == 0 && g_separate == 0 && g_wait_ticks == kWaitTicks && stream_decode_default(); }
 
 // synchronous read of the debug counter (tests)
 long fast_decode_fallbacks()

@@ -150,6 +150,7 @@ unsigned *decode_fallback_counter();
 bool stream_decode(const DecodeCall &c, kvc_status *st);
 size_t stream_decode_ws_bytes(const kvc_shape &s, int32_t max_text);
 void stream_decode_knob(int mode);
+bool stream_decode_default();
 long stream_decode_calls();
 kvc_status pack_theta(const kvc_shape &s, const void *theta, void *packed, hipStream_t stream);
 kvc_status pack_u(const kvc_shape &s, const void *U, void *packed, hipStream_t stream);
@@ -162,6 +163,8 @@ void full_decode_set_chunk_steps(int steps);
 bool any_decode_supported(const kvc_shape &s);
 size_t any_decode_ws_bytes(const kvc_shape &s, int32_t max_text);
 bool any_decode(const DecodeCall &c, kvc_status *st);
+bool any_decode_preferred(const DecodeCall &c);      // where the tuned kernels would take longer
+bool fast_decode_default();                          // no developer knob of the tuned kernels is set
 // fp32, and bf16 with any head_dim, on the fp32 matrix instruction: true when the call was taken
 bool float_compress(const CompressCall &c, kvc_status *st);
 size_t float_decode_ws_bytes(const kvc_shape &s, int32_t max_text);

@@ -759,6 +759,7 @@ template <int PB> void launch_fin(const SPlan &p, const DecodeCall &c)
 }  // namespace
 
 void stream_decode_knob(int mode) { g_stream_mode = mode; }
+bool stream_decode_default() { return g_stream_mode < 0; }
 long stream_decode_calls() { return g_stream_calls.load(); }
 
 size_t stream_decode_ws_bytes(const kvc_shape &s, int32_t max_text)

@@ -160,6 +160,21 @@ def test_decode_any_shape_packed_parameters(hq, hkv, B, I, n, m, t):
     decode_case(wl(n, I, B=B, hq=hq, hkv=hkv, t=t), m, packed=True)
 
 
+# small calls at block lengths that have tuned kernels too: around the limits of 10 steps of 32 rows and 256 workgroups
+# (the text's among them) that send them to the one-pass kernel
+@pytest.mark.parametrize("hq,hkv,B,I,n,m,t", [(28, 4, 1, 16, 256, 103, 200), (28, 4, 1, 32, 256, 154, 1), (32, 32, 1, 1, 576, 320, 0),
+                                              (14, 2, 1, 12, 576, 160, 700), (4, 1, 1, 1, 1024, 320, 5), (2, 2, 8, 7, 256, 31, 9),
+                                              (32, 8, 1, 2, 1024, 160, 129), (8, 8, 2, 3, 576, 97, 257)])
+def test_small_calls_of_tuned_block_lengths(hq, hkv, B, I, n, m, t):
+    before = kv.lib().kvc_dev_stream_calls()
+    decode_case(wl(n, I, B=B, hq=hq, hkv=hkv, t=t), m, packed=True)
+    assert kv.lib().kvc_dev_stream_calls() == before
+
+
+def test_small_ragged_batch_of_a_tuned_block_length():
+    decode_case(wl(256, 5, B=5, hq=14, hkv=2, t=140), 103, ragged=([5, 0, 1, 3, 4], [139, 0, 5, 128, 127]), packed=True)
+
+
 @pytest.mark.parametrize("n,m,packed", [(137, 41, False), (136, 41, True), (600, 100, False), (600, 100, True)])
 def test_ragged_batch_any_shape(n, m, packed):
     decode_case(wl(n, 5, B=5, hq=14, hkv=2, t=140), m, ragged=([5, 0, 1, 3, 4], [139, 0, 5, 128, 127]), packed=packed)
