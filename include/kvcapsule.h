@@ -40,8 +40,8 @@
  *  - The matrix-core (MFMA) kernels cover bf16 with d = 128: compression for n >= 8; the first layer of the
  *    two-layer key reconstructor for m >= 8; decode for n >= 8 and G <= 16.  Decode kernels tuned further, with
  *    scores and weights rounded to bf16 between the steps, serve n in {256, 576, 1024}, G in {1, 2, 4, 6, 7, 8}
- *    and at most 256 partial results per (batch element, KV head); every other decode keeps them at float32
- *    precision.  fp32, and bf16 with another d, run compression and decode on the fp32 matrix instruction
+ *    and at most 256 partial results per (batch element, KV head), save small calls with packed parameters; every
+ *    other decode keeps them at float32 precision.  fp32, and bf16 with another d, run compression and decode on the fp32 matrix instruction
  *    (n >= 4, G <= 16).  What is left runs shape-agnostic scalar kernels: same results within rounding, far
  *    lower speed; their decode is limited to n <= 16384 (KVC_ERR_UNSUPPORTED beyond).
  */

@@ -275,7 +275,7 @@ kvc_status kvc_reconstruct_attend_decode_generic(const kvc_shape *shape, const k
     return generic_decode(c);
 }
 
-// ---- variants that run on the shape-agnostic kernels -------------------------------------------------
+// ---- ragged batches, static variant, hidden rows -------------------------------------------------------
 kvc_status kvc_reconstruct_attend_decode_ragged(const kvc_shape *shape, const kvc_params *params,
                                                 const void *q, const void *Kc, const void *Vc,
                                                 void *K_text, void *V_text, const int32_t *n_images,
