@@ -303,7 +303,7 @@ kvc_status kvc_static_attend_decode(const kvc_shape *shape, const void *q, const
                                     const void *k_new, const void *v_new, float softmax_scale, void *out,
                                     float *lse_out, void *workspace, size_t workspace_bytes, void *stream)
 {
-    // theta, U and mu are not part of this variant; q stands in for them (never read)
+    // theta, U and mu are not part of this variant; q stands in for them (its values never enter a result in their place)
     kvc_params none;
     none.key_idx = nullptr; none.theta = q; none.U = q; none.mu = q; none.theta_packed = nullptr; none.U_packed = nullptr;
     DecodeCall c;
@@ -486,7 +486,7 @@ kvc_status kvc_attend_full_decode(int32_t batch, int32_t n_q_heads, int32_t n_kv
         return KVC_ERR_UNSUPPORTED;
     DecodeCall c;
     c.s = s;
-    c.theta = q; c.U = q; c.mu = q;          // never multiplied by anything but zero without vision tokens
+    c.theta = q; c.U = q; c.mu = q;          // not read without vision tokens
     c.q = q; c.Kc = q; c.Vc = q;
     c.Kt = K; c.Vt = V;
     c.t = t; c.t_in = kv_len; c.cap = kv_cap;

@@ -955,7 +955,8 @@ __global__ __launch_bounds__(128) void fd_finalize(Plan p, const uint16_t *__res
 #pragma unroll
         for (int k = 0; k < PB; ++k) y += sSc[pt0 + k] * cur[k];    // clamped duplicates carry weight zero
     }
-    y += (zv * rz) * bf_lo(mu[static_cast<size_t>(h) * D + c]);
+    const float centre = (zv * rz) * bf_lo(mu[static_cast<size_t>(h) * D + c]);
+    y += nvp > 0 ? centre : 0.f;                // without vision parts mu is no part of the result, whatever it holds
     out[static_cast<size_t>(bg) * D + c] = f32_to_bf16_bits(y);
     if (c == 0 && lse) lse[bg] = mx + __logf(z);
     TS(3, 4);
@@ -1018,7 +1019,7 @@ __global__ __launch_bounds__(128) void fd_finalize_few(const float *__restrict__
     const float rz = 1.f / z;
     const float wgt = a * rz;
     TS(3, 3);
-    float y = (zv * rz) * bf_lo(mub);
+    float y = p.nvp > 0 ? (zv * rz) * bf_lo(mub) : 0.f;   // without vision parts mu is no part of the result, whatever it holds
 #pragma unroll
     for (int k = 0; k < PB; ++k) y += __shfl(wgt, k, 64) * v[k];     // clamped duplicates: weight zero
     out[static_cast<size_t>(bg) * D + c] = f32_to_bf16_bits(y);

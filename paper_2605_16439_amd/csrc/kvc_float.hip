@@ -493,7 +493,7 @@ __global__ __launch_bounds__(256) void gx_merge(const float *__restrict__ Ypart,
     __syncthreads();
     if (static_cast<int>(threadIdx.x) < d) {
         for (int k = 1; k < SL; ++k) y += sY[k * d + c];
-        y += (zv * rz) * to_f(mu[static_cast<size_t>(h) * d + c]);
+        if (nvp > 0) y += (zv * rz) * to_f(mu[static_cast<size_t>(h) * d + c]);
         out[static_cast<size_t>(bg) * d + c] = from_f<T>(y);
     }
     if (threadIdx.x == 0 && lse) lse[bg] = mx + __logf(z);

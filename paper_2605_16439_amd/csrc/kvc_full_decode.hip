@@ -289,8 +289,7 @@ kvc_status fast_full_decode(const FullCall &c)
         static_cast<const uint16_t *>(c.q), static_cast<uint16_t *>(c.K), static_cast<uint16_t *>(c.V),
         static_cast<const uint16_t *>(c.k_new), static_cast<const uint16_t *>(c.v_new), p);
     if (hipGetLastError() != hipSuccess) return KVC_ERR_HIP;
-    // no vision parts: the finalize kernel's "+ (sum P_vis) mu" term is zero; q stands in for mu
-    // (at least H_kv d finite values)
+    // no vision parts: mu is read (q stands in for it, at least H_kv d values) but does not enter the result
     return finalize_parts(p.Ypart, p.NS, 0, p.rec, c.B, c.Hq, c.Hkv, c.q, c.out, c.lse, c.stream);
 }
 

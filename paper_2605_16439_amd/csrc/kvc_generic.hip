@@ -340,7 +340,7 @@ template <class T> kvc_status decode_t(const DecodeCall &c)
     g_output<T><<<B * Hq, kThreads, 0, c.stream>>>(
         w.W, w.Stxt, w.stats, static_cast<const T *>(c.Vc), static_cast<const T *>(c.Vt),
         static_cast<const T *>(c.mu), static_cast<T *>(c.out), c.lse, Hq, Hkv, d, Im, m, t, c.cap,
-        tstride, c.n_images_dev, c.text_len_dev, append, c.static_variant ? 0 : 1);
+        tstride, c.n_images_dev, c.text_len_dev, append, I > 0 && !c.static_variant ? 1 : 0);
     return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_HIP;
 }
 
