@@ -49,6 +49,13 @@ kvc_status kvc_probe_read(const void *buf, size_t bytes, void *sink, void *strea
  * not thread-safe; for sweeps only. */
 void kvc_dev_full_decode_chunk_steps(int32_t steps);
 
+/* Full-cache decode: splits that the rule chooses for `pairs` (batch element, KV head) pairs of `rows` cache rows on
+ * `cus` compute units (host arithmetic; 0 for sizes below one). */
+int32_t kvc_dev_full_decode_splits(int32_t pairs, int32_t rows, int32_t cus);
+
+/* Full-cache decode: workgroups of the split kernel that one compute unit of the current device holds, or -1. */
+int32_t kvc_dev_full_decode_resident(void);
+
 /* Knobs of the matrix-core decode kernels, for tests and sweeps; a negative value leaves a knob as it is.
  * Process-wide, not thread-safe.
  *  row_tiles : 16-row tiles of query rows per workgroup of the third kernel (1, 2, or 4 -- 4 only for

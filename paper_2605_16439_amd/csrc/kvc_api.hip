@@ -499,6 +499,13 @@ kvc_status kvc_attend_full_decode(int32_t batch, int32_t n_q_heads, int32_t n_kv
 
 void kvc_dev_full_decode_chunk_steps(int32_t steps) { full_decode_set_chunk_steps(steps); }
 
+int32_t kvc_dev_full_decode_splits(int32_t pairs, int32_t rows, int32_t cus)
+{
+    return pairs < 1 || rows < 1 || cus < 1 ? 0 : full_decode_splits(pairs, rows, cus);
+}
+
+int32_t kvc_dev_full_decode_resident(void) { return full_decode_resident(); }
+
 void kvc_dev_decode_knobs(int32_t row_tiles, int32_t separate, int32_t wait_ticks)
 {
     fast_decode_knobs(row_tiles, separate, wait_ticks);

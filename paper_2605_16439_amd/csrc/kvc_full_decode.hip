@@ -12,15 +12,18 @@
 //                  from memory; P = exp(S - max) stays in registers and is the B operand of the
 //                  second product as it comes out of the first (the 32 rows of a step are numbered
 //                  the same way on both sides of the contraction); the value rows are transposed
-//                  through a wave-private LDS tile to become its A operand.  Two steps are in flight;
-//                  none beyond the split is requested.  The four waves merge
+//                  through a wave-private LDS tile to become its A operand.  The next step's rows
+//                  are requested before the current step is multiplied.  The four waves merge
 //                  through LDS into one part record.
 //   finalize       the parts of a (batch element, query head) are merged by the finalize kernel of
 //                  the capsule path (a lane per part, shuffles only).
 //
 // Bound: HBM (2 B H_kv (S + 1) d 2 bytes are read once; 4 flop per byte).  B = 4, 28 / 4 heads, 8705 rows, 71 MB:
-// 24.2 us per call with 368 workgroups and requests past a split's end, 20.5 us (3.5 TB/s, the merge launch included)
-// with one workgroup per CU (make_full_plan).
+// 23.3 us per call with 368 workgroups, 18.7 us (3.8 TB/s, the merge launch included) with one per CU
+// (groups_per_split).  Two workgroups fit a CU, and have to: requesting two steps before the loop takes 284 registers
+// instead of 245, one wavefront per SIMD, and calls of more than one workgroup per CU lose by it (us per call, this loop
+// against that: B = 16, 32 / 32 heads, 1001 rows 51.0 / 54.7, 3137 rows 144.1 / 148.7; B = 12, 2001 rows 72.0 / 77.7;
+// the first shape 18.7 / 19.4).
 #include "kvc_internal.h"
 
 #include <algorithm>
@@ -95,9 +98,8 @@ __global__ __launch_bounds__(64 * kWaves) void full_split(const uint16_t *__rest
 
     // steps of this wave
     const int N = max((hi - lo - kRW * wave + kStep - 1) / kStep, 0);
-    u32x4 kA[2][4] = {}, vA[4][2] = {}, kB[2][4] = {}, vB[4][2] = {};
-    if (N > 0) load_tile(0, kA, vA);
-    if (N > 1) load_tile(1, kB, vB);
+    u32x4 kA[2][4], vA[4][2], kB[2][4], vB[4][2];
+    load_tile(0, kA, vA);
     u32x4 qf[4];
     {
         const u32x4 *qp = reinterpret_cast<const u32x4 *>(q + (static_cast<size_t>(b) * p.Hq + h * p.G + min(r16, p.G - 1)) * D) + kg;
@@ -172,17 +174,14 @@ __global__ __launch_bounds__(64 * kWaves) void full_split(const uint16_t *__rest
         __builtin_amdgcn_wave_barrier();
     };
 
-    // Two steps in flight in two register sets; no step is requested that the split does not have.
-    if (N > 0) {
-        int it = 0;
-        for (; it + 2 < N; it += 2) {
-            compute(it, kA, vA);
-            load_tile(it + 2, kA, vA);
-            compute(it + 1, kB, vB);
-            load_tile(min(it + 3, N - 1), kB, vB);
-        }
+    // two steps per round, so that the two register sets swap by name (loads of a step beyond the split repeat its
+    // last row)
+    for (int it = 0; it < N; it += 2) {
+        load_tile(it + 1, kB, vB);
         compute(it, kA, vA);
-        if (it + 1 < N) compute(it + 1, kB, vB);
+        if (it + 1 >= N) break;
+        load_tile(it + 2, kA, vA);
+        compute(it + 1, kB, vB);
     }
 
     // ---- the four waves merge into one part record ------------------------------------------------
@@ -224,6 +223,30 @@ __global__ __launch_bounds__(64 * kWaves) void full_split(const uint16_t *__rest
 
 int g_chunk_steps = 0;            // developer knob: steps of 128 rows per split (0: chosen by the rule below)
 
+// Rows per split, in groups of 32, one wave's step: the choice that minimises rounds of workgroups (one per CU counts as a
+// round) times a split's groups plus 10 for its start and its part record, and 0.15 rounds for the CUs that finish last.
+// Splits, groups per split, us per call: 16 (b, head) pairs of 8705 rows: 16 splits of 18 groups, every CU one workgroup,
+// 19.5; 12 of 23 19.4; 31 of 9 (two per CU) 19.6; 23 of 12 (368 workgroups, some CUs two) 23.2; 8 of 36 (128) 27.6.
+// 256 pairs: 5001 rows 1 split 120.7, 2 115.6 (the 0.15); 1501 rows 40.1 / 39.8; 705 rows 22.3 / 24.7 (the 10).
+// A split is at least a group per wave; the finalize kernel takes at most 64 parts.
+int groups_per_split(long bh, int rows, int cus)
+{
+    const int groups = (rows + kRW - 1) / kRW;
+    int cg = g_chunk_steps * kWaves;
+    if (cg <= 0) {
+        long best = -1;
+        const long first = (bh + cus - 1) / cus;
+        for (long rounds = first; rounds < first + 4; ++rounds) {          // as many splits as fit that many rounds
+            const int ns = static_cast<int>(std::min<long>(rounds * cus / bh, kMaxSplits));
+            const int g = std::max((groups + ns - 1) / ns, kWaves), used = (groups + g - 1) / g;
+            const long cost = ((bh * used + cus - 1) / cus * 20 + 3) * (g + 10);
+            if (best < 0 || cost < best) { best = cost; cg = g; }
+        }
+    }
+    while ((groups + cg - 1) / cg > kMaxSplits) ++cg;
+    return cg;
+}
+
 FullPlan make_full_plan(const FullCall &c, void *ws)
 {
     FullPlan p;
@@ -231,26 +254,7 @@ FullPlan make_full_plan(const FullCall &c, void *ws)
     p.t = c.t; p.t_in = c.t_in;
     p.sb = c.sb; p.sh = c.sh; p.ss = c.ss;
     p.scale = c.scale;
-    // Rows per split, in groups of 32, one wave's step: the choice that minimises rounds of workgroups (one per CU) times
-    // a split's groups plus 10 for its start and its part record.  At t = 8705, 16 (b, head) pairs: 18 groups,
-    // 16 splits, every CU one workgroup 20.5 us; 24 groups (192 workgroups) 21.3; 9 groups (two per CU) 24.5;
-    // 12 groups (368 workgroups, some CUs two) 25.3; 36 groups (128) 27.6; 17 groups (272: 16 CUs take two) 31.2.
-    // A split is at least a group per wave; the finalize kernel takes at most 64 parts.
-    const int groups = (c.t + kRW - 1) / kRW;
-    const long bh = static_cast<long>(c.B) * c.Hkv;
-    int cg = g_chunk_steps * kWaves;
-    if (cg <= 0) {
-        long best = -1;
-        const long first = (bh + c.cus - 1) / c.cus;
-        for (long rounds = first; rounds < first + 4; ++rounds) {          // as many splits as fit that many rounds
-            const int ns = static_cast<int>(std::min<long>(rounds * c.cus / bh, kMaxSplits));
-            const int g = std::max((groups + ns - 1) / ns, kWaves), used = (groups + g - 1) / g;
-            const long cost = (bh * used + c.cus - 1) / c.cus * (g + 10);
-            if (best < 0 || cost < best) { best = cost; cg = g; }
-        }
-    }
-    while ((groups + cg - 1) / cg > kMaxSplits) ++cg;
-    p.chunk = cg * kRW;
+    p.chunk = groups_per_split(static_cast<long>(c.B) * c.Hkv, c.t, c.cus) * kRW;
     p.NS = (c.t + p.chunk - 1) / p.chunk;
     p.rec = static_cast<int>(align_up(static_cast<size_t>(p.G) * D + 2 * p.G, 4));
     p.qNS = quot_multiplier(p.NS);
@@ -262,6 +266,14 @@ FullPlan make_full_plan(const FullCall &c, void *ws)
 }  // namespace
 
 void full_decode_set_chunk_steps(int steps) { g_chunk_steps = steps; }
+int full_decode_splits(long bh, int rows, int cus) { const int cg = groups_per_split(bh, rows, cus); return ((rows + kRW - 1) / kRW + cg - 1) / cg; }
+int full_decode_resident()
+{
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, full_split, 64 * kWaves, 0) == hipSuccess) return per_cu;
+    (void)hipGetLastError();
+    return -1;
+}
 
 bool fast_full_supported(int dtype, int head_dim, int G) { return dtype == KVC_BF16 && head_dim == D && G >= 1 && G <= 16; }
 

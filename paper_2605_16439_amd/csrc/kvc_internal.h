@@ -159,6 +159,8 @@ bool fast_full_supported(int dtype, int head_dim, int G);
 size_t fast_full_ws_bytes(int B, int Hq, int Hkv);
 kvc_status fast_full_decode(const FullCall &c);
 void full_decode_set_chunk_steps(int steps);
+int full_decode_splits(long bh, int rows, int cus);
+int full_decode_resident();
 // decode for the shapes the tuned kernels are not compiled for, bf16, head_dim 128: true when the call was taken
 bool any_decode_supported(const kvc_shape &s);
 size_t any_decode_ws_bytes(const kvc_shape &s, int32_t max_text);

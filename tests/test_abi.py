@@ -198,3 +198,15 @@ def test_pack_u_rejects_bad_arguments_before_any_launch():
     assert L.kvc_pack_u(ctypes.byref(odd), fake, fake2, None) == kv.KVC_ERR_UNSUPPORTED
     bad = kv.KvcParams(p.key_idx, p.theta, p.U, p.mu, None, 0x50004)
     assert _decode(s, bad) == kv.KVC_ERR_ALIGN
+
+
+def test_full_decode_splits_of_the_cost_rule():
+    """The rule's choices at sizes whose times stand beside it: few pairs fill the compute units once; a pair per
+    compute unit is split from some thousand rows on; never more than 64 splits, none shorter than 128 rows."""
+    f = kv.lib().kvc_dev_full_decode_splits
+    assert f(16, 8705, 256) == 16 and f(256, 705, 256) == 1 and f(256, 1501, 256) == 1 and f(256, 5001, 256) == 2
+    assert f(384, 2001, 256) == 2 and f(64, 4097, 256) == 4 and f(4, 40001, 256) == 63
+    for pairs in (1, 7, 255, 257, 5000):
+        for rows in (1, 127, 129, 4096, 1 << 20):
+            assert 1 <= f(pairs, rows, 256) <= min(64, -(-rows // 128))
+    assert f(0, 5, 256) == f(5, 0, 256) == f(5, 5, 0) == 0

@@ -121,6 +121,12 @@ def test_full_decode_rows_per_split(B, hq, hkv, kv_len):
     run_case(73, B, hq, hkv, 128, kv_len, steps=2)
 
 
+def test_full_decode_two_workgroups_fit_a_compute_unit():
+    """Large caches run more than one workgroup per compute unit; a split kernel that has to run them one after the
+    other loses up to 9 %."""
+    assert kv.lib().kvc_dev_full_decode_resident() >= 2
+
+
 def test_full_decode_scalar_path_fp32_and_other_head_dim():
     run_case(70, 2, 6, 3, 64, 150, steps=2, dtype=torch.float32)
     run_case(71, 1, 4, 2, 64, 90, steps=1, dtype=torch.bfloat16)
