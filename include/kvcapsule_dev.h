@@ -76,6 +76,15 @@ void kvc_dev_stream_decode(int32_t mode);
 /* Decode calls the one-pass kernel has served since the library was loaded (host-side count). */
 int64_t kvc_dev_stream_calls(void);
 
+/* Decode calls that the one-pass kernel for other block lengths and for small calls has served (host-side count). */
+int64_t kvc_dev_any_calls(void);
+
+/* How that kernel (kernel = 0), or the one on the fp32 matrix instruction (1), divides a decode call of this shape with
+ * text_len attended rows in a text cache of text_cap rows: plan = { positions per slice, image blocks per tile, tiles per
+ * workgroup, slices, vision workgroups, text runs, steps of 128 rows per run of a full text cache, 1 if a call with packed parameters
+ * takes kernel 0 also where tuned kernels serve the shape }.  Host arithmetic; returns 0 if it does not serve the shape. */
+int32_t kvc_dev_decode_plan(const kvc_shape *shape, int32_t text_len, int32_t text_cap, int32_t kernel, int32_t plan[8]);
+
 /* Workgroups that gave up waiting and computed alone since the library was loaded (current device;
  * synchronises with the device), or -1. */
 int64_t kvc_dev_decode_fallbacks(void);

@@ -28,6 +28,7 @@
 #include "kvc_rows_dev.h"
 
 #include <algorithm>
+#include <atomic>
 
 namespace kvc {
 
@@ -39,12 +40,13 @@ typedef u32x4 u32x4_a2 __attribute__((aligned(2)));     // a 16-byte access at a
 
 constexpr int kGW = 8;                // wavefronts
 constexpr int kMaxVisParts = 48, kMaxTextParts = 16;   // part records per (batch element, KV head): a lane each in the merge
+constexpr int kTextStep = kSR * kSW;  // text rows of a workgroup's step; run r takes the steps r, r + 16, r + 32, ...
 
 struct GPlan {
     int B, Hq, Hkv, G, I, n, m, KS;
     int PS, UP, NUT, NUG, F;          // positions per slice, image blocks per tile, tiles per workgroup, unit groups per sequence, slices
     int NGR, chunk, nvis;             // (head, sequence, unit group) groups, groups per XCD, vision workgroups
-    int NTX, cst, nparts, rec;        // text runs per (batch element, KV head), steps of 128 rows per run
+    int NTX, NTC, nparts, rec;        // text runs per (batch element, KV head), those of a cache filled to its capacity
     int t, t_in, cap;
     unsigned qF, qBU, qNUG, qT, qNTX, qHkv, qKS;
     float scale;
@@ -184,7 +186,7 @@ __global__ __launch_bounds__(64 * kGW) void ga_pass(const uint16_t *__restrict__
             t_in = min(tlb, p.t_in);
             t = fresh ? t_in + 1 : min(tlb, p.t);
         }
-        const int s0 = tc * p.cst * kSW;
+        const int s0 = tc * kSW;
         float m_run = -INFINITY, l_run = 0.f;
         f32x4 acc[8];
 #pragma unroll
@@ -198,13 +200,13 @@ __global__ __launch_bounds__(64 * kGW) void ga_pass(const uint16_t *__restrict__
 #pragma unroll
             for (int k = 0; k < 4; ++k) qf[k] = qp[4 * k];
             Rows rw;
-            rw.I = 0; rw.m = 8; rw.KS = 1; rw.SV = 0; rw.qKS = 0; rw.t = t; rw.cs = p.cst; rw.scale = p.scale;
-            walk<true>(rw, Ktb, Vtb, kn, vn, fresh ? t_in : -1, qf, s0, sVt[wave], m_run, l_run, acc);
+            rw.I = 0; rw.m = 8; rw.KS = 1; rw.SV = 0; rw.qKS = 0; rw.t = t; rw.cs = 1 << 30; rw.scale = p.scale;
+            walk<true, kSW * kMaxTextParts>(rw, Ktb, Vtb, kn, vn, fresh ? t_in : -1, qf, s0, sVt[wave], m_run, l_run, acc);
         }
         merge_waves(sVt, sM, sL, m_run, l_run, acc, G,
                     p.Ypart + (static_cast<size_t>(bh) * p.nparts + p.NUG * p.F + tc) * p.rec);
         // Sec. 3.2: the text cache keeps growing as in the backbone -- store the new token's k, v
-        if (fresh && t_in >= kSR * s0 && t_in < kSR * (s0 + kSW * p.cst) && threadIdx.x < 32) {
+        if (fresh && static_cast<unsigned>(t_in) / kTextStep % kMaxTextParts == static_cast<unsigned>(tc) && threadIdx.x < 32) {
             const int half = threadIdx.x >> 4, piece = threadIdx.x & 15;
             uint16_t *dst = (half ? Vtb : Ktb) + static_cast<size_t>(t_in) * D;
             *(reinterpret_cast<u32x4 *>(dst) + piece) = *(reinterpret_cast<const u32x4 *>(half ? vn : kn) + piece);
@@ -644,8 +646,12 @@ __global__ __launch_bounds__(64 * kGW) void ga_pass(const uint16_t *__restrict__
 
 constexpr size_t kPassLds = 156 * 1024;
 constexpr int kOneEach = 256;         // workgroups that find a compute unit each
+std::atomic<long> g_any_calls{0};     // debug counter (kvc_dev_any_calls)
 
-// false: no plan (slices or LDS beyond what the kernel holds)
+// false: no plan (slices or LDS beyond what the kernel holds).  What decides the order of the sums -- slices, tiles, the
+// text run that a row belongs to -- follows from the shape and the capacity of the text cache, not from the rows that it
+// holds: a ragged batch, whose row counts the host does not know, computes what the uniform call computes, bit for bit
+// (runs without a row add zeros), and a generation keeps one order from its first token to its last.
 bool make_gplan(GPlan &p, const kvc_shape &s, int t, int t_in, int cap)
 {
     p.B = s.batch; p.Hq = s.n_q_heads; p.Hkv = s.n_kv_heads; p.G = p.Hq / p.Hkv;
@@ -665,13 +671,13 @@ bool make_gplan(GPlan &p, const kvc_shape &s, int t, int t_in, int cap)
     p.PS = ps;
     p.F = (p.n + ps - 1) / ps;
     if (p.F > kMaxVisParts || pass_lds(p.m, ps, false) > kPassLds) return false;
-    const int steps = (t + kSR * kSW - 1) / (kSR * kSW);
-    p.cst = std::max(1, (steps + kMaxTextParts - 1) / kMaxTextParts);
-    p.NTX = (steps + p.cst - 1) / p.cst;
+    auto runs = [](int rows) { return std::min((rows + kTextStep - 1) / kTextStep, kMaxTextParts); };
+    p.NTX = runs(t);
+    p.NTC = runs(cap);
     // smaller tiles as long as every workgroup, those of the text with them, still has a compute unit to itself and one
     // tile: 12 blocks of n = 576, m = 346, B = 1, 12/2 heads, two tiles per workgroup 24.6 us, one twice as full 20.5
     if (ps == 128)
-        for (int up = (p.UP + 1) / 2; p.UP > 1 && groups(up) * p.F + bh * p.NTX <= kOneEach && (p.I + up - 1) / up * p.F <= kMaxVisParts;
+        for (int up = (p.UP + 1) / 2; p.UP > 1 && groups(up) * p.F + bh * p.NTC <= kOneEach && (p.I + up - 1) / up * p.F <= kMaxVisParts;
              up = (p.UP + 1) / 2)
             p.UP = up;
     const int tiles = (p.I + p.UP - 1) / p.UP, ug_max = kMaxVisParts / p.F;
@@ -688,7 +694,7 @@ bool make_gplan(GPlan &p, const kvc_shape &s, int t, int t_in, int cap)
     // quot(): dividends below 2^32 / divisor; 32-bit offsets into a head's theta and U
     const long lim = 1l << 31;
     return p.nparts >= 1 && static_cast<long>(p.nvis) * std::max(p.F, p.B * std::max(p.NUG, 1)) < lim &&
-           bh * p.NTX * std::max(std::max(p.NTX, 1), p.Hkv) < lim && static_cast<long>(16) * 2 * p.KS * 2 * p.KS < lim &&
+           bh * p.NTC * std::max(std::max(p.NTC, 1), p.Hkv) < lim && static_cast<long>(16) * 2 * p.KS * 2 * p.KS < lim &&
            static_cast<long>(p.KS) * 64 * p.n < lim;
 }
 
@@ -714,37 +720,55 @@ template <int NPW> bool launch_g(const GPlan &p, const DecodeCall &c)
 
 }  // namespace
 
+static bool any_shape(const kvc_shape &s)
+{
+    return s.dtype == KVC_BF16 && s.head_dim == D && s.n_q_heads / s.n_kv_heads <= 16 && s.n_img_tokens >= 8;
+}
+
+// Calls of shapes with tuned kernels that take less time here: a compute unit for every workgroup, the text's among them, at
+// most 10 steps of 32 compressed rows per workgroup, whose chains are its time.  us per layer, tuned kernels against this pass: n = 256, m = 154, 16 blocks, 28/4 heads 16.5 / 11.5, 32 blocks (10 steps) 16.6 / 14.0;
+// n = 576, m = 144, 5 blocks 14.9 / 12.0, 12 blocks (10 steps) 14.9 / 13.1; n = 1024, m = 256, one block 14.6 / 12.6, 8 blocks
+// (16 steps) 13.3 / 16.5; m = 615 (20 steps) 19.5 / 21.4.
+static bool small_call(const GPlan &p)
+{
+    return p.I > 0 && p.NUT == 1 && p.UP * p.KS <= 10 &&
+           static_cast<long>(p.NGR) * p.F + static_cast<long>(p.B) * p.Hkv * p.NTC <= kOneEach;
+}
+
 bool any_decode_supported(const kvc_shape &s)
 {
     GPlan p;
-    return s.dtype == KVC_BF16 && s.head_dim == D && s.n_q_heads / s.n_kv_heads <= 16 && s.n_img_tokens >= 8 && make_gplan(p, s, 1, 0, 1);
+    return any_shape(s) && make_gplan(p, s, 1, 0, 1);
 }
 
 size_t any_decode_ws_bytes(const kvc_shape &s, int32_t max_text)
 {
-    // (tiles, and with them the part records, are smallest and most where the text is short)
+    // (tiles, and with them the part records, are smallest and most where the text cache is small)
     GPlan p;
-    if (!make_gplan(p, s, s.n_images > 0 ? 0 : 1, 0, max_text)) return 0;
-    // (the number of text parts does not grow monotonically with the text length: its bound is taken)
-    const int ntx = std::min((std::max(max_text, 1) + kSR * kSW - 1) / (kSR * kSW), kMaxTextParts);
+    const int none = s.n_images > 0 ? 0 : 1;
+    if (!make_gplan(p, s, none, 0, none)) return 0;
+    const int ntx = std::min((std::max(max_text, 1) + kTextStep - 1) / kTextStep, kMaxTextParts);
     return static_cast<size_t>(p.B) * p.Hkv * (p.NUG * p.F + ntx) * p.rec * sizeof(float) + kTimelineBytes;
 }
 
-bool any_decode_preferred(const DecodeCall &c)
+bool any_decode_plan(const kvc_shape &s, int t, int cap, int32_t *plan)
 {
     GPlan p;
-    return c.theta_packed && c.U_packed && !c.static_variant && c.s.dtype == KVC_BF16 && c.s.head_dim == D &&
-           c.s.n_q_heads / c.s.n_kv_heads <= 16 && c.s.n_img_tokens >= 8 && c.s.n_images > 0 &&
-           make_gplan(p, c.s, c.t, c.t_in, c.cap) && p.NUT == 1 && p.UP * p.KS <= 10 &&
-           static_cast<long>(p.NGR) * p.F + static_cast<long>(p.B) * p.Hkv * p.NTX <= kOneEach;
+    if (!any_shape(s) || !make_gplan(p, s, t, t, cap)) return false;
+    const int32_t v[8] = {p.PS, p.UP, p.NUT, p.F, p.NGR * p.F, p.NTX, (cap + kMaxTextParts * kTextStep - 1) / (kMaxTextParts * kTextStep), small_call(p)};
+    std::copy(v, v + 8, plan);
+    return true;
 }
 
-bool any_decode(const DecodeCall &c, kvc_status *st)
+long any_decode_calls() { return g_any_calls.load(); }
+
+bool any_decode(const DecodeCall &c, kvc_status *st, bool small_only)
 {
-    if (c.static_variant || !any_decode_supported(c.s)) return false;
+    if (c.static_variant || !any_shape(c.s)) return false;
     if ((c.n_images_dev == nullptr) != (c.text_len_dev == nullptr)) return false;
     GPlan p;
     if (!make_gplan(p, c.s, c.t, c.t_in, c.cap)) return false;
+    if (small_only && !(c.theta_packed && c.U_packed && small_call(p))) return false;
     if (static_cast<size_t>(p.B) * p.Hkv * p.nparts * p.rec * sizeof(float) > c.ws_bytes) return false;
     p.scale = c.scale;
     p.Ypart = static_cast<float *>(c.ws);
@@ -753,6 +777,7 @@ bool any_decode(const DecodeCall &c, kvc_status *st)
     p.tl = reinterpret_cast<unsigned long long *>(static_cast<char *>(c.ws) + ((c.ws_bytes - kTimelineBytes) & ~size_t(255)));
 #endif
     const bool ok = p.PS == 512 ? launch_g<4>(p, c) : p.PS == 256 ? launch_g<2>(p, c) : launch_g<1>(p, c);
+    if (ok) ++g_any_calls;
     *st = ok && hipGetLastError() == hipSuccess
               ? finalize_parts(p.Ypart, p.nparts, p.NUG * p.F, p.rec, p.B, p.Hq, p.Hkv, c.mu, c.out, c.lse, c.stream)
               : KVC_ERR_HIP;

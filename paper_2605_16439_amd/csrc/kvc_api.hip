@@ -134,13 +134,9 @@ kvc_status prepare_compress(CompressCall &c, const kvc_shape *shape, const kvc_p
 kvc_status dispatch_decode(const DecodeCall &c)
 {
     kvc_status st = KVC_OK;
-    // Small calls with packed parameters: one latency-bound pass, with float32 weights, instead of three or four launches.
-    // "Small": a compute unit for every workgroup of that pass, and at most 10 steps of 32 compressed rows per workgroup,
-    // whose chains are its time (us per layer, tuned kernels against this pass: n = 256, m = 154, 16 blocks, 28/4 heads 16.5 / 11.5,
-    // 32 blocks (10 steps) 16.6 / 14.0; n = 576, m = 144, 5 blocks 14.9 / 12.0, 12 blocks (10 steps) 14.9 / 13.1; n = 1024,
-    // m = 256, one block 14.6 / 12.6, 8 blocks (16 steps) 13.3 / 16.5; m = 615 (20 steps) 19.5 / 21.4).  With plain parameters
-    // these shapes stay on the tuned kernels.
-    if (fast_decode_default() && any_decode_preferred(c) && any_decode(c, &st)) return st;
+    // small calls with packed parameters: one latency-bound pass, with float32 weights, instead of three or four launches
+    // (small_call in kvc_any_decode.hip); with plain parameters these shapes stay on the tuned kernels
+    if (fast_decode_default() && any_decode(c, &st, true)) return st;
     if (stream_decode(c, &st)) return st;
     if (fast_decode_supported(c.s)) return fast_decode(c);
     return other_decode(c);
@@ -171,7 +167,7 @@ namespace kvc {
 kvc_status other_decode(const DecodeCall &c)
 {
     kvc_status st = KVC_OK;
-    return any_decode(c, &st) || float_decode(c, &st) ? st : generic_decode(c);
+    return any_decode(c, &st, false) || float_decode(c, &st) ? st : generic_decode(c);
 }
 }  // namespace kvc
 
@@ -516,6 +512,14 @@ int64_t kvc_dev_decode_fallbacks(void) { return fast_decode_fallbacks(); }
 void kvc_dev_stream_decode(int32_t mode) { stream_decode_knob(mode); }
 
 int64_t kvc_dev_stream_calls(void) { return stream_decode_calls(); }
+
+int64_t kvc_dev_any_calls(void) { return any_decode_calls(); }
+
+int32_t kvc_dev_decode_plan(const kvc_shape *shape, int32_t text_len, int32_t text_cap, int32_t kernel, int32_t plan[8])
+{
+    if (check_shape(shape) != KVC_OK || !plan || text_len < 0 || text_len > text_cap) return 0;
+    return kernel == 0 ? any_decode_plan(*shape, text_len, text_cap, plan) : float_decode_plan(*shape, text_len, text_cap, plan);
+}
 
 void kvc_dev_compress_knobs(int32_t waves, int32_t jt) { fast_compress_knobs(waves, jt); }
 

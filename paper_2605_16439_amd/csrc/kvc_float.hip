@@ -30,7 +30,7 @@ namespace {
 
 constexpr int kXW = 8;                // wavefronts
 constexpr int kVisParts = 48, kTextParts = 16;     // part records per (batch element, KV head): a lane each in the merge
-constexpr int kTR = 16 * kXW;         // text rows per step
+constexpr int kTR = 16 * kXW;         // text rows per step; run r takes the steps r, r + 16, r + 32, ...
 
 // four consecutive elements at any element-aligned address
 template <class T> struct Vec4;
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(64 * kXW) void gx_project(const T *__restrict__ K, 
 struct XPlan {
     int B, Hq, Hkv, G, I, n, m, d, KB;                  // KB: 32-row steps of the compressed axis
     int UP, NUT, NUG, F, NP;                            // image blocks per tile, tiles per workgroup, unit groups, slices, position tiles per wavefront
-    int NTX, cst, nparts, rec, nvis;
+    int NTX, nparts, rec, nvis;
     int t, t_in, cap;
     unsigned qF, qNUG, qHkv, qNTX, qT;
     float scale;
@@ -226,8 +226,8 @@ __global__ __launch_bounds__(64 * kXW) void gx_pass(const T *__restrict__ q, con
         }
         const T *kn = fresh ? k_new + static_cast<size_t>(bh) * d : q, *vn = fresh ? v_new + static_cast<size_t>(bh) * d : q;
         T *Ktb = Kt + static_cast<size_t>(bh) * p.cap * d, *Vtb = Vt + static_cast<size_t>(bh) * p.cap * d;
-        const int t_new = fresh ? t_in : -1, x_lo = tc * p.cst * kTR, x_hi = min(t, x_lo + p.cst * kTR);
-        for (int x0 = x_lo; x0 < x_hi; x0 += kTR) {       // (a run that a shorter sequence does not have: nothing)
+        const int t_new = fresh ? t_in : -1;
+        for (int x0 = tc * kTR; x0 < t; x0 += kTR * kTextParts) {       // (a run that a shorter sequence does not have: nothing)
             const int xr = min(x0 + 16 * wave + r16, t - 1);
             const f32x4 a = score(xr == t_new ? kn : Ktb + static_cast<size_t>(xr) * d);
             f32x4 l;
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(64 * kXW) void gx_pass(const T *__restrict__ q, con
             __syncthreads();                              // the weights have been read
         }
         // Sec. 3.2: the text cache keeps growing as in the backbone -- store the new token's k, v
-        if (fresh && t_in >= x_lo && t_in < x_lo + p.cst * kTR)
+        if (fresh && static_cast<unsigned>(t_in) / kTR % kTextParts == static_cast<unsigned>(tc))
             for (int c = threadIdx.x; c < d; c += 64 * kXW) {
                 Ktb[static_cast<size_t>(t_in) * d + c] = kn[c];
                 Vtb[static_cast<size_t>(t_in) * d + c] = vn[c];
@@ -501,6 +501,8 @@ __global__ __launch_bounds__(256) void gx_merge(const float *__restrict__ Ypart,
 
 constexpr size_t kXLds = 156 * 1024;
 
+// What decides the order of the sums does not depend on the rows in the text cache: a ragged batch equals the uniform call
+// bit for bit.
 bool make_xplan(XPlan &p, const kvc_shape &s, int t, int t_in, int cap)
 {
     p.B = s.batch; p.Hq = s.n_q_heads; p.Hkv = s.n_kv_heads; p.G = p.Hq / p.Hkv;
@@ -522,9 +524,7 @@ bool make_xplan(XPlan &p, const kvc_shape &s, int t, int t_in, int cap)
     p.NUT = p.I > 0 ? (tiles + ug_max - 1) / ug_max : 1;
     p.NUG = p.I > 0 ? (tiles + p.NUT - 1) / p.NUT : 0;
     p.nvis = static_cast<int>(std::min(bh * p.NUG * p.F, 1l << 30));
-    const int steps = (t + kTR - 1) / kTR;
-    p.cst = std::max(1, (steps + kTextParts - 1) / kTextParts);
-    p.NTX = (steps + p.cst - 1) / p.cst;
+    p.NTX = std::min((t + kTR - 1) / kTR, kTextParts);
     p.nparts = p.NUG * p.F + p.NTX;
     p.rec = static_cast<int>(align_up(p.G * p.d + 2 * p.G, 4));
     p.qF = quot_multiplier(p.F); p.qNUG = quot_multiplier(p.NUG); p.qHkv = quot_multiplier(p.Hkv);
@@ -589,9 +589,18 @@ bool float_compress(const CompressCall &c, kvc_status *st)
 size_t float_decode_ws_bytes(const kvc_shape &s, int32_t max_text)
 {
     XPlan p;
-    if (!make_xplan(p, s, std::max(max_text, 1), 0, max_text)) return 0;
+    if (!make_xplan(p, s, std::max(max_text, 1), 0, std::max(max_text, 1))) return 0;
     const int ntx = std::min((std::max(max_text, 1) + kTR - 1) / kTR, kTextParts);
     return static_cast<size_t>(p.B) * p.Hkv * (p.NUG * p.F + ntx) * p.rec * sizeof(float);
+}
+
+bool float_decode_plan(const kvc_shape &s, int t, int cap, int32_t *plan)
+{
+    XPlan p;
+    if (!make_xplan(p, s, t, t, cap)) return false;
+    const int32_t v[8] = {64 * p.NP, p.UP, p.NUT, p.F, p.nvis, p.NTX, (cap + kTR * kTextParts - 1) / (kTR * kTextParts), 0};
+    std::copy(v, v + 8, plan);
+    return true;
 }
 
 bool float_decode(const DecodeCall &c, kvc_status *st)

@@ -164,13 +164,16 @@ int full_decode_resident();
 // decode for the shapes the tuned kernels are not compiled for, bf16, head_dim 128: true when the call was taken
 bool any_decode_supported(const kvc_shape &s);
 size_t any_decode_ws_bytes(const kvc_shape &s, int32_t max_text);
-bool any_decode(const DecodeCall &c, kvc_status *st);
-bool any_decode_preferred(const DecodeCall &c);      // where the tuned kernels would take longer
+// (small_only: only where the tuned kernels of the shape would take longer, which needs the packed parameters)
+bool any_decode(const DecodeCall &c, kvc_status *st, bool small_only);
+bool any_decode_plan(const kvc_shape &s, int t, int cap, int32_t *plan);
+long any_decode_calls();
 bool fast_decode_default();                          // no developer knob of the tuned kernels is set
 // fp32, and bf16 with any head_dim, on the fp32 matrix instruction: true when the call was taken
 bool float_compress(const CompressCall &c, kvc_status *st);
 size_t float_decode_ws_bytes(const kvc_shape &s, int32_t max_text);
 bool float_decode(const DecodeCall &c, kvc_status *st);
+bool float_decode_plan(const kvc_shape &s, int t, int cap, int32_t *plan);
 // those, or the scalar kernels
 kvc_status other_decode(const DecodeCall &c);
 // static variant (attention over the compressed rows themselves), bf16, head_dim 128

@@ -18,7 +18,7 @@ constexpr int kLDO = D + 4;           // floats per head row of a wavefront's ou
 struct Rows {
     int I, m, KS, SV;                 // compressed rows: blocks of m rows, KS 32-row steps each, SV = I KS steps
     int t;                            // rows of the text cache
-    int cs;                           // steps per wavefront and run
+    int cs;                           // steps per wavefront and run, at most
     unsigned qKS;
     float scale;
 };
@@ -48,8 +48,8 @@ __device__ __forceinline__ Split3 split3(const float (&p)[8])
     return r;
 }
 
-// One wavefront's pass over its steps of a run.  TEXT: rows of the text cache, else compressed rows.
-template <bool TEXT>
+// One wavefront's pass over its steps of a run: s0 + wave, then every ST-th.  TEXT: rows of the text cache, else compressed rows.
+template <bool TEXT, int ST>
 __device__ __forceinline__ void walk(const Rows &p, const uint16_t *__restrict__ Kb, const uint16_t *__restrict__ Vb,
                                      const uint16_t *__restrict__ kn, const uint16_t *__restrict__ vn, int t_new,
                                      const u32x4 (&qf)[4], int s0, uint32_t *vt, float &m_run, float &l_run, f32x4 (&acc)[8])
@@ -177,21 +177,21 @@ __device__ __forceinline__ void walk(const Rows &p, const uint16_t *__restrict__
     // Two steps in flight in two register sets.  No step is requested that the run does not have: with runs of one or
     // two steps a request ahead of the end would double what the kernel reads.
     const int all = TEXT ? (p.t + kSR - 1) / kSR : p.SV;
-    const int left_w = min(all - s0, kSW * p.cs) - wave, N = left_w > 0 ? (left_w + kSW - 1) / kSW : 0;
+    const int left_w = all - s0 - wave, N = left_w > 0 ? min(static_cast<int>(static_cast<unsigned>(left_w + ST - 1) / ST), p.cs) : 0;
     if (N == 0) return;
     const int sw = s0 + wave;
     u32x4 kA[2][4], vA[8], kB[2][4] = {}, vB[8] = {};
     load(sw, kA, vA);
-    if (N > 1) load(sw + kSW, kB, vB);
+    if (N > 1) load(sw + ST, kB, vB);
     int it = 0;
     for (; it + 2 < N; it += 2) {
-        compute(sw + kSW * it, kA, vA);
-        load(sw + kSW * (it + 2), kA, vA);
-        compute(sw + kSW * (it + 1), kB, vB);
-        load(sw + kSW * min(it + 3, N - 1), kB, vB);
+        compute(sw + ST * it, kA, vA);
+        load(sw + ST * (it + 2), kA, vA);
+        compute(sw + ST * (it + 1), kB, vB);
+        load(sw + ST * min(it + 3, N - 1), kB, vB);
     }
-    compute(sw + kSW * it, kA, vA);
-    if (it + 1 < N) compute(sw + kSW * (it + 1), kB, vB);
+    compute(sw + ST * it, kA, vA);
+    if (it + 1 < N) compute(sw + ST * (it + 1), kB, vB);
 }
 
 // The kSW wavefronts of a run merge into one part record: [G][D] un-normalised output, [G] maxima, [G] sums.

@@ -68,9 +68,9 @@ __global__ __launch_bounds__(64 * kSW, 2) void static_split(const uint16_t *__re
     const bool text = pt >= p.NV;
     const int s0 = (text ? pt - p.NV : pt) * p.cs * kSW;
     if (text)
-        walk<true>(p, Ktb, Vtb, kn, vn, fresh ? p.t_in : -1, qf, s0, sVt[wave], m_run, l_run, acc);
+        walk<true, kSW>(p, Ktb, Vtb, kn, vn, fresh ? p.t_in : -1, qf, s0, sVt[wave], m_run, l_run, acc);
     else
-        walk<false>(p, Kc + static_cast<size_t>(bh) * p.I * p.m * D, Vc + static_cast<size_t>(bh) * p.I * p.m * D, kn, vn, -1, qf, s0,
+        walk<false, kSW>(p, Kc + static_cast<size_t>(bh) * p.I * p.m * D, Vc + static_cast<size_t>(bh) * p.I * p.m * D, kn, vn, -1, qf, s0,
                     sVt[wave], m_run, l_run, acc);
 
     merge_waves(sVt, sM, sL, m_run, l_run, acc, p.G, p.Ypart + (static_cast<size_t>(bh) * p.NP + pt) * p.rec);

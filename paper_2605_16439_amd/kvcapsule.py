@@ -40,6 +40,7 @@ EXPORTS = [
     "kvc_capsule_value_offset", "kvc_unpack_values",
     "kvc_reconstruct_attend_decode_ragged", "kvc_mlp_hidden", "kvc_static_attend_decode",
     "kvc_pack_theta", "kvc_pack_u", "kvc_dev_stream_decode", "kvc_dev_stream_calls",
+    "kvc_dev_any_calls", "kvc_dev_decode_plan",
 ]
 
 
@@ -129,6 +130,10 @@ def lib() -> ctypes.CDLL:
         L.kvc_dev_stream_decode.argtypes = [i32]
         L.kvc_dev_stream_calls.restype = i64
         L.kvc_dev_stream_calls.argtypes = []
+        L.kvc_dev_any_calls.restype = i64
+        L.kvc_dev_any_calls.argtypes = []
+        L.kvc_dev_decode_plan.restype = i32
+        L.kvc_dev_decode_plan.argtypes = [ctypes.POINTER(KvcShape), i32, i32, i32, ctypes.POINTER(i32)]
         L.kvc_capsule_value_offset.restype = i64
         L.kvc_capsule_value_offset.argtypes = [i32, i32, i32, i32]
         L.kvc_unpack_values.restype = i32

@@ -210,3 +210,37 @@ def test_full_decode_splits_of_the_cost_rule():
         for rows in (1, 127, 129, 4096, 1 << 20):
             assert 1 <= f(pairs, rows, 256) <= min(64, -(-rows // 128))
     assert f(0, 5, 256) == f(5, 0, 256) == f(5, 5, 0) == 0
+
+
+def decode_plan(hq, hkv, B, I, n, m, t, cap, kernel=0, dtype=kv.KVC_BF16, d=128):
+    """(positions per slice, image blocks per tile, tiles per workgroup, slices, vision workgroups, text runs, steps per run,
+    small call) or None."""
+    plan = (ctypes.c_int32 * 8)()
+    ok = kv.lib().kvc_dev_decode_plan(ctypes.byref(kv.make_shape(B, hq, hkv, d, n, I, m, dtype)), t, cap, kernel, plan)
+    return tuple(plan) if ok else None
+
+
+@pytest.mark.parametrize("kernel,dtype,d", [(0, kv.KVC_BF16, 128), (1, kv.KVC_F32, 64)])
+@pytest.mark.parametrize("hq,hkv,B,I,n,m", [(14, 2, 16, 1, 256, 103), (14, 2, 5, 5, 137, 41), (28, 4, 1, 16, 256, 103), (28, 4, 4, 8, 1024, 410),
+                                            (32, 32, 1, 1, 576, 231), (2, 1, 1, 64, 515, 65)])
+def test_plan_follows_from_the_capacity_of_the_text_cache(hq, hkv, B, I, n, m, kernel, dtype, d):
+    """Whatever decides the order of the sums is the same for every number of rows in the cache: from the first token of
+    a generation to the last, and for a ragged batch, whose counts the host does not know."""
+    for cap in (1, 130, 2000, 2049, 9000, 40000):
+        full = decode_plan(hq, hkv, B, I, n, m, cap, cap, kernel, dtype, d)
+        for t in {1, cap // 3, cap}:
+            p = decode_plan(hq, hkv, B, I, n, m, t, cap, kernel, dtype, d)
+            assert p[:5] == full[:5] and p[6:] == full[6:]
+            assert p[5] == min(-(-t // 128), 16) and p[6] == -(-cap // 2048)
+
+
+def test_small_calls_of_tuned_block_lengths_and_those_just_beyond():
+    """10 steps of 32 rows, 256 workgroups with the text's among them."""
+    small = lambda *a: decode_plan(*a)[7]
+    assert small(32, 32, 1, 1, 576, 320, 1, 64) and not small(32, 32, 1, 1, 576, 321, 1, 64)           # 10 / 11 steps
+    assert small(28, 4, 1, 32, 256, 154, 1, 64) and not small(28, 4, 1, 64, 256, 154, 1, 64)           # one tile / several per workgroup
+    # 32 pairs x 2 slices, and 32 workgroups per 128 rows of capacity
+    assert small(14, 2, 16, 1, 256, 103, 1, 768) and not small(14, 2, 16, 1, 256, 103, 1, 769)
+    assert not small(28, 4, 1, 0, 256, 103, 1, 64)
+    assert decode_plan(34, 2, 1, 1, 256, 103, 1, 64) is None and decode_plan(4, 2, 1, 1, 7, 3, 1, 64) is None
+    assert kv.lib().kvc_dev_decode_plan(None, 1, 1, 0, None) == 0

@@ -233,3 +233,32 @@ def test_ragged_batch_fp32(d):
                                                      f64(kn), f64(vn))
     e = np.linalg.norm(f64(L.out) - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
     assert e.max() <= 1e-5 and np.abs(f64(L.lse) - lref).max() <= 1e-4
+
+
+# A ragged batch plans for the text cache's capacity, as the uniform call does: small calls that would take other kernels,
+# tiles of other sizes and text runs of another length if the rows in the cache decided
+@pytest.mark.parametrize("hq,hkv,B,I,n,m,t,cap,dtype,d", [
+    (14, 2, 16, 1, 256, 103, 100, 2000, "bf16", 128), (14, 2, 5, 5, 137, 41, 100, 2000, "bf16", 128), (28, 4, 1, 3, 256, 60, 30, 500, "bf16", 128),
+    (14, 2, 2, 3, 137, 41, 1500, 5000, "bf16", 128), (8, 2, 2, 2, 150, 33, 1500, 5000, "f32", 64), (8, 2, 2, 0, 150, 33, 700, 2100, "f32", 64)])
+def test_uniform_batch_through_the_ragged_entry_point(hq, hkv, B, I, n, m, t, cap, dtype, d):
+    w = synth.Workload("rag_eq", 95, 1, B, hq, hkv, d, dtype, n, I, 0.6, t, cap - t)
+    assert w.text_cap == cap
+    res = []
+    for ragged in (False, True):
+        L = Layer(w, m)
+        g = torch.Generator().manual_seed(m)
+        L.gKc, L.gVc = (torch.randn(L.gKc.shape, generator=g).to(L.gKc.dtype).to(DEV) for _ in range(2))
+        if n % 8 == 0:
+            L.params = kv.make_params(L.g["key_idx"], L.g["theta"], L.g["U"], L.g["mu"], kv.kvc_pack_theta(L.shape, L.g["theta"]),
+                                      kv.kvc_pack_u(L.shape, L.g["U"]))
+        q, kn, vn = (x.to(DEV) for x in synth.make_step_inputs(w, 0, 0))
+        print(f"[any] uniform call, ragged={ragged}: {hq}/{hkv} B={B} n={n} m={m} I={I} t={t} cap={cap} {dtype}", flush=True)
+        if ragged:
+            counts = [torch.full((B,), x, dtype=torch.int32, device=DEV) for x in (I, t)]
+            kv.kvc_reconstruct_attend_decode_ragged(L.shape, L.params, q, L.gKc, L.gVc, L.gKt, L.gVt, *counts, cap, kn, vn, 0.0, L.out,
+                                                    L.lse, L.ws)
+            torch.cuda.synchronize()
+            res.append((f64(L.out), f64(L.lse)))
+        else:
+            res.append(L.decode(q, t, kn, vn))
+    assert np.array_equal(res[0][0], res[1][0]) and np.array_equal(res[0][1], res[1][1])
