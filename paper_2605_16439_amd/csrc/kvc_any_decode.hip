@@ -726,12 +726,15 @@ static bool any_shape(const kvc_shape &s)
 }
 
 // Calls of shapes with tuned kernels that take less time here: a compute unit for every workgroup, the text's among them, at
-// most 10 steps of 32 compressed rows per workgroup, whose chains are its time.  us per layer, tuned kernels against this pass: n = 256, m = 154, 16 blocks, 28/4 heads 16.5 / 11.5, 32 blocks (10 steps) 16.6 / 14.0;
+// most 10 steps of 32 compressed rows per workgroup, whose chains are its time, and text runs of at most 4 steps.  us per
+// layer, tuned kernels against this pass: n = 256, m = 154, 16 blocks, 28/4 heads 16.5 / 11.5, 32 blocks (10 steps) 16.6 / 14.0;
 // n = 576, m = 144, 5 blocks 14.9 / 12.0, 12 blocks (10 steps) 14.9 / 13.1; n = 1024, m = 256, one block 14.6 / 12.6, 8 blocks
-// (16 steps) 13.3 / 16.5; m = 615 (20 steps) 19.5 / 21.4.
+// (16 steps) 13.3 / 16.5; m = 615 (20 steps) 19.5 / 21.4.  Text rows at n = 256, m = 103, 2 blocks, 28/4 heads, B = 1:
+// 4000 16.0 / 12.0, 8000 (4 steps per run) 18.5 / 17.7, 16000 20.7 / 27.2, 28000 26.7 / 41.3: the tuned kernels give every
+// 128 rows a workgroup.
 static bool small_call(const GPlan &p)
 {
-    return p.I > 0 && p.NUT == 1 && p.UP * p.KS <= 10 &&
+    return p.I > 0 && p.NUT == 1 && p.UP * p.KS <= 10 && p.cap <= 4 * kMaxTextParts * kTextStep &&
            static_cast<long>(p.NGR) * p.F + static_cast<long>(p.B) * p.Hkv * p.NTC <= kOneEach;
 }
 

@@ -235,12 +235,13 @@ def test_plan_follows_from_the_capacity_of_the_text_cache(hq, hkv, B, I, n, m, k
 
 
 def test_small_calls_of_tuned_block_lengths_and_those_just_beyond():
-    """10 steps of 32 rows, 256 workgroups with the text's among them."""
+    """10 steps of 32 rows, 256 workgroups with the text's among them, text runs of 4 steps of 128 rows."""
     small = lambda *a: decode_plan(*a)[7]
     assert small(32, 32, 1, 1, 576, 320, 1, 64) and not small(32, 32, 1, 1, 576, 321, 1, 64)           # 10 / 11 steps
     assert small(28, 4, 1, 32, 256, 154, 1, 64) and not small(28, 4, 1, 64, 256, 154, 1, 64)           # one tile / several per workgroup
     # 32 pairs x 2 slices, and 32 workgroups per 128 rows of capacity
     assert small(14, 2, 16, 1, 256, 103, 1, 768) and not small(14, 2, 16, 1, 256, 103, 1, 769)
+    assert small(28, 4, 1, 2, 256, 103, 1, 8192) and not small(28, 4, 1, 2, 256, 103, 1, 8193)         # 4 / 5 steps per text run
     assert not small(28, 4, 1, 0, 256, 103, 1, 64)
     assert decode_plan(34, 2, 1, 1, 256, 103, 1, 64) is None and decode_plan(4, 2, 1, 1, 7, 3, 1, 64) is None
     assert kv.lib().kvc_dev_decode_plan(None, 1, 1, 0, None) == 0
