@@ -751,7 +751,7 @@ size_t any_decode_ws_bytes(const kvc_shape &s, int32_t max_text)
     const int none = s.n_images > 0 ? 0 : 1;
     if (!make_gplan(p, s, none, 0, none)) return 0;
     const int ntx = std::min((std::max(max_text, 1) + kTextStep - 1) / kTextStep, kMaxTextParts);
-    return static_cast<size_t>(p.B) * p.Hkv * (p.NUG * p.F + ntx) * p.rec * sizeof(float) + kTimelineBytes;
+    return kCounterBytes + static_cast<size_t>(p.B) * p.Hkv * (p.NUG * p.F + ntx) * p.rec * sizeof(float) + kTimelineBytes;
 }
 
 bool any_decode_plan(const kvc_shape &s, int t, int cap, int32_t *plan)
@@ -772,9 +772,9 @@ bool any_decode(const DecodeCall &c, kvc_status *st, bool small_only)
     GPlan p;
     if (!make_gplan(p, c.s, c.t, c.t_in, c.cap)) return false;
     if (small_only && !(c.theta_packed && c.U_packed && small_call(p))) return false;
-    if (static_cast<size_t>(p.B) * p.Hkv * p.nparts * p.rec * sizeof(float) > c.ws_bytes) return false;
+    if (kCounterBytes + static_cast<size_t>(p.B) * p.Hkv * p.nparts * p.rec * sizeof(float) > c.ws_bytes) return false;
     p.scale = c.scale;
-    p.Ypart = static_cast<float *>(c.ws);
+    p.Ypart = reinterpret_cast<float *>(static_cast<char *>(c.ws) + kCounterBytes);
     p.n_img = c.n_images_dev; p.tlen = c.text_len_dev;
 #if defined(KVC_TIMELINE)
     p.tl = reinterpret_cast<unsigned long long *>(static_cast<char *>(c.ws) + ((c.ws_bytes - kTimelineBytes) & ~size_t(255)));

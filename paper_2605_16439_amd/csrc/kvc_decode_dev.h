@@ -30,6 +30,9 @@ constexpr int kWLD = kJC + 8;   // padded row (bf16) of the W tile in LDS
 constexpr size_t kLdsBudget = 150 * 1024;
 constexpr int kCtrStride = 16;  // 64-bit words per arrival counter: one counter per 128-byte line
 constexpr int kMaxFlags = 512;  // arrival counters at the start of the workspace
+// Every matrix-core decode kernel leaves these bytes to the counters: other words there would cost the next call that
+// counts its arrivals the whole waiting limit (see below).
+constexpr size_t kCounterBytes = static_cast<size_t>(kMaxFlags) * kCtrStride * sizeof(unsigned long long);
 constexpr int kDenseRows = 24;  // "image blocks per 64-row block" = 2^24: the dense layout of the query rows
 
 struct Plan {

@@ -1111,7 +1111,7 @@ Plan make_plan_layout(const kvc_shape &s, int t, int t_in, int cap, float scale,
         off += align_up(bytes, 256);
         return static_cast<char *>(base) + o;
     };
-    p.flags = reinterpret_cast<u64 *>(take(static_cast<size_t>(kMaxFlags) * kCtrStride * sizeof(u64)));   // always first
+    p.flags = reinterpret_cast<u64 *>(take(kCounterBytes));   // always first
     p.S = reinterpret_cast<uint16_t *>(take(static_cast<size_t>(p.Hkv) * p.R_pad * p.m_pad * 2));
     p.P = reinterpret_cast<uint16_t *>(take(static_cast<size_t>(p.Hkv) * p.R_pad * p.n * 2));
     p.stats = reinterpret_cast<f32x2 *>(take(static_cast<size_t>(p.Hkv) * p.R_pad * p.NC * 8));

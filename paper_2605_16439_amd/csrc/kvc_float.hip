@@ -591,7 +591,7 @@ size_t float_decode_ws_bytes(const kvc_shape &s, int32_t max_text)
     XPlan p;
     if (!make_xplan(p, s, std::max(max_text, 1), 0, std::max(max_text, 1))) return 0;
     const int ntx = std::min((std::max(max_text, 1) + kTR - 1) / kTR, kTextParts);
-    return static_cast<size_t>(p.B) * p.Hkv * (p.NUG * p.F + ntx) * p.rec * sizeof(float);
+    return dd::kCounterBytes + static_cast<size_t>(p.B) * p.Hkv * (p.NUG * p.F + ntx) * p.rec * sizeof(float);
 }
 
 bool float_decode_plan(const kvc_shape &s, int t, int cap, int32_t *plan)
@@ -608,9 +608,9 @@ bool float_decode(const DecodeCall &c, kvc_status *st)
     if (c.static_variant || (c.n_images_dev == nullptr) != (c.text_len_dev == nullptr)) return false;
     XPlan p;
     if (!make_xplan(p, c.s, c.t, c.t_in, c.cap)) return false;
-    if (static_cast<size_t>(p.B) * p.Hkv * p.nparts * p.rec * sizeof(float) > c.ws_bytes) return false;
+    if (dd::kCounterBytes + static_cast<size_t>(p.B) * p.Hkv * p.nparts * p.rec * sizeof(float) > c.ws_bytes) return false;
     p.scale = c.scale;
-    p.Ypart = static_cast<float *>(c.ws);
+    p.Ypart = reinterpret_cast<float *>(static_cast<char *>(c.ws) + dd::kCounterBytes);
     p.n_img = c.n_images_dev; p.tlen = c.text_len_dev;
     const bool f32 = c.s.dtype == KVC_F32;
     if (!(f32 ? launch_x<float>(p, c) : launch_x<bf16_t>(p, c)) || hipGetLastError() != hipSuccess) { *st = KVC_ERR_HIP; return true; }

@@ -118,7 +118,7 @@ size_t fast_static_ws_bytes(const kvc_shape &s)
 {
     const int G = s.n_q_heads / s.n_kv_heads;
     const size_t bh = static_cast<size_t>(s.batch) * s.n_kv_heads;
-    return (kTargetWg + 2 * bh) * align_up(G * D + 2 * G, 4) * sizeof(float);
+    return kCounterBytes + (kTargetWg + 2 * bh) * align_up(G * D + 2 * G, 4) * sizeof(float);
 }
 
 kvc_status fast_static_decode(const DecodeCall &c)
@@ -127,7 +127,7 @@ kvc_status fast_static_decode(const DecodeCall &c)
     if (!make_st_plan(p, c.s, c.t, c.t_in, c.cap)) return generic_decode(c);
     if (fast_static_ws_bytes(c.s) > c.ws_bytes) return generic_decode(c);
     p.scale = c.scale;
-    p.Ypart = static_cast<float *>(c.ws);
+    p.Ypart = reinterpret_cast<float *>(static_cast<char *>(c.ws) + kCounterBytes);
     static_split<<<c.s.batch * p.Hkv * p.NP, 64 * kSW, 0, c.stream>>>(
         static_cast<const uint16_t *>(c.q), static_cast<const uint16_t *>(c.Kc), static_cast<const uint16_t *>(c.Vc),
         static_cast<uint16_t *>(c.Kt), static_cast<uint16_t *>(c.Vt), static_cast<const uint16_t *>(c.k_new),

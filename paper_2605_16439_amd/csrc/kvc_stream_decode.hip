@@ -685,7 +685,7 @@ bool make_splan(SPlan &p, const DecodeCall &c, void *base, size_t *bytes)
     if (static_cast<long>(8) * p.chunk * p.F * std::max(p.F, p.B * p.IU) >= (1l << 31)) return false;
     if (p.F != 4 || p.NGR > kMaxFlags) return false;
     // workspace: arrival counters (the same 64 KB the four-kernel form keeps its counters in), part records, scores
-    const size_t fbytes = static_cast<size_t>(kMaxFlags) * kCtrStride * sizeof(u64);
+    const size_t fbytes = kCounterBytes;
     const size_t ybytes = align_up(static_cast<size_t>(p.B) * p.Hkv * p.nparts * p.rec * sizeof(float), 256);
     const size_t sbytes = static_cast<size_t>(p.NGR) * 16 * (32 * ((p.m + 31) / 32)) * sizeof(uint16_t);
     p.flags = static_cast<u64 *>(base);

@@ -262,3 +262,53 @@ def test_uniform_batch_through_the_ragged_entry_point(hq, hkv, B, I, n, m, t, ca
         else:
             res.append(L.decode(q, t, kn, vn))
     assert np.array_equal(res[0][0], res[1][0]) and np.array_equal(res[0][1], res[1][1])
+
+
+# The first 64 KB of a workspace belong to the arrival counters of the tuned kernels: what another kernel leaves there
+# makes their next call wait out its limit in every workgroup
+def layer_of(hq, hkv, B, I, n, m, t, dtype="bf16", d=128, packed=False):
+    L = Layer(synth.Workload("ctr", 96, 1, B, hq, hkv, d, dtype, n, I, 0.6, t, 2), m)
+    g = torch.Generator().manual_seed(m)
+    L.gKc, L.gVc = (torch.randn(L.gKc.shape, generator=g).to(L.gKc.dtype).to(DEV) for _ in range(2))
+    if packed:
+        L.packed = kv.kvc_pack_theta(L.shape, L.g["theta"]), kv.kvc_pack_u(L.shape, L.g["U"])
+        L.params = kv.make_params(L.g["key_idx"], L.g["theta"], L.g["U"], L.g["mu"], *L.packed)
+    return L
+
+
+def step_of(L, ws, static=False):
+    q, kn, vn = (x.to(DEV) for x in synth.make_step_inputs(L.w, 0, 0))
+    tail = (q, L.gKc, L.gVc, L.gKt, L.gVt, L.w.text_len, L.w.text_cap, kn, vn, 0.0, L.out, L.lse, ws)
+    if static:
+        kv.kvc_static_attend_decode(L.shape, *tail)
+    else:
+        kv.kvc_reconstruct_attend_decode(L.shape, L.params, *tail)
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("hq,hkv,B,I,n,m,t,dtype,d,packed,static", [
+    (28, 4, 1, 1, 1024, 256, 100, "bf16", 128, True, False), (28, 4, 1, 3, 729, 292, 100, "bf16", 128, False, False),
+    (28, 4, 4, 8, 1024, 410, 100, "bf16", 128, False, True), (8, 2, 1, 2, 576, 231, 64, "f32", 64, False, False)])
+def test_arrival_counters_are_left_alone(hq, hkv, B, I, n, m, t, dtype, d, packed, static):
+    L = layer_of(hq, hkv, B, I, n, m, t, dtype, d, packed)
+    ws = torch.full((kv.kvc_workspace_bytes(L.shape, L.w.text_cap) + 256,), 0x5A, dtype=torch.uint8, device=DEV)
+    print(f"[any] counters {hq}/{hkv} n={n} {dtype} static={static}", flush=True)
+    step_of(L, ws, static)
+    head = ws[(-ws.data_ptr()) % 256:][:65536]
+    assert (head == 0x5A).all()
+
+
+def test_large_calls_after_small_ones_do_not_wait():
+    small = layer_of(28, 4, 1, 1, 1024, 256, 100, packed=True)
+    large = [layer_of(28, 4, 4, 8, 1024, 410, 300, packed=True), layer_of(8, 8, 8, 1, 576, 231, 128)]
+    size = max(kv.kvc_workspace_bytes(L.shape, L.w.text_cap) for L in [small] + large)
+    ws = torch.zeros(size + 256, dtype=torch.uint8, device=DEV)
+    calls = kv.lib().kvc_dev_any_calls()
+    for L in large:
+        step_of(L, ws)
+        alone = kv.lib().kvc_dev_decode_fallbacks()
+        step_of(small, ws)
+        step_of(small, ws, static=True)
+        step_of(L, ws)
+        assert kv.lib().kvc_dev_decode_fallbacks() == alone
+    assert kv.lib().kvc_dev_any_calls() == calls + 2
