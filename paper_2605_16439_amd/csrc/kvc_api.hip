@@ -130,24 +130,26 @@ kvc_status prepare_compress(CompressCall &c, const kvc_shape *shape, const kvc_p
     return KVC_OK;
 }
 
-// the matrix-core kernels where the shape allows it, else the scalar kernels
-kvc_status dispatch_decode(const DecodeCall &c)
-{
-    kvc_status st = KVC_OK;
-    // small calls with packed parameters: one latency-bound pass, with float32 weights, instead of three or four launches
-    // (small_call in kvc_any_decode.hip); with plain parameters these shapes stay on the tuned kernels
-    if (fast_decode_default() && any_decode(c, &st, true)) return st;
-    if (stream_decode(c, &st)) return st;
-    if (fast_decode_supported(c.s)) return fast_decode(c);
-    return other_decode(c);
-}
-
 // scratch without which no kernel serves the shape (kvc_workspace_bytes also covers kernels that have a fallback)
 size_t least_decode_ws_bytes(const kvc_shape &s, int32_t max_text)
 {
     size_t need = generic_decode_ws_bytes(s, max_text);
     if (fast_decode_supported(s)) need = std::max(need, fast_decode_ws_bytes(s, max_text));
     return std::max(need, stream_decode_ws_bytes(s, max_text));
+}
+
+// the matrix-core kernels where the shape allows it, else the scalar kernels
+kvc_status dispatch_decode(const DecodeCall &c)
+{
+    kvc_status st = KVC_OK;
+    // small calls with packed parameters: one latency-bound pass, with float32 weights, instead of three or four launches
+    // (small_call in kvc_any_decode.hip); with plain parameters, or a workspace that the shape's other kernels may refuse,
+    // these shapes stay on the tuned kernels
+    if (c.theta_packed && c.U_packed && fast_decode_default() && c.ws_bytes >= least_decode_ws_bytes(c.s, c.cap) && any_decode(c, &st, true))
+        return st;
+    if (stream_decode(c, &st)) return st;
+    if (fast_decode_supported(c.s)) return fast_decode(c);
+    return other_decode(c);
 }
 
 template <class T>
@@ -166,7 +168,8 @@ __global__ __launch_bounds__(256) void unpack_values(const T *__restrict__ Vc, T
 namespace kvc {
 kvc_status other_decode(const DecodeCall &c)
 {
-    kvc_status st = KVC_OK;
+    kvc_status st = generic_decode_check(c);
+    if (st != KVC_OK) return st;
     return any_decode(c, &st, false) || float_decode(c, &st) ? st : generic_decode(c);
 }
 }  // namespace kvc
@@ -307,6 +310,8 @@ kvc_status kvc_static_attend_decode(const kvc_shape *shape, const void *q, const
                                    softmax_scale, out, lse_out, workspace, workspace_bytes, stream);
     if (st != KVC_OK) return st;
     c.static_variant = true;
+    st = generic_decode_check(c);
+    if (st != KVC_OK) return st;
     return fast_static_supported(c.s) ? fast_static_decode(c) : generic_decode(c);
 }
 

@@ -366,11 +366,17 @@ size_t generic_decode_ws_bytes(const kvc_shape &s, int32_t max_text)
     return carve(s, max_text, nullptr).bytes;
 }
 
-kvc_status generic_decode(const DecodeCall &c)
+kvc_status generic_decode_check(const DecodeCall &c)
 {
     // dynamic LDS of g_expand / g_project holds one row of m / n floats
     if (static_cast<size_t>(c.s.n_img_tokens) * sizeof(float) > 64 * 1024) return KVC_ERR_UNSUPPORTED;
-    if (carve(c.s, c.cap, nullptr).bytes > c.ws_bytes) return KVC_ERR_WORKSPACE;
+    return carve(c.s, c.cap, nullptr).bytes > c.ws_bytes ? KVC_ERR_WORKSPACE : KVC_OK;
+}
+
+kvc_status generic_decode(const DecodeCall &c)
+{
+    const kvc_status st = generic_decode_check(c);
+    if (st != KVC_OK) return st;
     return c.s.dtype == KVC_F32 ? decode_t<float>(c) : decode_t<bf16_t>(c);
 }
 

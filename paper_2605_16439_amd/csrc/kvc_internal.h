@@ -127,6 +127,8 @@ inline bool allow_lds(const void *fn, size_t bytes, bool *done)
 
 // scalar (shape-agnostic) path
 size_t generic_decode_ws_bytes(const kvc_shape &s, int32_t max_text);
+// (what the scalar kernels refuse is refused for every kernel that stands in for them)
+kvc_status generic_decode_check(const DecodeCall &c);
 kvc_status generic_decode(const DecodeCall &c);
 kvc_status generic_compress(const CompressCall &c);
 kvc_status generic_mlp_hidden(const kvc_shape &s, const void *W1, int act, const void *Kc, void *H, hipStream_t stream);

@@ -99,6 +99,31 @@ def test_decode_rejects_bad_arguments_before_any_launch():
     assert _decode(empty, p, t=0, cap=0, Kt=None, Vt=None) == kv.KVC_ERR_SHAPE
 
 
+def scalar_workspace(B, hq, I, n, m, cap):
+    """Scratch of the scalar decode kernels: compressed and text scores, expanded logits, statistics, weights."""
+    return sum(-(-4 * B * hq * x // 256) * 256 for x in (I * m, max(cap, 1), I * n, 4, I * m))
+
+
+@pytest.mark.parametrize("hq,hkv,B,I,n,m,d,dtype,packed", [
+    (28, 4, 1, 3, 729, 292, 128, kv.KVC_BF16, False), (8, 2, 1, 1, 576, 231, 64, kv.KVC_F32, False), (28, 4, 1, 2, 256, 103, 128, kv.KVC_BF16, True),
+    (28, 4, 1, 2, 1024, 256, 128, kv.KVC_BF16, True), (4, 2, 1, 2, 100, 41, 72, kv.KVC_BF16, False)])
+def test_workspace_smaller_than_the_scalar_kernels_need_is_refused(hq, hkv, B, I, n, m, d, dtype, packed):
+    """Whatever kernel would have had enough of it."""
+    s = kv.make_shape(B, hq, hkv, d, n, I, m, dtype)
+    p = kv.KvcParams(0x1000, 0x2000, 0x3000, 0x4000, 0x5000, 0x6000) if packed else kv.KvcParams(0x1000, 0x2000, 0x3000, 0x4000)
+    cap = 8
+    need = scalar_workspace(B, hq, I, n, m, cap)
+    assert kv.kvc_workspace_bytes(s, cap) >= need
+    small = 65536 if packed else need - 1
+    assert _decode(s, p, wsb=small) == kv.KVC_ERR_WORKSPACE
+    static = lambda wsb, s=s: kv.lib().kvc_static_attend_decode(ctypes.byref(s), 0x10000, 0x20000, 0x30000, 0x40000, 0x50000, 4, cap, None, None,
+                                                                ctypes.c_float(0.0), 0x60000, None, 0x70000, wsb, None)
+    assert static(need - 1) == kv.KVC_ERR_WORKSPACE
+    long_block = kv.make_shape(B, hq, hkv, d, 16385, I, m, dtype)
+    assert static(1 << 40, long_block) == kv.KVC_ERR_UNSUPPORTED
+    assert _decode(long_block, kv.KvcParams(0x1000, 0x2000, 0x3000, 0x4000), wsb=1 << 40) == kv.KVC_ERR_UNSUPPORTED
+
+
 def test_compress_rejects_bad_arguments_before_any_launch():
     s, p = _valid()
 

@@ -312,3 +312,23 @@ def test_large_calls_after_small_ones_do_not_wait():
         step_of(L, ws)
         assert kv.lib().kvc_dev_decode_fallbacks() == alone
     assert kv.lib().kvc_dev_any_calls() == calls + 2
+
+
+# A workspace that is enough for the scalar kernels only (no more than the counters of the others): they serve the call
+@pytest.mark.parametrize("dtype,d,static", [("bf16", 128, False), ("bf16", 128, True), ("f32", 64, False), ("bf16", 64, False)])
+def test_smallest_accepted_workspace(dtype, d, static):
+    hq, B, I, n, m, t = 16, 1, 20, 8, 3, 5
+    L = layer_of(hq, 1, B, I, n, m, t, dtype, d)
+    need = sum(-(-4 * B * hq * x // 256) * 256 for x in (I * m, L.w.text_cap, I * n, 4, I * m))
+    assert need < 65536
+    calls = kv.lib().kvc_dev_any_calls()
+    res = []
+    for ws in (torch.zeros(need + 512, dtype=torch.uint8, device=DEV), L.ws):
+        ws = ws[(-ws.data_ptr()) % 256:]
+        L.out.zero_()
+        step_of(L, ws[:need] if ws.numel() < 65536 else ws, static)
+        res.append(f64(L.out))
+    assert kv.lib().kvc_dev_any_calls() == calls + (1 if d == 128 and not static else 0)
+    e = np.linalg.norm(res[0] - res[1], axis=-1) / np.linalg.norm(res[1], axis=-1)
+    print(f"[any] smallest workspace {dtype} d={d} static={static}: {e.max():.3e}", flush=True)
+    assert e.max() <= (1e-5 if dtype == "f32" else OUT_ROUNDING * 2)          # two roundings of nearly the same value
