@@ -511,13 +511,17 @@ bool make_xplan(XPlan &p, const kvc_shape &s, int t, int t_in, int cap)
     if (p.G > 16 || p.n < 4) return false;
     const long bh = static_cast<long>(p.B) * p.Hkv;
     // narrow slices spread a small call over the chip; wide ones read the keys and values less often, taken as soon
-    // as they leave two workgroups per compute unit
+    // as they leave two workgroups per compute unit.  Smaller tiles spread it further, as long as every workgroup keeps one
+    // tile: beyond the part records that the merge takes they would follow each other in the same workgroups (us per layer,
+    // B = 1, d = 64: 8/2 heads, 16 blocks of n = 576 one tile of four 36.7, four of one 51.6; 14/2, 4 of 1024 34.9 / 43.0).
     p.UP = std::max(1, std::min(16 / p.G, p.I));
     auto groups = [&](int up) { return bh * ((p.I + up - 1) / up); };
     p.NP = groups(p.UP) * ((p.n + 255) / 256) >= 512 ? 4 : 1;
     if ((p.n + 63) / 64 > kVisParts) p.NP = 4;
     if (p.NP == 1)
-        while (p.UP > 1 && groups(p.UP) * ((p.n + 63) / 64) < 256) p.UP = (p.UP + 1) / 2;
+        for (int up = (p.UP + 1) / 2; p.UP > 1 && groups(p.UP) * ((p.n + 63) / 64) < 256 && (p.I + up - 1) / up * ((p.n + 63) / 64) <= kVisParts;
+             up = (p.UP + 1) / 2)
+            p.UP = up;
     p.F = (p.n + 64 * p.NP - 1) / (64 * p.NP);
     if (p.F > kVisParts || x_lds(p.m, p.NP) > kXLds) return false;
     const int tiles = (p.I + p.UP - 1) / p.UP, ug_max = kVisParts / p.F;

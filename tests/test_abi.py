@@ -259,6 +259,13 @@ def test_plan_follows_from_the_capacity_of_the_text_cache(hq, hkv, B, I, n, m, k
             assert p[5] == min(-(-t // 128), 16) and p[6] == -(-cap // 2048)
 
 
+@pytest.mark.parametrize("hq,hkv,B,I,n,m,tile", [(8, 2, 1, 16, 576, 231, 4), (14, 2, 1, 4, 1024, 410, 2), (8, 2, 1, 4, 576, 231, 1), (8, 2, 1, 1, 576, 231, 1),
+                                                 (4, 4, 1, 40, 130, 52, 4)])
+def test_fp32_tiles_shrink_only_while_every_workgroup_keeps_one(hq, hkv, B, I, n, m, tile):
+    p = decode_plan(hq, hkv, B, I, n, m, 1, 64, 1, kv.KVC_F32, 64)
+    assert p[1] == tile and p[2] == 1
+
+
 def test_small_calls_of_tuned_block_lengths_and_those_just_beyond():
     """10 steps of 32 rows, 256 workgroups with the text's among them, text runs of 4 steps of 128 rows."""
     small = lambda *a: decode_plan(*a)[7]
