@@ -82,8 +82,8 @@ template <int LD> __device__ inline int sv_index(int c, int p) { return c * LD +
 // FORM 0: compress, n a multiple of 64.
 // FORM 1: compress, any n >= 8.  Rows of U start at any 2-byte address and the last tile is partial: a 16-byte
 //         piece that would leave its row is read from the row's last 8 columns instead and shifted into place
-//         with register moves when it is stored to LDS (zeros come in behind it); rows of V past the end repeat
-//         the last one and meet those zeros.
+//         with register moves when it is stored to LDS (zeros come in behind it); rows of V past the end are stored
+//         as zeros as well (the repeated last row would turn into NaNs where it holds an infinity).
 // FORM 2: first layer of the two-layer key reconstructor, p.n = m.  W1 [m][m] is stored with the contraction
 //         index slow, so its tile is transposed on its way into LDS as V's is; the same treatment of the edges.
 //         The operands of the matrix instruction trade places, so that a lane ends up with four consecutive
@@ -262,14 +262,30 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
 #pragma unroll
         for (int k = 0; k < 2 * MT; ++k) ua[k] = load_u(kt, k);
     };
+    // Rows of V past the end of the block: zeros in the registers of its last tile (FORM 1), or on the way to LDS (FORM 2, which
+    // has no registers to spare: at the shape above 18.9 us, 19.4 with five of them spilled, 18.6 with the rows left as they are).
+    auto row_keep = [&](int kt, int row) -> uint32_t { return kt * kKT + row < p.n ? 0xffffffffu : 0u; };
+    auto clear_tail = [&](int kt, u32x4 (&va)[NV][2]) {
+        if constexpr (FORM == 1) {
+            if (kt != NK - 1) return;                    // uniform; registers only
+#pragma unroll
+            for (int q = 0; q < NV; ++q)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const uint32_t keep = row_keep(kt, 2 * (pair0 + RP * q) + e);
+                    va[q][e] = u32x4{va[q][e].x & keep, va[q][e].y & keep, va[q][e].z & keep, va[q][e].w & keep};
+                }
+        }
+    };
     auto store_tile = [&](int kt, const u32x4 (&va)[NV][2], const u32x4 (&ua)[2 * MT]) {
         uint16_t *buf = sVt + (kt & 1) * (D * kLD);
         // transposed store: positions (2 pair, 2 pair + 1) of channel c share one 32-bit word
 #pragma unroll
         for (int q = 0; q < NV; ++q) {
             const int pl = 2 * (pair0 + RP * q);
-            const uint32_t a[4] = {va[q][0].x, va[q][0].y, va[q][0].z, va[q][0].w};
-            const uint32_t c2[4] = {va[q][1].x, va[q][1].y, va[q][1].z, va[q][1].w};
+            const uint32_t k0 = FORM == 2 ? row_keep(kt, pl) : 0xffffffffu, k1 = FORM == 2 ? row_keep(kt, pl + 1) : 0xffffffffu;
+            const uint32_t a[4] = {va[q][0].x & k0, va[q][0].y & k0, va[q][0].z & k0, va[q][0].w & k0};
+            const uint32_t c2[4] = {va[q][1].x & k1, va[q][1].y & k1, va[q][1].z & k1, va[q][1].w & k1};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 *reinterpret_cast<uint32_t *>(buf + sv_index<kLD>(8 * cs + 2 * e, pl)) = (a[e] & 0xffffu) | (c2[e] << 16);
@@ -289,7 +305,11 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
 #pragma unroll
             for (int q = 0; q < NV; ++q) {
                 const int pl = 2 * (pair0 + RP * q);
-                const uint32_t a = va[q][0][i], c2 = va[q][1][i];
+                uint32_t a = va[q][0][i], c2 = va[q][1][i];
+                if (FORM == 2 && kt >= NK - 1) {         // uniform; registers only
+                    a &= row_keep(kt, pl);
+                    c2 &= row_keep(kt, pl + 1);
+                }
                 *reinterpret_cast<uint32_t *>(buf + sv_index<kLD>(8 * cs + 2 * i, pl)) = (a & 0xffffu) | (c2 << 16);
                 *reinterpret_cast<uint32_t *>(buf + sv_index<kLD>(8 * cs + 2 * i + 1, pl)) = (a >> 16) | (c2 & 0xffff0000u);
             }
@@ -365,6 +385,7 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
         for (int q = 0; q < MT; ++q) af[0][q] = frag_u(kt, 0, q);
     };
     auto step = [&](int kt, u32x4 (&va)[NV][2], u32x4 (&ua)[2 * MT]) {
+        clear_tail(kt + 1, va);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int f = 0; f < 16; ++f) {
@@ -403,6 +424,7 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
             __builtin_amdgcn_sched_barrier(0);
         }
     };
+    clear_tail(0, vaX);
     store_tile(0, vaX, uaX);
     load_tile(min(2, NK - 1), vaX, uaX);
     uint16_t mur[8];                                     // the channel means the epilogue needs, requested early

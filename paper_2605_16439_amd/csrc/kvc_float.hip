@@ -98,7 +98,7 @@ __global__ __launch_bounds__(64 * kXW) void gx_project(const T *__restrict__ K, 
     f32x4 acc[DT];
 #pragma unroll
     for (int ct = 0; ct < DT; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // 16 positions per step; the rows of V past the end meet zeros of U
+    // 16 positions per step; past the end the centre itself, a zero, meets zeros of U
     for (int s = wave; 16 * s < n; s += kXW) {
         const f32x4 a = load4_in(Ub, 16 * s + 4 * kg, n);
         float v[4][DT];
@@ -106,6 +106,12 @@ __global__ __launch_bounds__(64 * kXW) void gx_project(const T *__restrict__ K, 
         for (int e = 0; e < 4; ++e)
 #pragma unroll
             for (int ct = 0; ct < DT; ++ct) v[e][ct] = to_f(Vb[static_cast<int64_t>(min(16 * s + 4 * kg + e, n - 1)) * p.ss + ch[ct]]);
+        if (16 * s + 16 > n) {                           // uniform; registers only
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int ct = 0; ct < DT; ++ct) v[e][ct] = 16 * s + 4 * kg + e < n ? v[e][ct] : muc[ct];
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll

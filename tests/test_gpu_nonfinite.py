@@ -8,7 +8,10 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import kvc_oracle as orc
 from paper_2605_16439_amd import kvcapsule as kv
+
+from helpers import f64, unpack_vc
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -62,3 +65,53 @@ def test_non_finite_query_stays_in_its_own_head(what, dtype, d, bad):
     keep = torch.ones((B, hq), dtype=torch.bool)
     keep[0, :2] = False
     assert torch.equal(out[keep], clean[keep]) and torch.equal(lse[keep], clean_lse[keep])
+
+
+def check_same_kind(got, ref, bar):
+    """The same NaNs and infinities; finite values within `bar` of the reference's norm, per row of the last axis."""
+    assert np.array_equal(np.isnan(got), np.isnan(ref)), (np.isnan(got).sum(), np.isnan(ref).sum())
+    assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and np.array_equal(np.isneginf(got), np.isneginf(ref))
+    fin = np.isfinite(ref)
+    g, r = np.where(fin, got, 0.0), np.where(fin, ref, 0.0)
+    e = np.linalg.norm(g - r, axis=-1) / np.maximum(np.linalg.norm(r, axis=-1), 1e-30)
+    assert e.max() <= bar, e.max()
+
+
+# Rows past the end of a block fill the last tile of positions: they are zeros, not the last row again, whose infinity
+# would meet the zeros of U or W1.  n and m around the tiles of 64 (bf16, d = 128) and 16 (fp32) positions.
+@pytest.mark.parametrize("n,m,dtype,d", [(65, 33, torch.bfloat16, 128), (71, 20, torch.bfloat16, 128), (126, 126, torch.bfloat16, 128),
+                                         (729, 292, torch.bfloat16, 128), (64, 20, torch.bfloat16, 128), (9, 4, torch.bfloat16, 128),
+                                         (65, 33, torch.float32, 64), (30, 7, torch.float32, 128), (100, 40, torch.bfloat16, 72)])
+def test_infinite_value_rows_of_compress(n, m, dtype, d):
+    B, hkv, I, pre = 1, 2, 3, 5
+    shape = kv.make_shape(B, 4, hkv, d, n, I, m, dtype)
+    idx = torch.arange(m, dtype=torch.int32, device=DEV)
+    U, mu = normal(1, hkv, m, n, dtype=dtype) * n ** -0.5, normal(2, hkv, d, dtype=dtype)
+    K, V = normal(3, B, hkv, pre + I * n + 2, d, dtype=dtype), normal(4, B, hkv, pre + I * n + 2, d, dtype=dtype)
+    V[0, 0, pre + n - 1, 3] = INF               # last row of the first block
+    V[0, 0, pre + n - 1, 4] = -INF
+    V[0, 1, pre + 3 * n - 1, 7] = INF           # last row of the last block
+    V[0, 1, pre + 3 * n - 1, 8] = NAN
+    V[0, 1, pre + n, 9] = INF                   # first row of the second block
+    V[0, 1, pre + 3 * n, 10] = NAN              # behind the last block: nobody's
+    Kc, Vc = (torch.zeros((B, hkv, I, m, d), dtype=dtype, device=DEV) for _ in range(2))
+    print(f"[nonfinite] compress n={n} m={m} {dtype} d={d}", flush=True)
+    kv.kvc_compress(shape, kv.make_params(idx, U, U, mu), K, V, pre, Kc, Vc, kv.new_workspace(shape, 1))
+    torch.cuda.synchronize()
+    code = orc.STORE_F32 if dtype == torch.float32 else orc.STORE_BF16
+    Kc_ref, Vc_ref = orc.compress(f64(K), f64(V), idx.cpu().numpy(), f64(U), f64(mu), n, I, pre, code)
+    assert np.array_equal(f64(Kc), Kc_ref)
+    check_same_kind(unpack_vc(Vc, m, d), Vc_ref, 1e-5 if dtype == torch.float32 else 3e-3)
+
+
+@pytest.mark.parametrize("act", [kv.KVC_ACT_IDENTITY, kv.KVC_ACT_RELU, kv.KVC_ACT_GELU])
+@pytest.mark.parametrize("m", [9, 63, 64, 65, 103, 410])
+def test_infinite_key_rows_of_the_hidden_layer(m, act):
+    B, hkv, I, d = 1, 2, 2, 128
+    Kc, W1 = normal(5, B, hkv, I, m, d), normal(6, hkv, m, m) * m ** -0.5
+    Kc[0, 0, 0, m - 1, 3], Kc[0, 0, 0, m - 1, 4], Kc[0, 1, 1, m - 1, 5], Kc[0, 1, 0, 0, 6] = INF, -INF, NAN, INF
+    H = torch.zeros_like(Kc)
+    print(f"[nonfinite] hidden m={m} act={act}", flush=True)
+    kv.kvc_mlp_hidden(kv.make_shape(B, 4, hkv, d, 1024, I, m, torch.bfloat16), W1, act, Kc, H)
+    torch.cuda.synchronize()
+    check_same_kind(f64(H), orc.mlp_hidden(f64(Kc), f64(W1), act, orc.STORE_BF16), 3e-3)
