@@ -89,7 +89,7 @@ template <int LD> __device__ inline int sv_index(int c, int p) { return c * LD +
 //         The operands of the matrix instruction trade places, so that a lane ends up with four consecutive
 //         channels of one row: the result is row-major.
 // The scalar kernels that FORM 1 and 2 replace run one multiply-add per lane and load; the same two shapes here
-// (n = 729, m = 292, 12 image blocks: 595 -> 13.5 us; m = 410, 128 image blocks, GELU: 1011 -> 18.9 us) are
+// (n = 729, m = 292, 12 image blocks: 595 -> 12.5 us; m = 410, 128 image blocks, GELU: 1011 -> 18.9 us) are
 // bound as FORM 0 is, by the latency of a tile step and, when few workgroups are resident, by their number.
 // 16-byte register image of 8 elements, shifted down by `sh` elements (sh >= 8: nothing is left)
 __device__ inline u32x4 drop_elems(u32x4 v, int sh)
