@@ -1021,7 +1021,11 @@ __global__ __launch_bounds__(128) void fd_finalize_few(const float *__restrict__
     TS(3, 3);
     float y = p.nvp > 0 ? (zv * rz) * bf_lo(mub) : 0.f;   // without vision parts mu is no part of the result, whatever it holds
 #pragma unroll
-    for (int k = 0; k < PB; ++k) y += __shfl(wgt, k, 64) * v[k];     // clamped duplicates: weight zero
+    for (int k = 0; k < PB; ++k) {
+        // clamped duplicates (among the last eight) weigh zero; the one that they repeat may be infinite
+        const float vk = k < PB - 8 || k < np ? v[k] : 0.f;
+        y += __shfl(wgt, k, 64) * vk;
+    }
     out[static_cast<size_t>(bg) * D + c] = f32_to_bf16_bits(y);
     if (c == 0 && lse) lse[bg] = mx + __logf(z);
     // the arrival counters of fab_fused go back to zero

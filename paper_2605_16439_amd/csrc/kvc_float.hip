@@ -74,8 +74,9 @@ struct XProj {
     int64_t sb, sh, ss;
 };
 
+// (bf16, d <= 64: four workgroups per CU instead of three, which 72 registers would leave)
 template <class T, int DT>
-__global__ __launch_bounds__(64 * kXW) void gx_project(const T *__restrict__ K, const T *__restrict__ V, const int32_t *__restrict__ idx,
+__global__ __launch_bounds__(64 * kXW, DT == 4 && sizeof(T) == 2 ? 8 : 2) void gx_project(const T *__restrict__ K, const T *__restrict__ V, const int32_t *__restrict__ idx,
                                                        const T *__restrict__ U, const T *__restrict__ mu, T *__restrict__ Kc,
                                                        T *__restrict__ Vc, XProj p)
 {
@@ -98,19 +99,17 @@ __global__ __launch_bounds__(64 * kXW) void gx_project(const T *__restrict__ K, 
     f32x4 acc[DT];
 #pragma unroll
     for (int ct = 0; ct < DT; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // 16 positions per step; past the end the centre itself, a zero, meets zeros of U
+    // 16 positions per step; past the end the centre stands in for a row of V: its zero meets zeros of U
+    const T *muh = mu + static_cast<size_t>(h) * d;
     for (int s = wave; 16 * s < n; s += kXW) {
         const f32x4 a = load4_in(Ub, 16 * s + 4 * kg, n);
         float v[4][DT];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
+        for (int e = 0; e < 4; ++e) {
+            const int pos = 16 * s + 4 * kg + e;
+            const T *row = pos < n ? Vb + static_cast<int64_t>(pos) * p.ss : muh;
 #pragma unroll
-            for (int ct = 0; ct < DT; ++ct) v[e][ct] = to_f(Vb[static_cast<int64_t>(min(16 * s + 4 * kg + e, n - 1)) * p.ss + ch[ct]]);
-        if (16 * s + 16 > n) {                           // uniform; registers only
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int ct = 0; ct < DT; ++ct) v[e][ct] = 16 * s + 4 * kg + e < n ? v[e][ct] : muc[ct];
+            for (int ct = 0; ct < DT; ++ct) v[e][ct] = to_f(row[ch[ct]]);
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -277,6 +276,7 @@ __global__ __launch_bounds__(64 * kXW) void gx_pass(const T *__restrict__ q, con
                     for (int e = 0; e < 4; ++e) {
                         const int x = min(x0 + 16 * k + 4 * kg + e, t - 1);
                         v[e] = to_f((x == t_new ? vn : Vtb + static_cast<size_t>(x) * d)[cc]);
+                        v[e] = x0 + 16 * k + 4 * kg + e < t ? v[e] : 0.f;
                     }
                     o[c] = mfma16(v, w, o[c]);
                 }
@@ -390,20 +390,17 @@ __global__ __launch_bounds__(64 * kXW) void gx_pass(const T *__restrict__ q, con
                 *reinterpret_cast<f32x4 *>(sS + r16 * LDM + j) = a;
             }
             __syncthreads();
-            // ---- step 4: Y^T[c][row] = sum_j Vc^T[c][j] W[row][j]; the weights of other blocks' rows are selected to zero
-            f32x4 o[CW];
+            // ---- step 4: Y^T[c][row] = sum_j Vc^T[c][j] W[row][j]; of a block's product the rows of that block are taken
+            f32x4 o[CW], yu[CW];
 #pragma unroll
             for (int c = 0; c < CW; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
             const int sfull = m >> 4, send = (m + 15) >> 4;      // 16-row steps inside full 8-row blocks, all steps
             for (int u = 0; u < nu; ++u) {
                 const bool mine = r16 >= u * G && r16 < (u + 1) * G;
                 const T *rec = vc_b + static_cast<size_t>(u) * m * d;
-                auto weights = [&](int k) __attribute__((always_inline)) {
-                    f32x4 w = *reinterpret_cast<const f32x4 *>(sS + r16 * LDM + 16 * k + 4 * kg);
+                auto weights = [&](int k) __attribute__((always_inline)) { return *reinterpret_cast<const f32x4 *>(sS + r16 * LDM + 16 * k + 4 * kg); };
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) w[e] = mine ? w[e] : 0.f;
-                    return w;
-                };
+                for (int c = 0; c < CW; ++c) yu[c] = f32x4{0.f, 0.f, 0.f, 0.f};
                 // (unrolled: the loads of four steps together)
 #pragma unroll 4
                 for (int k = kh4; k < sfull; k += KH) {
@@ -411,7 +408,7 @@ __global__ __launch_bounds__(64 * kXW) void gx_pass(const T *__restrict__ q, con
 #pragma unroll
                     for (int c = 0; c < CW; ++c) {
                         const int cc = min(16 * (ct4 + kXW * c) + r16, d - 1);
-                        o[c] = mfma16(load4(rec + static_cast<size_t>(2 * k + (kg >> 1)) * 8 * d + cc * 8 + 4 * (kg & 1)), w, o[c]);
+                        yu[c] = mfma16(load4(rec + static_cast<size_t>(2 * k + (kg >> 1)) * 8 * d + cc * 8 + 4 * (kg & 1)), w, yu[c]);
                     }
                 }
                 if (sfull < send && (KH == 1 || (sfull & 1) == kh4)) {
@@ -425,9 +422,13 @@ __global__ __launch_bounds__(64 * kXW) void gx_pass(const T *__restrict__ q, con
                             const int j = 16 * sfull + 4 * kg + e;
                             v[e] = j < m ? to_f(rec[vc_offset(min(j, m - 1), cc, m, d)]) : 0.f;
                         }
-                        o[c] = mfma16(v, w, o[c]);
+                        yu[c] = mfma16(v, w, yu[c]);
                     }
                 }
+#pragma unroll
+                for (int c = 0; c < CW; ++c)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[c][e] = mine ? yu[c][e] : o[c][e];
             }
             if (r16 < nu * G) advance(mx, sm, o);         // rows of the tile that hold no image block keep their state
             __syncthreads();                              // W and P have been read

@@ -115,3 +115,69 @@ def test_infinite_key_rows_of_the_hidden_layer(m, act):
     kv.kvc_mlp_hidden(kv.make_shape(B, 4, hkv, d, 1024, I, m, torch.bfloat16), W1, act, Kc, H)
     torch.cuda.synchronize()
     check_same_kind(f64(H), orc.mlp_hidden(f64(Kc), f64(W1), act, orc.STORE_BF16), 3e-3)
+
+
+# Infinite values reach their own channel of their own (sequence, KV head) only.  Text values and the rows of the static
+# variant, whose weights are positive, stay infinities; a compressed value's weights have either sign in the parts that a
+# decode kernel adds up, so its channel is infinite or NaN there.  m around the blocks of 8 rows and the steps of 16 and 32,
+# several image blocks per tile, text around the step of 128.
+def poisoned(dtype, d, B, hkv, I, m, t):
+    Kc, Vc = normal(11, B, hkv, max(I, 1), m, d, dtype=dtype), normal(12, B, hkv, max(I, 1), m, d, dtype=dtype)
+    Kt, Vt = normal(13, B, hkv, t + 1, d, dtype=dtype), normal(14, B, hkv, t + 1, d, dtype=dtype)
+    vc = lambda j, c: kv.lib().kvc_capsule_value_offset(j, c, m, d)
+    flat = Vc.view(B, hkv, max(I, 1), m * d)
+    if I > 0:
+        flat[0, 0, I - 1, vc(m - 1, 3)] = INF                # last row of the last block
+        flat[0, 0, 0, vc(0, 7)] = -INF                       # first row of the first one
+        flat[B - 1, hkv - 1, I // 2, vc(m // 2, 12)] = INF
+        flat[B - 1, hkv - 1, I // 2, vc(m - 1, 20)] = NAN
+    kn, vn = normal(15, B, hkv, d, dtype=dtype), normal(16, B, hkv, d, dtype=dtype)
+    if t > 0:
+        Vt[0, 0, t - 1, 30] = INF                            # last row but the new one
+        Vt[B - 1, hkv - 1, 0, 31] = -INF
+    vn[0, 0, 40] = INF                                       # the new row, which the rows past the end repeat
+    return Kc, Vc, Kt, Vt, kn, vn
+
+
+@pytest.mark.parametrize("hq,hkv,B,I,n,m,t,dtype,d,packed", [
+    (14, 2, 2, 5, 130, 41, 70, torch.bfloat16, 128, False), (8, 8, 1, 3, 136, 64, 128, torch.bfloat16, 128, True), (7, 1, 1, 2, 9, 5, 3, torch.bfloat16, 128, False),
+    (4, 1, 1, 9, 600, 33, 300, torch.bfloat16, 128, False), (28, 4, 1, 2, 256, 103, 200, torch.bfloat16, 128, True), (14, 2, 1, 33, 200, 40, 9, torch.bfloat16, 128, False),
+    (2, 2, 2, 0, 50, 20, 260, torch.bfloat16, 128, False), (14, 2, 2, 5, 130, 41, 70, torch.float32, 64, False), (8, 2, 1, 3, 300, 33, 127, torch.float32, 128, False),
+    (16, 2, 1, 2, 65, 16, 130, torch.bfloat16, 72, False), (4, 4, 1, 2, 40, 7, 0, torch.float32, 256, False)])
+def test_infinite_values_in_decode(hq, hkv, B, I, n, m, t, dtype, d, packed):
+    shape = kv.make_shape(B, hq, hkv, d, n, I, m, dtype)
+    U = normal(17, hkv, m, n, dtype=dtype) * n ** -0.5
+    par = [torch.arange(m, dtype=torch.int32, device=DEV), normal(18, hkv, m, n, dtype=dtype) * m ** -0.5, U, normal(19, hkv, d, dtype=dtype)]
+    if packed:
+        par += [kv.kvc_pack_theta(shape, par[1]), kv.kvc_pack_u(shape, U)]
+    params, q, ws = kv.make_params(*par), normal(20, B, hq, d, dtype=dtype) * 0.25, kv.new_workspace(shape, t + 1)
+    res = []
+    for generic in (False, True):
+        Kc, Vc, Kt, Vt, kn, vn = poisoned(dtype, d, B, hkv, I, m, t)
+        out = torch.zeros((B, hq, d), dtype=dtype, device=DEV)
+        print(f"[nonfinite] decode {hq}/{hkv} B={B} I={I} n={n} m={m} t={t} {dtype} d={d} generic={generic}", flush=True)
+        kv.kvc_reconstruct_attend_decode(shape, params, q, Kc, Vc, Kt, Vt, t, t + 1, kn, vn, 0.0, out, None, ws, generic=generic)
+        torch.cuda.synchronize()
+        res.append(f64(out))
+    assert not np.isfinite(res[1]).all()
+    vision = [3, 7, 12, 20] if I > 0 else []
+    assert np.array_equal(np.isfinite(res[0]), np.isfinite(res[1]))
+    rest = [c for c in range(d) if c not in vision]
+    check_same_kind(res[0][..., rest], res[1][..., rest], 1e-5 if dtype == torch.float32 else 2 * (2.0 ** -8 + 1e-4))
+
+
+@pytest.mark.parametrize("hq,hkv,B,I,m,t", [(14, 2, 2, 5, 41, 70), (7, 1, 1, 2, 7, 1), (8, 8, 1, 3, 64, 128), (28, 4, 1, 64, 103, 40), (6, 2, 1, 3, 8, 127),
+                                            (2, 2, 1, 0, 20, 260)])
+def test_infinite_values_in_the_static_variant(hq, hkv, B, I, m, t):
+    d, dtype = 128, torch.bfloat16
+    shape = kv.make_shape(B, hq, hkv, d, max(m, 64), I, m, dtype)
+    q = normal(21, B, hq, d) * 0.25
+    Kc, Vc, Kt, Vt, kn, vn = poisoned(dtype, d, B, hkv, I, m, t)
+    out = torch.zeros((B, hq, d), dtype=dtype, device=DEV)
+    dense, Kth, Vth = unpack_vc(Vc, m, d)[:, :, :I], f64(Kt).copy(), f64(Vt).copy()
+    print(f"[nonfinite] static {hq}/{hkv} B={B} I={I} m={m} t={t}", flush=True)
+    kv.kvc_static_attend_decode(shape, q, Kc, Vc, Kt, Vt, t, t + 1, kn, vn, 0.0, out, None, kv.new_workspace(shape, t + 1))
+    torch.cuda.synchronize()
+    ref, _ = orc.static_attend_decode(f64(q), f64(Kc)[:, :, :I], dense, Kth, Vth, t, f64(kn), f64(vn))
+    assert not np.isfinite(ref).all()
+    check_same_kind(f64(out), ref, 2.0 ** -8 + 1e-4)
