@@ -54,3 +54,14 @@ def unpack_vc(vc: torch.Tensor, m: int, d: int) -> np.ndarray:
     flat = f64(vc).reshape(vc.shape[:-2] + (m * d,))
     off = np.array([[kv.lib().kvc_capsule_value_offset(j, c, m, d) for c in range(d)] for j in range(m)])
     return flat[..., off]
+
+
+def decode_plan(hq, hkv, B, I, n, m, t, cap, kernel=0, dtype=1, d=128):
+    """How the library divides a decode call (kvc_dev_decode_plan): (positions per slice, image blocks per tile, tiles per
+    workgroup, slices, vision workgroups, text runs, steps per run, small call), or None."""
+    import ctypes
+
+    from paper_2605_16439_amd import kvcapsule as kv
+    plan = (ctypes.c_int32 * 8)()
+    ok = kv.lib().kvc_dev_decode_plan(ctypes.byref(kv.make_shape(B, hq, hkv, d, n, I, m, dtype)), t, cap, kernel, plan)
+    return tuple(plan) if ok else None

@@ -9,6 +9,8 @@ import pytest
 
 from paper_2605_16439_amd import kvcapsule as kv
 
+from helpers import decode_plan
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 GOLDEN = os.path.join(ROOT, "tests", "golden")
 
@@ -235,14 +237,6 @@ def test_full_decode_splits_of_the_cost_rule():
         for rows in (1, 127, 129, 4096, 1 << 20):
             assert 1 <= f(pairs, rows, 256) <= min(64, -(-rows // 128))
     assert f(0, 5, 256) == f(5, 0, 256) == f(5, 5, 0) == 0
-
-
-def decode_plan(hq, hkv, B, I, n, m, t, cap, kernel=0, dtype=kv.KVC_BF16, d=128):
-    """(positions per slice, image blocks per tile, tiles per workgroup, slices, vision workgroups, text runs, steps per run,
-    small call) or None."""
-    plan = (ctypes.c_int32 * 8)()
-    ok = kv.lib().kvc_dev_decode_plan(ctypes.byref(kv.make_shape(B, hq, hkv, d, n, I, m, dtype)), t, cap, kernel, plan)
-    return tuple(plan) if ok else None
 
 
 @pytest.mark.parametrize("kernel,dtype,d", [(0, kv.KVC_BF16, 128), (1, kv.KVC_F32, 64)])

@@ -13,7 +13,7 @@ from oracle import kvc_oracle as orc
 from paper_2605_16439_amd import kvcapsule as kv
 from paper_2605_16439_amd import synth
 
-from helpers import block_rel_err, f64, store_code, unpack_vc
+from helpers import block_rel_err, decode_plan, f64, store_code, unpack_vc
 from test_gpu_parity import Layer
 
 pytestmark = pytest.mark.gpu
@@ -142,8 +142,7 @@ def decode_case(w, m, ragged=None, packed=False):
 
 
 # n around the 8-column piece and the slices of 128 / 256 / 512 positions; m around 8, 16 and 32 rows; tiles with fewer
-# image blocks than they hold; several tiles per workgroup; group sizes without a tuned kernel; batches that select
-# each slice width
+# image blocks than they hold; group sizes without a tuned kernel; batches that select each slice width
 @pytest.mark.parametrize("hq,hkv,B,I,n,m,t", [
     (4, 4, 1, 1, 8, 3, 0), (7, 1, 1, 3, 9, 9, 1), (6, 2, 2, 1, 127, 8, 5), (3, 1, 1, 5, 128, 128, 127), (14, 2, 1, 2, 129, 31, 128),
     (28, 4, 1, 3, 729, 292, 200), (16, 1, 1, 2, 333, 33, 130), (5, 1, 2, 7, 257, 103, 300), (12, 1, 1, 4, 511, 64, 20),
@@ -160,15 +159,56 @@ def test_decode_any_shape_packed_parameters(hq, hkv, B, I, n, m, t):
     decode_case(wl(n, I, B=B, hq=hq, hkv=hkv, t=t), m, packed=True)
 
 
-# small calls at block lengths that have tuned kernels too: around the limits of 10 steps of 32 rows and 256 workgroups
-# (the text's among them) that send them to the one-pass kernel
+# Several tiles per workgroup, the last workgroup with fewer of them, the last tile partly filled: state carried from tile
+# to tile, LDS used again.  Every slice width, both forms of the parameters; ragged batches whose sequences end inside the
+# first, a middle and the last tile of a workgroup, before the first and behind the last.
+@pytest.mark.parametrize("hq,hkv,B,I,n,m,t,ps,tiles,packed", [s + (packed,) for s in [
+    (7, 1, 1, 99, 40, 17, 9, 128, 2), (7, 1, 2, 61, 136, 33, 140, 128, 2), (7, 1, 1, 99, 136, 41, 0, 128, 3), (28, 4, 1, 33, 729, 70, 30, 128, 3),
+    (96, 6, 1, 25, 304, 20, 5, 256, 2), (96, 6, 1, 25, 600, 33, 5, 512, 2)] for packed in (False, True) if not packed or s[4] % 8 == 0])
+def test_decode_several_tiles_per_workgroup(hq, hkv, B, I, n, m, t, ps, tiles, packed):
+    plan = decode_plan(hq, hkv, B, I, n, m, t + 1, t + 1)
+    assert (plan[0], plan[2]) == (ps, tiles)
+    calls = kv.lib().kvc_dev_any_calls()
+    decode_case(wl(n, I, B=B, hq=hq, hkv=hkv, t=t), m, packed=packed)
+    assert kv.lib().kvc_dev_any_calls() == calls + 1
+
+
+@pytest.mark.parametrize("hq,hkv,I,n,m,ni,ps,tiles", [
+    (7, 1, 99, 136, 41, [1, 4, 99, 50, 0], 128, 3), (16, 1, 25, 304, 20, [25, 1, 0, 24, 13, 2], 256, 2), (16, 1, 25, 600, 33, [25, 1, 0, 24, 13, 2], 512, 2),
+    (32, 8, 2, 304, 40, [2, 1, 0, 2] * 4, 256, 1), (8, 8, 3, 520, 40, [3, 0, 1, 2] * 8, 512, 1)])
+@pytest.mark.parametrize("packed", [False, True])
+def test_ragged_batch_of_every_slice_width_and_several_tiles(hq, hkv, I, n, m, ni, ps, tiles, packed):
+    B, t = len(ni), 130
+    plan = decode_plan(hq, hkv, B, I, n, m, t + 1, t + 1)
+    assert (plan[0], plan[2]) == (ps, tiles)
+    calls = kv.lib().kvc_dev_any_calls()
+    decode_case(wl(n, I, B=B, hq=hq, hkv=hkv, t=t), m, ragged=(ni, [(37 * b + 5) % (t + 1) for b in range(B)]), packed=packed)
+    assert kv.lib().kvc_dev_any_calls() == calls + 1
+
+
+# small calls at block lengths that have tuned kernels too: inside and just beyond the limits of 10 steps of 32 rows and
+# 256 workgroups (the text's among them) that send them to the one-pass kernel
 @pytest.mark.parametrize("hq,hkv,B,I,n,m,t", [(28, 4, 1, 16, 256, 103, 200), (28, 4, 1, 32, 256, 154, 1), (32, 32, 1, 1, 576, 320, 0),
                                               (14, 2, 1, 12, 576, 160, 700), (4, 1, 1, 1, 1024, 320, 5), (2, 2, 8, 7, 256, 31, 9),
                                               (32, 8, 1, 2, 1024, 160, 129), (8, 8, 2, 3, 576, 97, 257)])
 def test_small_calls_of_tuned_block_lengths(hq, hkv, B, I, n, m, t):
-    before = kv.lib().kvc_dev_stream_calls()
+    before, calls = kv.lib().kvc_dev_stream_calls(), kv.lib().kvc_dev_any_calls()
     decode_case(wl(n, I, B=B, hq=hq, hkv=hkv, t=t), m, packed=True)
-    assert kv.lib().kvc_dev_stream_calls() == before
+    assert kv.lib().kvc_dev_stream_calls() == before and kv.lib().kvc_dev_any_calls() == calls + 1
+
+
+@pytest.mark.parametrize("hq,hkv,B,I,n,m,t", [(32, 32, 1, 1, 576, 321, 0), (14, 2, 16, 1, 256, 103, 768), (28, 4, 1, 50, 256, 154, 1), (28, 4, 1, 2, 256, 103, 8192)])
+def test_calls_just_beyond_the_small_ones_take_the_tuned_kernels(hq, hkv, B, I, n, m, t):
+    calls = kv.lib().kvc_dev_any_calls()
+    L = layer_of(hq, hkv, B, I, n, m, t, packed=True)
+    step_of(L, L.ws)
+    assert kv.lib().kvc_dev_any_calls() == calls and torch.isfinite(L.out).all()
+    L.params = kv.make_params(L.g["key_idx"], L.g["theta"], L.g["U"], L.g["mu"])       # plain parameters: the same kernels, the same result
+    out = L.out.clone()
+    step_of(L, L.ws)
+    assert kv.lib().kvc_dev_any_calls() == calls
+    if n != 1024:
+        assert torch.equal(out, L.out)
 
 
 def test_small_ragged_batch_of_a_tuned_block_length():
