@@ -59,14 +59,6 @@ struct GPlan {
 
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// 16-byte register image of 8 elements, shifted down by `sh` elements (0 .. 8), zeros behind
-__device__ __forceinline__ u32x4 drop_elems(u32x4 v, int sh)
-{
-    const u32x4 r = shift_window(v, (sh >> 1) & 3, (sh & 1) * 16u);
-    const uint32_t keep = sh >= 8 ? 0u : 0xffffffffu;
-    return u32x4_mk(r.x & keep, r.y & keep, r.z & keep, r.w & keep);
-}
-
 // four consecutive values of a row of an LDS matrix in three planes of bf16 terms
 __device__ __forceinline__ void store_planes(uint16_t *dst, int plane, const float (&x)[4])
 {

@@ -147,6 +147,14 @@ __device__ __forceinline__ u32x4 shift_window(u32x4 wv, int ds, uint32_t bs)
                     __builtin_amdgcn_alignbit(x3, x2, bs), x3 >> bs);
 }
 
+// 16-byte register image of 8 elements, shifted down by `sh` elements (0 .. 8), zeros behind
+__device__ __forceinline__ u32x4 drop_elems(u32x4 v, int sh)
+{
+    const u32x4 r = shift_window(v, (sh >> 1) & 3, (sh & 1) * 16u);
+    const uint32_t keep = sh >= 8 ? 0u : 0xffffffffu;
+    return u32x4_mk(r.x & keep, r.y & keep, r.z & keep, r.w & keep);
+}
+
 // first query row of image block ub (b*I + i) of a KV head
 __host__ __device__ inline int unit_row(int ub, int UPBs, int G) { return ((ub >> UPBs) << 6) + (ub & ((1 << UPBs) - 1)) * G; }
 // rows of a 64-row block beyond its image blocks, and rows beyond the last image block, hold nothing

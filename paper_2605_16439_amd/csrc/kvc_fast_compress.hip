@@ -27,10 +27,12 @@
 // Keys (Sec. 3.1, "Selective Retention and Reconstruction for Keys"): every workgroup copies the
 // key rows that the mask selects for its own rows j, 16 bytes per lane, one pass of rows per step
 // of the projection, so the copy (and its writes) overlap the projection instead of preceding it.
-#include "kvc_internal.h"
+#include "kvc_decode_dev.h"
 
 namespace kvc {
 namespace {
+
+using dd::drop_elems;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -91,17 +93,6 @@ template <int LD> __device__ inline int sv_index(int c, int p) { return c * LD +
 // The scalar kernels that FORM 1 and 2 replace run one multiply-add per lane and load; the same two shapes here
 // (n = 729, m = 292, 12 image blocks: 595 -> 12.5 us; m = 410, 128 image blocks, GELU: 1011 -> 18.9 us) are
 // bound as FORM 0 is, by the latency of a tile step and, when few workgroups are resident, by their number.
-// 16-byte register image of 8 elements, shifted down by `sh` elements (sh >= 8: nothing is left)
-__device__ inline u32x4 drop_elems(u32x4 v, int sh)
-{
-    const int dw = sh >> 1;
-    const uint32_t bits = (sh & 1) * 16u;
-    const uint32_t y0 = dw & 1 ? v.y : v.x, y1 = dw & 1 ? v.z : v.y, y2 = dw & 1 ? v.w : v.z, y3 = dw & 1 ? 0u : v.w;
-    const uint32_t x0 = dw & 2 ? y2 : y0, x1 = dw & 2 ? y3 : y1, x2 = dw & 2 ? 0u : y2, x3 = dw & 2 ? 0u : y3;
-    const uint32_t keep = sh >= 8 ? 0u : 0xffffffffu;
-    return u32x4{__builtin_amdgcn_alignbit(x1, x0, bits) & keep, __builtin_amdgcn_alignbit(x2, x1, bits) & keep,
-                 __builtin_amdgcn_alignbit(x3, x2, bits) & keep, (x3 >> bits) & keep};
-}
 // GELU, erf form: x Phi(x) = max(x, 0) - |x| Q(|x|), Q(a) = erfc(a / sqrt 2) / 2 = exp(-a^2 / 2) t P(t) with
 // t = 1 / (1 + 0.21875 a).  P is a fit of degree 8 to the ratio over 0 <= a <= 14.5, largest relative error 6e-8.
 // Against float64 on N(0, 1) arguments: 3.6e-8 of the norm (0.5 x (1 + erff): 3.8e-8), and for negative x no

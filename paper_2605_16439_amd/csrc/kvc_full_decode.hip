@@ -301,7 +301,7 @@ kvc_status fast_full_decode(const FullCall &c)
         static_cast<const uint16_t *>(c.q), static_cast<uint16_t *>(c.K), static_cast<uint16_t *>(c.V),
         static_cast<const uint16_t *>(c.k_new), static_cast<const uint16_t *>(c.v_new), p);
     if (hipGetLastError() != hipSuccess) return KVC_ERR_HIP;
-    // no vision parts: mu is read (q stands in for it, at least H_kv d values) but does not enter the result
+    // no vision parts: mu is not read (q stands in for it)
     return finalize_parts(p.Ypart, p.NS, 0, p.rec, c.B, c.Hq, c.Hkv, c.q, c.out, c.lse, c.stream);
 }
 

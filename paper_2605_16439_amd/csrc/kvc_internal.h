@@ -140,7 +140,7 @@ kvc_status fast_decode(const DecodeCall &c);
 void fast_decode_knobs(int row_tiles, int separate, int wait_ticks);
 long fast_decode_fallbacks();
 // merges nparts part records ([G][128] un-normalised outputs, [G] maxima, [G] sums; the first nvp
-// of them vision parts, whose probability mass multiplies mu; without vision parts mu is read but not used)
+// of them vision parts, whose probability mass multiplies mu; without vision parts mu is not read)
 // of every (batch element, query head) into out / lse; nparts <= 64
 kvc_status finalize_parts(const float *Ypart, int nparts, int nvp, int rec, int B, int Hq, int Hkv, const void *mu,
                           void *out, float *lse, hipStream_t stream);

@@ -133,7 +133,7 @@ kvc_status fast_static_decode(const DecodeCall &c)
         static_cast<uint16_t *>(c.Kt), static_cast<uint16_t *>(c.Vt), static_cast<const uint16_t *>(c.k_new),
         static_cast<const uint16_t *>(c.v_new), p);
     if (hipGetLastError() != hipSuccess) return KVC_ERR_HIP;
-    // no vision parts: mu is read (q stands in for it, at least H_kv d values) but does not enter the result
+    // no vision parts: mu is not read (q stands in for it)
     return finalize_parts(p.Ypart, p.NP, 0, p.rec, c.s.batch, p.Hq, p.Hkv, c.q, c.out, c.lse, c.stream);
 }
 
