@@ -38,12 +38,25 @@
  *    element), m = ceil((1 - c) n) compressed length for compression ratio c,
  *    t text tokens in the cache.
  *  - The matrix-core (MFMA) kernels cover bf16 with d = 128: compression for n >= 8; the first layer of the
- *    two-layer key reconstructor for m >= 8; decode for n >= 8 and G <= 16.  Decode kernels tuned further, with
- *    scores and weights rounded to bf16 between the steps, serve n in {256, 576, 1024}, G in {1, 2, 4, 6, 7, 8}
- *    and at most 256 partial results per (batch element, KV head), save small calls with packed parameters; every
- *    other decode keeps them at float32 precision.  fp32, and bf16 with another d, run compression and decode on the fp32 matrix instruction
- *    (n >= 4, G <= 16).  What is left runs shape-agnostic scalar kernels: same results within rounding, far
- *    lower speed; their decode is limited to n <= 16384 (KVC_ERR_UNSUPPORTED beyond).
+ *    two-layer key reconstructor for m >= 8; decode for 8 <= n <= 6144, m <= 1152 and G <= 16.  Decode kernels tuned
+ *    further, with scores and weights rounded to bf16 between the steps, serve n in {256, 576, 1024}, G in
+ *    {1, 2, 4, 6, 7, 8} and at most 256 partial results per (batch element, KV head), save small calls with packed
+ *    parameters and a text_cap of at most 8192; every other decode keeps them at float32 precision.  fp32, bf16 with
+ *    another d, and bf16 with d = 128 beyond those limits run compression (n >= 4) and decode (4 <= n <= 12288,
+ *    m <= 1952, G <= 16) on the fp32 matrix instruction.  What is left runs shape-agnostic scalar kernels: same
+ *    results within rounding, far lower speed; decode is limited to n <= 16384 (KVC_ERR_UNSUPPORTED beyond).
+ *    Which kernel serves a decode call follows from the shape, text_cap, the parameter forms and the workspace size,
+ *    not from text_len -- save that the tuned kernels hand long texts on, the one-pass kernel to the others and these,
+ *    at 256 partial results, to the kernels for any shape -- so a generation keeps its kernel.  Packed and plain
+ *    parameters may run on different kernels, and then differ by the rounding of scores and weights.
+ *  - A decode call whose workspace is smaller than kvc_workspace_bytes says is served as long as it is enough for the
+ *    scalar kernels (n = 256, 576, 1024: for the tuned ones), if need be by these; below that it is refused with
+ *    KVC_ERR_WORKSPACE, whatever kernel would serve it.
+ *  - Parameters are taken to be finite.  A non-finite query reaches its own head only.  A non-finite value among V, the
+ *    compressed values or the text values reaches its own channel of its own (batch element, KV head) only (in the tuned
+ *    decode kernels perhaps a neighbouring channel too), and no other sequence.  An infinite result stays an infinity in
+ *    compression, in the hidden rows, in the static variant and, outside the tuned kernels, for text values; elsewhere
+ *    it may come out as a NaN: a decode adds up parts whose weights for a compressed value have either sign.
  */
 #ifndef KVCAPSULE_H
 #define KVCAPSULE_H
@@ -126,7 +139,9 @@ kvc_status kvc_memory_footprint(const kvc_shape *shape, int64_t c_prompt, int64_
  * "Prefilling Stage"):
  *     Kc[b,h,i,j,:] = K[b,h, vis_start + i n + M[j], :]            (bit-exact copy)
  *     Vc[b,h,i,j,:] = sum_p U[h,j,p] (V[b,h, vis_start + i n + p, :] - mu[h,:])
- * with fp32 accumulation and one round-to-nearest-even to the storage type.
+ * with fp32 accumulation and one round-to-nearest-even to the storage type.  bf16 with d = 128 evaluates it as
+ * U V - (U 1) mu^T: the same after the rounding, but a channel that equals its centre throughout comes out as float32
+ * rounding (about 1e-6 |mu|) and not as zeros.
  *  K, V  in : [B][H_kv][S][d], S = seq_len, with element strides stride_b / stride_h /
  *             stride_s (d contiguous; strides multiples of 8 elements); rows outside the
  *             span [vis_start, vis_start + I n) are not touched -- text K/V stays
@@ -209,9 +224,10 @@ kvc_status kvc_pack_u(const kvc_shape *shape, const void *U, void *packed, void 
  *             clamped on the device to [0, I] and [0, text_cap] ([0, text_cap - 1] with a new token).
  *             A sequence left with no key at all gets NaNs.
  * Everything else as in kvc_reconstruct_attend_decode, the kernels included (matrix cores for the shapes
- * that have them, the one-pass kernel with kvc_params.theta_packed; a uniform batch gives the uniform call's result bit for bit).  Capsule slots beyond
- * n_images[b] may be read but never reach the result, whatever they hold (NaNs included); text rows
- * beyond the sequence's own are not read.
+ * that have them, the one-pass kernel with the packed parameters).  A uniform batch gives the uniform call's result
+ * bit for bit, save on the one-pass kernel of n = 1024, which shares out the text rows by text_len there and by text_cap
+ * here (the same up to the order of float32 sums).  Capsule slots beyond n_images[b] may be read but never reach the
+ * result, whatever they hold (NaNs included); text rows beyond the sequence's own are not read.
  * Errors: as kvc_reconstruct_attend_decode, plus NULL / misaligned count arrays, text_cap < 1. */
 kvc_status kvc_reconstruct_attend_decode_ragged(const kvc_shape *shape, const kvc_params *params,
                                                 const void *q, const void *Kc, const void *Vc,
@@ -242,8 +258,8 @@ kvc_status kvc_mlp_hidden(const kvc_shape *shape, const void *W1, int32_t activa
  * reconstruction disabled, the compressed KV used directly throughout decoding): plain attention over
  * the I*m compressed rows of each (batch element, KV head) and the text rows,
  *     out[b,g,:] = softmax(scale * q[b,g] . [Kc[b,g/G] ; K_text]^T) [Vc[b,g/G] ; V_text],
- * no theta, no U^T, no mu.  Arguments as in kvc_reconstruct_attend_decode (Vc in its blocked layout;
- * shape->n_img_tokens is not used).  bf16 with d = 128 and G <= 16 runs on the matrix cores (weights kept at
+ * no theta, no U^T, no mu.  Arguments and limits as in kvc_reconstruct_attend_decode (Vc in its blocked layout;
+ * shape->n_img_tokens takes no part in the result).  bf16 with d = 128 and G <= 16 runs on the matrix cores (weights kept at
  * float32 precision), the rest on the shape-agnostic scalar kernels. */
 kvc_status kvc_static_attend_decode(const kvc_shape *shape, const void *q, const void *Kc, const void *Vc,
                                     void *K_text, void *V_text, int32_t text_len, int32_t text_cap,
@@ -264,11 +280,12 @@ kvc_status kvc_unpack_values(const void *Vc, void *dense, int64_t records, int32
 
 /* For callers that cannot allocate or hand over device memory at call time (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): kvc_reconstruct_attend_decode
- * without the workspace arguments.  Same operation, same kernels, same results; the scratch lives in a
- * device array inside the library, kvc_static_scratch_bytes() = 32 MiB per GPU, held until the process
- * ends.  The call allocates nothing and frees nothing.  A shape whose kvc_workspace_bytes(shape,
- * text_cap) exceeds that size is refused with KVC_ERR_WORKSPACE before anything is launched (the five
- * benchmark configurations fit).  Every call on a GPU shares that GPU's one array: calls that overlap
+ * without the workspace arguments: the call above with a workspace of kvc_static_scratch_bytes() = 32 MiB.
+ * The scratch lives in a device array inside the library, one per GPU, held until the process ends.  The
+ * call allocates nothing and frees nothing.  Same kernels and same results where kvc_workspace_bytes(shape,
+ * text_cap) does not exceed that size (the five benchmark configurations fit); beyond it a shape runs on
+ * kernels that need less, or is refused with KVC_ERR_WORKSPACE before anything is launched where the scalar or
+ * tuned kernels need more.  Every call on a GPU shares that GPU's one array: calls that overlap
  * on one GPU (two streams, overlapping graph replays) race on it and must be ordered by the caller;
  * the array keeps the previous call's contents, none of which a later call relies on. */
 size_t kvc_static_scratch_bytes(void);

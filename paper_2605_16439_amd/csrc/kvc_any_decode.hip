@@ -1,6 +1,7 @@
 // Decode step for the shapes that the tuned kernels are not compiled for, and for small calls of the others
-// (any_decode_preferred): bf16 storage, head_dim 128, any number n >= 8 of tokens per image block, any compressed length, at most 16 query heads per KV head.  One launch in the
-// score-space order of Alg. 1, then the merge of the part records:
+// (small_call): bf16 storage, head_dim 128, 8 to 6144 tokens per image block (48 slices of 128), compressed lengths up to
+// 1152 (LDS), at most 16 query heads per KV head.  One launch in the score-space order of Alg. 1, then the merge of the
+// part records:
 //
 //   ga_pass   a vision workgroup owns a slice of PS positions of one (batch element, KV head) and walks tiles of
 //             UP image blocks (UP G <= 16 query rows, one matrix-core tile):
@@ -18,13 +19,13 @@
 // What bounds it: like fs_stream (kvc_stream_decode.hip) the latency of the four dependent phases for a few
 // workgroups, and for many the bytes pulled through the L1s -- every slice reads the blocks' keys and values, and
 // every tile of rows its slices of theta and U.  So a slice is as wide as leaves a workgroup per compute unit
-// (make_gplan).  theta and U come in the packed forms where the caller has them (PK); from the plain form theta is
-// read two bytes at a time (its rows are the contraction index, and at odd n start at odd elements), U in 16-byte
-// pieces at element alignment.
+// (make_gplan).  theta and U come in the packed forms where the caller has them (PK); from the plain form both are read
+// in 16-byte pieces of rows at element alignment (at odd n rows start at odd elements).  theta's rows are the contraction
+// index: its pieces are turned into operands in registers, 8 rows by 8 positions per lane; U's through LDS.
 //
 // n = 729, m = 292, 3 blocks, B = 1, 28/4 heads, 201 text rows: 205 us per layer on the scalar
-// kernels (six launches; their output step alone 135 us), 16.4 us here -- 12 us in this kernel (keys 3.5, theta 1.5,
-// softmax 1.7, U 2.4, values 2.0), the rest launches and the merge.
+// kernels (six launches; their output step alone 135 us), 16.0 us here -- 13.8 us in this kernel at best, 14.7 on average
+// (kernel trace; keys, theta, softmax, U and values about 3 : 1.5 : 1.5 : 2 : 2), the rest the merge.
 #include "kvc_rows_dev.h"
 
 #include <algorithm>
@@ -642,7 +643,7 @@ __global__ __launch_bounds__(64 * kGW) void ga_pass(const uint16_t *__restrict__
 }
 
 constexpr size_t kPassLds = 156 * 1024;
-constexpr int kOneEach = 256;         // workgroups that find a compute unit each
+constexpr int kOneEach = 256;         // workgroups that find a compute unit each (MI355X has 256)
 std::atomic<long> g_any_calls{0};     // debug counter (kvc_dev_any_calls)
 
 // false: no plan (slices or LDS beyond what the kernel holds).  What decides the order of the sums -- slices, tiles, the

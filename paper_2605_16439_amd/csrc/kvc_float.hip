@@ -1,6 +1,7 @@
 // fp32 storage, and bf16 storage with a head_dim other than 128: compression and decode on the fp32 matrix
-// instruction of gfx950 (v_mfma_f32_16x16x4_f32: fp32 operands and sums), any n >= 4, any m, head_dim up to 256, at
-// most 16 query heads per KV head.  bf16 values are widened where they are loaded.
+// instruction of gfx950 (v_mfma_f32_16x16x4_f32: fp32 operands and sums), head_dim up to 256.  Compression: any n >= 4,
+// any m.  Decode: n from 4 to 12288 (48 slices of 256), m up to 1952 (LDS), at most 16 query heads per KV head; also bf16
+// with head_dim 128 beyond the limits of ga_pass.  bf16 values are widened where they are loaded.
 //
 //   gx_project  Vc = U (V - 1 mu^T) for 16 rows of U of one image block: eight wavefronts share the positions and add
 //               up through LDS.  The workgroup's key rows are copied by the way.

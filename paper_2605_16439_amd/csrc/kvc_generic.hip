@@ -4,7 +4,8 @@
 // text keys (Sec. 3.2):
 //     S = sigma q Kc^T  ->  L = S theta  ->  P = softmax([L ; text logits])
 //     W = P_vis U^T     ->  out = sum_blocks W Vc + (sum P_vis) mu + P_txt V_text
-// What the matrix-core kernels do not cover runs here: block lengths below four, more than 16 query heads per KV head,
+// What the matrix-core kernels do not cover runs here: blocks of fewer than 4 or more than 12288 tokens, compressed
+// lengths above 1952, more than 16 query heads per KV head, workspaces too small for the part records of the others,
 // the static variant, the full-cache comparison and the first layer of the two-layer reconstructor outside bf16 with
 // d = 128 -- and, through the forced entry points, anything, as a second implementation to check against.
 #include "kvc_internal.h"

@@ -79,7 +79,9 @@ __device__ __forceinline__ void walk_once(const Rows &p, const uint16_t *__restr
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r16 = lane & 15, kg = lane >> 4;
     const int nfull = p.m >> 3, wt = p.m & 7;
-    // key rows of a tile are permuted (see the top of the file)
+    // Key rows of a tile are permuted: tile tt, row i holds key row 8 (i / 4) + 4 tt + i % 4 of the step.  A lane's
+    // probabilities are then those of 8 consecutive rows, and a 16-byte piece of the compressed values (8 consecutive
+    // rows of one channel) is the other operand as it lies in memory.
     const int krow = 8 * (r16 >> 2) + (r16 & 3);
 
     // step s: first row, and how many rows from there on exist (at most 32 count)

@@ -18,7 +18,7 @@
 // wavefront: 20 times the rate at which memory delivers).
 //
 // Headline capsule (B = 4, 28 / 4 heads, 8 blocks of m = 410, 513 text rows, 31 MB): 595 us on the scalar
-// kernels (output kernel 472 us: a workgroup per query head), 12.3 us here -- this kernel 8 to 10 us, the merge 2 to 4
+// kernels (output kernel 472 us: a workgroup per query head), 12.4 us here -- this kernel 9 to 10 us, the merge 2 to 3
 // (15.0 us while every wavefront also requested the step behind its run; runs of two steps instead of one 13.3).
 #include "kvc_rows_dev.h"
 

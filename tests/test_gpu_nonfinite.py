@@ -27,15 +27,20 @@ def normal(seed, *size, dtype=torch.bfloat16):
 # H_kv rows a merge kernel would read as mu) must not reach other sequences or heads.
 @pytest.mark.parametrize("bad", [NAN, INF])
 @pytest.mark.parametrize("what,dtype,d", [("static", torch.bfloat16, 128), ("static", torch.float32, 64), ("full", torch.bfloat16, 128),
-                                          ("full", torch.float32, 64), ("text only", torch.bfloat16, 128), ("text only", torch.float32, 64)])
+                                          ("full", torch.float32, 64), ("text only", torch.bfloat16, 128), ("text only", torch.float32, 64),
+                                          ("decode", torch.bfloat16, 128), ("decode", torch.float32, 64), ("tuned", torch.bfloat16, 128),
+                                          ("packed", torch.bfloat16, 128)])
 def test_non_finite_query_stays_in_its_own_head(what, dtype, d, bad):
     B, hq, hkv, I, m, t = 3, 14, 2, 2, 41, 70
     I = 0 if what == "text only" else I
     cap = t + 1
-    shape = kv.make_shape(B, hq, hkv, d, 100, I, m, dtype)
-    mu = torch.full((hkv, d), bad, dtype=dtype, device=DEV)      # text only: a centre that no vision row refers to
-    par = [normal(1, hkv, m, 100, dtype=dtype), normal(2, hkv, m, 100, dtype=dtype)]
-    params = kv.make_params(torch.arange(m, dtype=torch.int32, device=DEV), *par, mu)
+    n = 256 if what in ("tuned", "packed") else 100
+    shape = kv.make_shape(B, hq, hkv, d, n, I, m, dtype)
+    # text only: a centre that no vision row refers to
+    mu = torch.full((hkv, d), bad if what == "text only" else 0.5, dtype=dtype, device=DEV)
+    par = [normal(1, hkv, m, n, dtype=dtype), normal(2, hkv, m, n, dtype=dtype)]
+    packed = [kv.kvc_pack_theta(shape, par[0]), kv.kvc_pack_u(shape, par[1])] if what == "packed" else []
+    params = kv.make_params(torch.arange(m, dtype=torch.int32, device=DEV), *par, mu, *packed)
     Kc, Vc = normal(3, B, hkv, max(I, 1), m, d, dtype=dtype), normal(4, B, hkv, max(I, 1), m, d, dtype=dtype)
     kn, vn = normal(5, B, hkv, d, dtype=dtype), normal(6, B, hkv, d, dtype=dtype)
     if what == "full":
