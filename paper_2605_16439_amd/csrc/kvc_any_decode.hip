@@ -41,15 +41,16 @@ typedef u32x4 u32x4_a2 __attribute__((aligned(2)));     // a 16-byte access at a
 
 constexpr int kGW = 8;                // wavefronts
 constexpr int kMaxVisParts = 48, kMaxTextParts = 16;   // part records per (batch element, KV head): a lane each in the merge
-constexpr int kTextStep = kSR * kSW;  // text rows of a workgroup's step; run r takes the steps r, r + 16, r + 32, ...
+constexpr int kTextStep = kSR * kSW;  // text rows of a workgroup's step
 
 struct GPlan {
     int B, Hq, Hkv, G, I, n, m, KS;
     int PS, UP, NUT, NUG, F;          // positions per slice, image blocks per tile, tiles per workgroup, unit groups per sequence, slices
     int NGR, chunk, nvis;             // (head, sequence, unit group) groups, groups per XCD, vision workgroups
-    int NTX, NTC, nparts, rec;        // text runs per (batch element, KV head), those of a cache filled to its capacity
+    int NTX, NTC, nparts, rec;        // text runs per (batch element, KV head), those of a cache filled to its capacity:
+                                      // run r takes the steps r, r + NTC, r + 2 NTC, ...
     int t, t_in, cap;
-    unsigned qF, qBU, qNUG, qT, qNTX, qHkv, qKS;
+    unsigned qF, qBU, qNUG, qT, qNTX, qHkv, qKS, qNTC, qst;
     float scale;
     float *Ypart;
     const int32_t *n_img, *tlen;      // ragged batch (RAG): per-sequence counts; I, t and t_in are then the largest
@@ -193,13 +194,14 @@ __global__ __launch_bounds__(64 * kGW) void ga_pass(const uint16_t *__restrict__
 #pragma unroll
             for (int k = 0; k < 4; ++k) qf[k] = qp[4 * k];
             Rows rw;
-            rw.I = 0; rw.m = 8; rw.KS = 1; rw.SV = 0; rw.qKS = 0; rw.t = t; rw.cs = 1 << 30; rw.scale = p.scale;
-            walk<true, kSW * kMaxTextParts>(rw, Ktb, Vtb, kn, vn, fresh ? t_in : -1, qf, s0, sVt[wave], m_run, l_run, acc);
+            rw.I = 0; rw.m = 8; rw.KS = 1; rw.SV = 0; rw.qKS = 0; rw.t = t; rw.cs = 1 << 30; rw.st = kSW * p.NTC; rw.qst = p.qst; rw.scale = p.scale;
+            walk<true>(rw, Ktb, Vtb, kn, vn, fresh ? t_in : -1, qf, s0, sVt[wave], m_run, l_run, acc);
         }
         merge_waves(sVt, sM, sL, m_run, l_run, acc, G,
                     p.Ypart + (static_cast<size_t>(bh) * p.nparts + p.NUG * p.F + tc) * p.rec);
         // Sec. 3.2: the text cache keeps growing as in the backbone -- store the new token's k, v
-        if (fresh && static_cast<unsigned>(t_in) / kTextStep % kMaxTextParts == static_cast<unsigned>(tc) && threadIdx.x < 32) {
+        const int own = t_in / kTextStep;
+        if (fresh && own - quot(own, p.qNTC) * p.NTC == tc && threadIdx.x < 32) {
             const int half = threadIdx.x >> 4, piece = threadIdx.x & 15;
             uint16_t *dst = (half ? Vtb : Ktb) + static_cast<size_t>(t_in) * D;
             *(reinterpret_cast<u32x4 *>(dst) + piece) = *(reinterpret_cast<const u32x4 *>(half ? vn : kn) + piece);
@@ -669,13 +671,20 @@ bool make_gplan(GPlan &p, const kvc_shape &s, int t, int t_in, int cap)
     p.PS = ps;
     p.F = (p.n + ps - 1) / ps;
     if (p.F > kMaxVisParts || pass_lds(p.m, ps, false) > kPassLds) return false;
-    auto runs = [](int rows) { return std::min((rows + kTextStep - 1) / kTextStep, kMaxTextParts); };
-    p.NTX = runs(t);
-    p.NTC = runs(cap);
-    // smaller tiles as long as every workgroup, those of the text with them, still has a compute unit to itself and one
-    // tile: 12 blocks of n = 576, m = 346, B = 1, 12/2 heads, two tiles per workgroup 24.6 us, one twice as full 20.5
+    // (as many runs as give every one the same number of steps in a full cache: the chip is full of workgroups where the
+    // text is long, and takes 12 runs of two steps in less time than 16 of one or two)
+    auto steps = [](int rows) { return (rows + kTextStep - 1) / kTextStep; };
+    const int each = std::max(1, (steps(cap) + kMaxTextParts - 1) / kMaxTextParts);
+    p.NTC = std::max(1, (steps(cap) + each - 1) / each);
+    p.NTX = std::min(steps(t), p.NTC);
+    // Smaller tiles as long as every workgroup, those of a full text cache with them, still has a compute unit to itself and
+    // one tile: 12 blocks of n = 576, m = 346, B = 1, 12/2 heads, two tiles per workgroup 24.6 us, one twice as full 20.5.
+    // Where the text's workgroups would come behind, in a second round of some 3 us, only if that saves 16 steps of 32
+    // compressed rows (a second round against full tiles: 8/8 heads, B = 2, 3 blocks of n = 600, m = 97, 300 text rows, 4
+    // steps saved 14.2 / 12.0 us; 16/8, B = 2, 12 blocks of n = 379, m = 178, 2000 rows, 24 steps saved 22.1 / 33.1).
     if (ps == 128)
-        for (int up = (p.UP + 1) / 2; p.UP > 1 && groups(up) * p.F + bh * p.NTC <= kOneEach && (p.I + up - 1) / up * p.F <= kMaxVisParts;
+        for (int up = (p.UP + 1) / 2; p.UP > 1 && groups(up) * p.F <= kOneEach && (p.I + up - 1) / up * p.F <= kMaxVisParts &&
+                                      (groups(up) * p.F + bh * p.NTC <= kOneEach || (p.UP - up) * p.KS >= 16);
              up = (p.UP + 1) / 2)
             p.UP = up;
     const int tiles = (p.I + p.UP - 1) / p.UP, ug_max = kMaxVisParts / p.F;
@@ -688,6 +697,7 @@ bool make_gplan(GPlan &p, const kvc_shape &s, int t, int t_in, int cap)
     p.rec = static_cast<int>(align_up(p.G * D + 2 * p.G, 4));
     p.qF = quot_multiplier(p.F); p.qBU = quot_multiplier(p.B * p.NUG); p.qNUG = quot_multiplier(p.NUG);
     p.qT = quot_multiplier(2 * p.KS); p.qNTX = quot_multiplier(p.NTX); p.qHkv = quot_multiplier(p.Hkv); p.qKS = quot_multiplier(p.KS);
+    p.qNTC = quot_multiplier(p.NTC); p.qst = quot_multiplier(kSW * p.NTC);
     p.n_img = p.tlen = nullptr;
     // quot(): dividends below 2^32 / divisor; 32-bit offsets into a head's theta and U
     const long lim = 1l << 31;
@@ -723,17 +733,20 @@ static bool any_shape(const kvc_shape &s)
     return s.dtype == KVC_BF16 && s.head_dim == D && s.n_q_heads / s.n_kv_heads <= 16 && s.n_img_tokens >= 8;
 }
 
-// Calls of shapes with tuned kernels that take less time here: a compute unit for every workgroup, the text's among them, at
-// most 10 steps of 32 compressed rows per workgroup, whose chains are its time, and text runs of at most 4 steps.  us per
-// layer, tuned kernels against this pass: n = 256, m = 154, 16 blocks, 28/4 heads 16.5 / 11.5, 32 blocks (10 steps) 16.6 / 14.0;
-// n = 576, m = 144, 5 blocks 14.9 / 12.0, 12 blocks (10 steps) 14.9 / 13.1; n = 1024, m = 256, one block 14.6 / 12.6, 8 blocks
-// (16 steps) 13.3 / 16.5; m = 615 (20 steps) 19.5 / 21.4.  Text rows at n = 256, m = 103, 2 blocks, 28/4 heads, B = 1:
-// 4000 16.0 / 12.0, 8000 (4 steps per run) 18.5 / 17.7, 16000 20.7 / 27.2, 28000 26.7 / 41.3: the tuned kernels give every
+// Calls of shapes with tuned kernels that take less time here: a compute unit for every vision workgroup, at most 10 steps of
+// 32 compressed rows in each, whose chains are its time, at most 512 workgroups with one for every 128 rows of a full text
+// cache, and text runs of at most 4 steps.  us per layer, tuned kernels against this pass: n = 256, m = 154, 16 blocks, 28/4
+// heads 16.5 / 11.5, 32 blocks (10 steps) 16.6 / 14.0; n = 576, m = 144, 5 blocks 14.9 / 12.0, 12 blocks (10 steps) 14.9 / 13.1;
+// n = 1024, m = 256, one block 14.6 / 12.6, 8 blocks (16 steps) 13.3 / 16.5; m = 615 (20 steps) 19.5 / 21.4.  Workgroups, at
+// n = 576, m = 200, one block, B = 4, 16/8 heads: 448 (1000 text rows) 17.3 / 16.2, 704 19.8 / 20.6, 1216 25.6 / 31.6; at n = 256,
+// m = 103, one block, B = 16, 14/2 heads: 320 16.6 / 13.1, 576 18.9 / 19.6.  Text rows at n = 256, m = 103, 2 blocks, 28/4 heads,
+// B = 1: 4000 16.0 / 12.0, 8000 (4 steps per run) 18.5 / 17.7, 16000 20.7 / 27.2, 28000 26.7 / 41.3: the tuned kernels give every
 // 128 rows a workgroup.
 static bool small_call(const GPlan &p)
 {
-    return p.I > 0 && p.NUT == 1 && p.UP * p.KS <= 10 && p.cap <= 4 * kMaxTextParts * kTextStep &&
-           static_cast<long>(p.NGR) * p.F + static_cast<long>(p.B) * p.Hkv * p.NTC <= kOneEach;
+    const long vision = static_cast<long>(p.NGR) * p.F, text = static_cast<long>(p.B) * p.Hkv * ((p.cap + kTextStep - 1) / kTextStep);
+    return p.I > 0 && p.NUT == 1 && p.UP * p.KS <= 10 && vision <= kOneEach && vision + text <= 2 * kOneEach &&
+           p.cap <= 4 * kMaxTextParts * kTextStep;
 }
 
 bool any_decode_supported(const kvc_shape &s)
@@ -744,10 +757,8 @@ bool any_decode_supported(const kvc_shape &s)
 
 size_t any_decode_ws_bytes(const kvc_shape &s, int32_t max_text)
 {
-    // (tiles, and with them the part records, are smallest and most where the text cache is small)
     GPlan p;
-    const int none = s.n_images > 0 ? 0 : 1;
-    if (!make_gplan(p, s, none, 0, none)) return 0;
+    if (!make_gplan(p, s, s.n_images > 0 ? 0 : 1, 0, std::max(max_text, 1))) return 0;
     const int ntx = std::min((std::max(max_text, 1) + kTextStep - 1) / kTextStep, kMaxTextParts);
     return kCounterBytes + static_cast<size_t>(p.B) * p.Hkv * (p.NUG * p.F + ntx) * p.rec * sizeof(float) + kTimelineBytes;
 }

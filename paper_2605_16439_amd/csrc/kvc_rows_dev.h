@@ -18,8 +18,8 @@ constexpr int kLDO = D + 4;           // floats per head row of a wavefront's ou
 struct Rows {
     int I, m, KS, SV;                 // compressed rows: blocks of m rows, KS 32-row steps each, SV = I KS steps
     int t;                            // rows of the text cache
-    int cs;                           // steps per wavefront and run, at most
-    unsigned qKS;
+    int cs, st;                       // steps per wavefront and run, at most; their distance
+    unsigned qKS, qst;
     float scale;
 };
 
@@ -69,9 +69,9 @@ __device__ __forceinline__ u32x4 finite_elems(u32x4 v)
     return u32x4_mk(one(v.x), one(v.y), one(v.z), one(v.w));
 }
 
-// One wavefront's pass over its steps of a run: s0 + wave, then every ST-th.  TEXT: rows of the text cache, else compressed rows.
-// GUARD: infinities among the values stay infinities (see walk()).
-template <bool TEXT, int ST, bool GUARD>
+// One wavefront's pass over its steps of a run: s0 + wave, then every p.st-th.  TEXT: rows of the text cache, else compressed
+// rows.  GUARD: infinities among the values stay infinities (see walk()).
+template <bool TEXT, bool GUARD>
 __device__ __forceinline__ void walk_once(const Rows &p, const uint16_t *__restrict__ Kb, const uint16_t *__restrict__ Vb,
                                      const uint16_t *__restrict__ kn, const uint16_t *__restrict__ vn, int t_new,
                                      const u32x4 (&qf)[4], int s0, uint32_t *vt, float &m_run, float &l_run, f32x4 (&acc)[8])
@@ -207,7 +207,7 @@ __device__ __forceinline__ void walk_once(const Rows &p, const uint16_t *__restr
     // Two steps in flight in two register sets.  No step is requested that the run does not have: with runs of one or
     // two steps a request ahead of the end would double what the kernel reads.
     const int all = TEXT ? (p.t + kSR - 1) / kSR : p.SV;
-    const int left_w = all - s0 - wave, N = left_w > 0 ? min(static_cast<int>(static_cast<unsigned>(left_w + ST - 1) / ST), p.cs) : 0;
+    const int ST = p.st, left_w = all - s0 - wave, N = left_w > 0 ? min(quot(left_w + ST - 1, p.qst), p.cs) : 0;
     if (N == 0) return;
     const int sw = s0 + wave;
     u32x4 kA[2][4], vA[8], kB[2][4] = {}, vB[8] = {};
@@ -228,7 +228,7 @@ __device__ __forceinline__ void walk_once(const Rows &p, const uint16_t *__restr
 // channel) and the lower terms of the others make NaNs of infinities among the values.  Such values are not expected, so the
 // sums are looked at once, behind the pass, and where they hold a NaN the pass is repeated with the values guarded: guarding
 // every step costs 5 %, the look 1.5 % (B = 16, 32/8 heads, 5 blocks of m = 231, 256 text rows: 23.9, 25.1 and 24.2 us).
-template <bool TEXT, int ST>
+template <bool TEXT>
 __device__ __forceinline__ void walk(const Rows &p, const uint16_t *__restrict__ Kb, const uint16_t *__restrict__ Vb,
                                      const uint16_t *__restrict__ kn, const uint16_t *__restrict__ vn, int t_new,
                                      const u32x4 (&qf)[4], int s0, uint32_t *vt, float &m_run, float &l_run, f32x4 (&acc)[8])
@@ -240,14 +240,14 @@ __device__ __forceinline__ void walk(const Rows &p, const uint16_t *__restrict__
         for (int ct = 0; ct < 8; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
     start();
-    walk_once<TEXT, ST, false>(p, Kb, Vb, kn, vn, t_new, qf, s0, vt, m_run, l_run, acc);
+    walk_once<TEXT, false>(p, Kb, Vb, kn, vn, t_new, qf, s0, vt, m_run, l_run, acc);
     f32x4 sum = acc[0];
 #pragma unroll
     for (int ct = 1; ct < 8; ++ct) sum += acc[ct];
     const float x = (sum[0] + sum[1]) + (sum[2] + sum[3]);
     if (__any(x != x)) {
         start();
-        walk_once<TEXT, ST, true>(p, Kb, Vb, kn, vn, t_new, qf, s0, vt, m_run, l_run, acc);
+        walk_once<TEXT, true>(p, Kb, Vb, kn, vn, t_new, qf, s0, vt, m_run, l_run, acc);
     }
 }
 

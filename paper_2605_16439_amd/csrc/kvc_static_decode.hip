@@ -68,9 +68,9 @@ __global__ __launch_bounds__(64 * kSW, 2) void static_split(const uint16_t *__re
     const bool text = pt >= p.NV;
     const int s0 = (text ? pt - p.NV : pt) * p.cs * kSW;
     if (text)
-        walk<true, kSW>(p, Ktb, Vtb, kn, vn, fresh ? p.t_in : -1, qf, s0, sVt[wave], m_run, l_run, acc);
+        walk<true>(p, Ktb, Vtb, kn, vn, fresh ? p.t_in : -1, qf, s0, sVt[wave], m_run, l_run, acc);
     else
-        walk<false, kSW>(p, Kc + static_cast<size_t>(bh) * p.I * p.m * D, Vc + static_cast<size_t>(bh) * p.I * p.m * D, kn, vn, -1, qf, s0,
+        walk<false>(p, Kc + static_cast<size_t>(bh) * p.I * p.m * D, Vc + static_cast<size_t>(bh) * p.I * p.m * D, kn, vn, -1, qf, s0,
                     sVt[wave], m_run, l_run, acc);
 
     merge_waves(sVt, sM, sL, m_run, l_run, acc, p.G, p.Ypart + (static_cast<size_t>(bh) * p.NP + pt) * p.rec);
@@ -101,6 +101,7 @@ bool make_st_plan(StPlan &p, const kvc_shape &s, int t, int t_in, int cap)
     p.NV = (wv + p.cs - 1) / p.cs;
     p.NP = p.NV + (wt + p.cs - 1) / p.cs;
     p.rec = static_cast<int>(align_up(p.G * D + 2 * p.G, 4));
+    p.st = kSW; p.qst = quot_multiplier(kSW);
     p.qNP = quot_multiplier(p.NP); p.qHkv = quot_multiplier(p.Hkv); p.qKS = quot_multiplier(p.KS);
     // quot(): dividends below 2^32 / divisor
     return p.NP > 0 && bh * p.NP * std::max(p.NP, p.Hkv) < (1ll << 32) && static_cast<long>(p.SV) * p.KS < (1ll << 32);

@@ -250,7 +250,7 @@ def test_plan_follows_from_the_capacity_of_the_text_cache(hq, hkv, B, I, n, m, k
         for t in {1, cap // 3, cap}:
             p = decode_plan(hq, hkv, B, I, n, m, t, cap, kernel, dtype, d)
             assert p[:5] == full[:5] and p[6:] == full[6:]
-            assert p[5] == min(-(-t // 128), 16) and p[6] == -(-cap // 2048)
+            assert p[5] <= 16 and p[5] == min(-(-t // 128), full[5]) and p[6] == -(-cap // 2048)
 
 
 @pytest.mark.parametrize("hq,hkv,B,I,n,m,tile", [(8, 2, 1, 16, 576, 231, 4), (14, 2, 1, 4, 1024, 410, 2), (8, 2, 1, 4, 576, 231, 1), (8, 2, 1, 1, 576, 231, 1),
@@ -261,12 +261,13 @@ def test_fp32_tiles_shrink_only_while_every_workgroup_keeps_one(hq, hkv, B, I, n
 
 
 def test_small_calls_of_tuned_block_lengths_and_those_just_beyond():
-    """10 steps of 32 rows, 256 workgroups with the text's among them, text runs of 4 steps of 128 rows."""
+    """10 steps of 32 rows, 256 vision workgroups, 512 with one per 128 rows of a full text cache, text runs of 4 steps."""
     small = lambda *a: decode_plan(*a)[7]
     assert small(32, 32, 1, 1, 576, 320, 1, 64) and not small(32, 32, 1, 1, 576, 321, 1, 64)           # 10 / 11 steps
     assert small(28, 4, 1, 32, 256, 154, 1, 64) and not small(28, 4, 1, 64, 256, 154, 1, 64)           # one tile / several per workgroup
     # 32 pairs x 2 slices, and 32 workgroups per 128 rows of capacity
-    assert small(14, 2, 16, 1, 256, 103, 1, 768) and not small(14, 2, 16, 1, 256, 103, 1, 769)
+    assert small(14, 2, 16, 1, 256, 103, 1, 1792) and not small(14, 2, 16, 1, 256, 103, 1, 1793) and not small(14, 2, 16, 1, 256, 103, 1, 2100)
+    assert small(14, 2, 64, 1, 256, 103, 1, 128) and not small(14, 2, 65, 1, 256, 103, 1, 128)         # 256 / 260 vision workgroups
     assert small(28, 4, 1, 2, 256, 103, 1, 8192) and not small(28, 4, 1, 2, 256, 103, 1, 8193)         # 4 / 5 steps per text run
     assert not small(28, 4, 1, 0, 256, 103, 1, 64)
     assert decode_plan(34, 2, 1, 1, 256, 103, 1, 64) is None and decode_plan(4, 2, 1, 1, 7, 3, 1, 64) is None

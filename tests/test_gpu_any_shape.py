@@ -186,8 +186,8 @@ def test_ragged_batch_of_every_slice_width_and_several_tiles(hq, hkv, I, n, m, n
     assert kv.lib().kvc_dev_any_calls() == calls + 1
 
 
-# small calls at block lengths that have tuned kernels too: inside and just beyond the limits of 10 steps of 32 rows and
-# 256 workgroups (the text's among them) that send them to the one-pass kernel
+# small calls at block lengths that have tuned kernels too: inside and just beyond the limits of 10 steps of 32 rows, 256
+# vision workgroups and 512 with the text's that send them to the one-pass kernel
 @pytest.mark.parametrize("hq,hkv,B,I,n,m,t", [(28, 4, 1, 16, 256, 103, 200), (28, 4, 1, 32, 256, 154, 1), (32, 32, 1, 1, 576, 320, 0),
                                               (14, 2, 1, 12, 576, 160, 700), (4, 1, 1, 1, 1024, 320, 5), (2, 2, 8, 7, 256, 31, 9),
                                               (32, 8, 1, 2, 1024, 160, 129), (8, 8, 2, 3, 576, 97, 257)])
@@ -197,7 +197,7 @@ def test_small_calls_of_tuned_block_lengths(hq, hkv, B, I, n, m, t):
     assert kv.lib().kvc_dev_stream_calls() == before and kv.lib().kvc_dev_any_calls() == calls + 1
 
 
-@pytest.mark.parametrize("hq,hkv,B,I,n,m,t", [(32, 32, 1, 1, 576, 321, 0), (14, 2, 16, 1, 256, 103, 768), (28, 4, 1, 50, 256, 154, 1), (28, 4, 1, 2, 256, 103, 8192)])
+@pytest.mark.parametrize("hq,hkv,B,I,n,m,t", [(32, 32, 1, 1, 576, 321, 0), (14, 2, 16, 1, 256, 103, 1800), (28, 4, 1, 50, 256, 154, 1), (28, 4, 1, 2, 256, 103, 8192)])
 def test_calls_just_beyond_the_small_ones_take_the_tuned_kernels(hq, hkv, B, I, n, m, t):
     calls = kv.lib().kvc_dev_any_calls()
     L = layer_of(hq, hkv, B, I, n, m, t, packed=True)
@@ -372,3 +372,28 @@ def test_smallest_accepted_workspace(dtype, d, static):
     e = np.linalg.norm(res[0] - res[1], axis=-1) / np.linalg.norm(res[1], axis=-1)
     print(f"[any] smallest workspace {dtype} d={d} static={static}: {e.max():.3e}", flush=True)
     assert e.max() <= (1e-5 if dtype == "f32" else OUT_ROUNDING * 2)          # two roundings of nearly the same value
+
+
+# Many very short blocks: either side of the rules that leave them to the scalar kernels
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 256)])
+@pytest.mark.parametrize("n,m,I", [(8, 3, 1), (8, 3, 9), (9, 9, 66), (15, 7, 66), (16, 8, 66), (24, 8, 66)])
+def test_compress_many_short_blocks(n, m, I, dtype, d):
+    w = synth.Workload("short", 97, 1, 4, 4, 2, d, dtype, n, I, 0.6, 1, 1)
+    L = Layer(w, m, pre=1, post=1)
+    print(f"[any] compress n={n} m={m} I={I} {dtype} d={d}", flush=True)
+    L.compress()
+    Kc_ref, Vc_ref = orc.compress(f64(L.K), f64(L.V), L.p["key_idx"].numpy(), f64(L.p["U"]), f64(L.p["mu"]), n, I, 1, store_code(w))
+    assert np.array_equal(f64(L.gKc), Kc_ref)
+    assert block_rel_err(unpack_vc(L.gVc, m, d), Vc_ref) <= (1e-5 if dtype == "f32" else ONE_ROUNDING)
+
+
+@pytest.mark.parametrize("m,I", [(8, 32), (8, 33), (9, 33)])
+def test_hidden_rows_of_many_short_blocks(m, I):
+    B, hkv, d = 4, 2, 128
+    g = torch.Generator().manual_seed(m)
+    Kc = torch.randn((B, hkv, I, m, d), generator=g).to(torch.bfloat16)
+    W1 = (torch.randn((hkv, m, m), generator=g) * m ** -0.5).to(torch.bfloat16)
+    H = torch.full_like(Kc, float("nan")).to(DEV)
+    kv.kvc_mlp_hidden(kv.make_shape(B, 4, hkv, d, 64, I, m, torch.bfloat16), W1.to(DEV), kv.KVC_ACT_GELU, Kc.to(DEV), H)
+    torch.cuda.synchronize()
+    assert block_rel_err(f64(H), orc.mlp_hidden(f64(Kc), f64(W1), kv.KVC_ACT_GELU, orc.STORE_BF16)) <= ONE_ROUNDING
