@@ -564,9 +564,13 @@ template <int FORM> static bool launch_compress(const CPlan &p, const CompressCa
     }
 }
 
+// At least a 16-byte piece of a row of U.  Many very short blocks stay on the scalar kernel (us per call, scalar against
+// this: 5120 blocks, n = 8, m = 2 21.4 / 49.5; n = 12, m = 4 42.1 / 51.1; n = 16, m = 5 58.4 / 50.9; 490 blocks, one round of
+// workgroups, n = 8 6.7 / 6.0).
 bool fast_compress_supported(const kvc_shape &s)
 {
-    return s.dtype == KVC_BF16 && s.head_dim == D && s.n_img_tokens >= 8;      // a 16-byte piece of a row of U
+    return s.dtype == KVC_BF16 && s.head_dim == D && s.n_img_tokens >= 8 &&
+           (scalar_chain(s.n_img_tokens, s.m) >= 16 || static_cast<long>(s.batch) * s.n_kv_heads * s.n_images <= 512);
 }
 
 size_t fast_compress_ws_bytes(const kvc_shape &) { return 0; }
@@ -590,7 +594,13 @@ kvc_status fast_compress(const CompressCall &c)
     return ok && hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_HIP;
 }
 
-bool fast_mlp_hidden_supported(const kvc_shape &s) { return s.dtype == KVC_BF16 && s.head_dim == D && s.m >= 8; }
+// (m = 8: 8 blocks 7.5 us on the scalar kernel, 6.3 on this, 490 blocks 8.2 / 9.0, 5120 blocks 23.9 / 55.6; m = 12, 5120
+// blocks 69.9 / 55.5)
+bool fast_mlp_hidden_supported(const kvc_shape &s)
+{
+    return s.dtype == KVC_BF16 && s.head_dim == D && s.m >= 8 &&
+           (scalar_chain(s.m, s.m) >= 16 || static_cast<long>(s.batch) * s.n_kv_heads * s.n_images <= 256);
+}
 
 kvc_status fast_mlp_hidden(const kvc_shape &s, const void *W1, int act, const void *Kc, void *H, hipStream_t stream)
 {

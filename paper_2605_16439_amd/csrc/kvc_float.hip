@@ -31,7 +31,7 @@ namespace {
 
 constexpr int kXW = 8;                // wavefronts
 constexpr int kVisParts = 48, kTextParts = 16;     // part records per (batch element, KV head): a lane each in the merge
-constexpr int kTR = 16 * kXW;         // text rows per step; run r takes the steps r, r + 16, r + 32, ...
+constexpr int kTR = 16 * kXW;         // text rows per step; run r of NTC takes the steps r, r + NTC, r + 2 NTC, ...
 
 // four consecutive elements at any element-aligned address
 template <class T> struct Vec4;
@@ -147,9 +147,9 @@ __global__ __launch_bounds__(64 * kXW, DT == 4 && sizeof(T) == 2 ? 8 : 2) void g
 struct XPlan {
     int B, Hq, Hkv, G, I, n, m, d, KB;                  // KB: 32-row steps of the compressed axis
     int UP, NUT, NUG, F, NP;                            // image blocks per tile, tiles per workgroup, unit groups, slices, position tiles per wavefront
-    int NTX, nparts, rec, nvis;
+    int NTX, NTC, nparts, rec, nvis;
     int t, t_in, cap;
-    unsigned qF, qNUG, qHkv, qNTX, qT;
+    unsigned qF, qNUG, qHkv, qNTX, qT, qNTC;
     float scale;
     float *Ypart;
     const int32_t *n_img, *tlen;
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(64 * kXW) void gx_pass(const T *__restrict__ q, con
         const T *kn = fresh ? k_new + static_cast<size_t>(bh) * d : q, *vn = fresh ? v_new + static_cast<size_t>(bh) * d : q;
         T *Ktb = Kt + static_cast<size_t>(bh) * p.cap * d, *Vtb = Vt + static_cast<size_t>(bh) * p.cap * d;
         const int t_new = fresh ? t_in : -1;
-        for (int x0 = tc * kTR; x0 < t; x0 += kTR * kTextParts) {       // (a run that a shorter sequence does not have: nothing)
+        for (int x0 = tc * kTR; x0 < t; x0 += kTR * p.NTC) {       // (a run that a shorter sequence does not have: nothing)
             const int xr = min(x0 + 16 * wave + r16, t - 1);
             const f32x4 a = score(xr == t_new ? kn : Ktb + static_cast<size_t>(xr) * d);
             f32x4 l;
@@ -286,7 +286,8 @@ __global__ __launch_bounds__(64 * kXW) void gx_pass(const T *__restrict__ q, con
             __syncthreads();                              // the weights have been read
         }
         // Sec. 3.2: the text cache keeps growing as in the backbone -- store the new token's k, v
-        if (fresh && static_cast<unsigned>(t_in) / kTR % kTextParts == static_cast<unsigned>(tc))
+        const int own = t_in / kTR;
+        if (fresh && own - quot(own, p.qNTC) * p.NTC == tc)
             for (int c = threadIdx.x; c < d; c += 64 * kXW) {
                 Ktb[static_cast<size_t>(t_in) * d + c] = kn[c];
                 Vtb[static_cast<size_t>(t_in) * d + c] = vn[c];
@@ -509,8 +510,8 @@ __global__ __launch_bounds__(256) void gx_merge(const float *__restrict__ Ypart,
 
 constexpr size_t kXLds = 156 * 1024;
 
-// What decides the order of the sums does not depend on the rows in the text cache: a ragged batch equals the uniform call
-// bit for bit.
+// What decides the order of the sums follows from the shape and the capacity of the text cache, not from the rows that it
+// holds: a ragged batch equals the uniform call bit for bit.
 bool make_xplan(XPlan &p, const kvc_shape &s, int t, int t_in, int cap)
 {
     p.B = s.batch; p.Hq = s.n_q_heads; p.Hkv = s.n_kv_heads; p.G = p.Hq / p.Hkv;
@@ -536,7 +537,10 @@ bool make_xplan(XPlan &p, const kvc_shape &s, int t, int t_in, int cap)
     p.NUT = p.I > 0 ? (tiles + ug_max - 1) / ug_max : 1;
     p.NUG = p.I > 0 ? (tiles + p.NUT - 1) / p.NUT : 0;
     p.nvis = static_cast<int>(std::min(bh * p.NUG * p.F, 1l << 30));
-    p.NTX = std::min((t + kTR - 1) / kTR, kTextParts);
+    const int full = (cap + kTR - 1) / kTR, each = std::max(1, (full + kTextParts - 1) / kTextParts);
+    p.NTC = std::max(1, (full + each - 1) / each);
+    p.NTX = std::min((t + kTR - 1) / kTR, p.NTC);
+    p.qNTC = quot_multiplier(p.NTC);
     p.nparts = p.NUG * p.F + p.NTX;
     p.rec = static_cast<int>(align_up(p.G * p.d + 2 * p.G, 4));
     p.qF = quot_multiplier(p.F); p.qNUG = quot_multiplier(p.NUG); p.qHkv = quot_multiplier(p.Hkv);
@@ -586,6 +590,18 @@ bool float_compress(const CompressCall &c, kvc_status *st)
 {
     const kvc_shape &s = c.s;
     if (s.n_img_tokens < 4 || s.n_images == 0) return false;
+    // Many very short blocks stay on the scalar kernel: a workgroup here costs the same for them, and the more LDS its sums
+    // take the fewer of them a compute unit holds (4, 2, 1).  us per call, scalar against this, 5120 blocks: d = 64, n = 8, m = 2
+    // 13.8 / 23.0, n = 16, m = 5 27.4 / 22.8; d = 128 39.6 / 41.6 there, n = 24, m = 8 70.7 / 56.5; d = 256, n = 24 102 / 139,
+    // n = 32, m = 10 168 / 166; 576 blocks (2.3 rounds at d = 256) n = 17 16.0 / 18.3, n = 24 24.8 / 18.9; 8 blocks, d = 256,
+    // n = 8 5.6 / 6.0, n = 16 9.1 / 5.8.
+    {
+        const long wgs = static_cast<long>(s.batch) * s.n_kv_heads * s.n_images * ((s.m + 15) / 16);
+        const long round = 256 * (s.head_dim <= 64 ? 4 : s.head_dim <= 128 ? 2 : 1);
+        const int chain = scalar_chain(s.n_img_tokens, s.m);
+        const int least = s.head_dim <= 64 ? 16 : s.head_dim <= 128 ? (wgs > 8 * round ? 20 : 16) : wgs > 8 * round ? 48 : 24;
+        if (chain < (wgs > round ? least : s.head_dim > 128 ? 12 : 0)) return false;
+    }
     XProj p;
     p.Hkv = s.n_kv_heads; p.n = s.n_img_tokens; p.m = s.m; p.I = s.n_images; p.d = s.head_dim; p.vis0 = c.vis_start;
     p.sb = c.stride_b; p.sh = c.stride_h; p.ss = c.stride_s;

@@ -125,6 +125,10 @@ inline bool allow_lds(const void *fn, size_t bytes, bool *done)
     return true;
 }
 
+// Serial multiply-adds of a thread of the scalar projection kernels (8 rows per workgroup) over the workgroups of an image
+// block: what a matrix-core kernel, whose workgroup costs the same however short the block, has to beat once the chip is full.
+inline int scalar_chain(int n, int m) { return n * ((m + 7) / 8); }
+
 // scalar (shape-agnostic) path
 size_t generic_decode_ws_bytes(const kvc_shape &s, int32_t max_text);
 // (what the scalar kernels refuse is refused for every kernel that stands in for them)
