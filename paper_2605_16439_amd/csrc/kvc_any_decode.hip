@@ -24,7 +24,7 @@
 // index: its pieces are turned into operands in registers, 8 rows by 8 positions per lane; U's through LDS.
 //
 // n = 729, m = 292, 3 blocks, B = 1, 28/4 heads, 201 text rows: 205 us per layer on the scalar
-// kernels (six launches; their output step alone 135 us), 16.0 us here -- 13.8 us in this kernel at best, 14.7 on average
+// kernels (six launches; their output step alone 135 us), 16.3 us here -- 13.8 us in this kernel at best, 14.7 on average
 // (kernel trace; keys, theta, softmax, U and values about 3 : 1.5 : 1.5 : 2 : 2), the rest the merge.
 #include "kvc_rows_dev.h"
 
@@ -581,33 +581,34 @@ __global__ __launch_bounds__(64 * kGW) void ga_pass(const uint16_t *__restrict__
         pipe2(NX, fold, load_u, ua0, ua1);
 
         // ---- step 4: Y^T[c][row] = sum_j Vc^T[c][j] W[row][j]: k-steps of all image blocks of the tile in one
-        // row; of a block's product the rows of that block are taken.  (An infinite value makes its own channel of the head
+        // row; the weights of other blocks' rows are selected to zero.  (An infinite value makes its own channel of the head
         // infinite or NaN, as the slices' weights for it have either sign.)
         lds_barrier();
         TS(5, 4);
         Acc3 ao;
-        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+        // (what lies behind the lane's values in the short last block belongs to the next channel)
+        const u32x4 vtail = keep_elems(u32x4_mk(0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu), m - 32 * (KS - 1) - 8 * kg);
         auto out_step = [&](int f, u32x4 v) __attribute__((always_inline)) {
             const int u = quot(f, p.qKS), ks = f - u * KS;
-            // (what lies behind the lane's values in the short last block belongs to the next channel)
-            if (wt && ks == KS - 1) v = keep_elems(shift_window(v, vc_sh >> 2, (vc_sh & 2) * 8u), m - 32 * ks - 8 * kg);
+            if (wt && ks == KS - 1) {
+                v = shift_window(v, vc_sh >> 2, (vc_sh & 2) * 8u);
+                v = u32x4_mk(v.x & vtail.x, v.y & vtail.y, v.z & vtail.z, v.w & vtail.w);
+            }
+            const uint32_t keep = r16 >= u * G && r16 < (u + 1) * G ? 0xffffffffu : 0u;
             bf16x8 wf[3];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) wf[k] = *reinterpret_cast<const bf16x8 *>(sS + k * PLM + r16 * LDM + 32 * ks + 8 * kg);
-            ao.add(as_bf16x8(v), wf);
-            if (ks == KS - 1) {                          // uniform; registers only
-                const f32x4 a = ao.sum();
-                const bool mine = r16 >= u * G && r16 < (u + 1) * G;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = mine ? a[e] : o[e];
-                ao = Acc3();
+            for (int k = 0; k < 3; ++k) {
+                const u32x4 w = *reinterpret_cast<const u32x4 *>(sS + k * PLM + r16 * LDM + 32 * ks + 8 * kg);
+                wf[k] = as_bf16x8(u32x4_mk(w.x & keep, w.y & keep, w.z & keep, w.w & keep));
             }
+            ao.add(as_bf16x8(v), wf);
         };
         pipe2(NV, [&](int r, u32x4 (&b)[4]) __attribute__((always_inline)) {
 #pragma unroll
             for (int c = 0; c < 4; ++c)
                 if (c == 0 || 4 * r + c < NF) out_step(4 * r + c, b[c]);      // uniform; no loads from memory inside
         }, load_v4, va0, va1);
+        const f32x4 o = ao.sum();
         TS(5, 5);
         // rows of the tile that hold no image block keep their state
         if (r16 < nu * G) {
