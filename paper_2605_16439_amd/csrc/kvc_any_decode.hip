@@ -24,7 +24,7 @@
 // index: its pieces are turned into operands in registers, 8 rows by 8 positions per lane; U's through LDS.
 //
 // n = 729, m = 292, 3 blocks, B = 1, 28/4 heads, 201 text rows: 205 us per layer on the scalar
-// kernels (six launches; their output step alone 135 us), 16.3 us here -- 13.8 us in this kernel at best, 14.7 on average
+// kernels (six launches; their output step alone 135 us), 16.3 us here -- 14.0 us in this kernel at best, 14.9 on average
 // (kernel trace; keys, theta, softmax, U and values about 3 : 1.5 : 1.5 : 2 : 2), the rest the merge.
 #include "kvc_rows_dev.h"
 
