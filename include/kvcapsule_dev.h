@@ -91,8 +91,9 @@ int64_t kvc_dev_decode_fallbacks(void);
 
 /* Developer switches of the matrix-core compress kernel (process-wide; negative leaves a setting
  * unchanged).
- *  waves: 4 or 8 wavefronts per workgroup; 0 restores the built-in rule (8 when a workgroup owns more
- *         than 4 tiles of 16 rows of U).
+ *  waves: 4 or 8 wavefronts per workgroup of the kernel that walks a block's positions in steps, 6: that kernel with its own
+ *         rule (8 when a workgroup owns more than 4 tiles of 16 rows of U); 1, 2, 3: the kernel that shares the positions out
+ *         over the wavefronts (8 wavefronts and one tile, 8 and two tiles, 4 and one tile); 0 restores the built-in rule.
  *  jt   : workgroups per image block (clamped to what the kernel supports); 0 restores the cost model. */
 void kvc_dev_compress_knobs(int32_t waves, int32_t jt);
 

@@ -20,6 +20,9 @@
 // the paper's workloads the kernel is bound by what the L2s deliver to the compute units (every
 // workgroup streams its rows of U and its block of V once), not by the matrix cores.
 //
+// Launches that leave compute units idle, or whose blocks have few rows, take fk_split, which shares the positions out over
+// the wavefronts (split_kind() has the rule and both sides' times).
+//
 // The first layer of the two-layer key reconstructor, H = act(W1^T K_tilde) (kvc_mlp_hidden), is the same
 // product with W1 in the place of U and the compressed keys in the place of V, so it runs on the same
 // kernel (FORM 2).
@@ -27,6 +30,8 @@
 // Keys (Sec. 3.1, "Selective Retention and Reconstruction for Keys"): every workgroup copies the
 // key rows that the mask selects for its own rows j, 16 bytes per lane, one pass of rows per step
 // of the projection, so the copy (and its writes) overlap the projection instead of preceding it.
+#include <algorithm>
+
 #include "kvc_decode_dev.h"
 
 namespace kvc {
@@ -486,6 +491,225 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
     TSC(5);
 }
 
+// ---- few workgroups: the contraction shared out over the wavefronts --------------------------------
+// transposed read of 16-bit elements: lane i of 16 passes the address of 4 elements of row i / 4 (columns 4 (i % 4) ...) of a
+// [4][16] tile and gets column i of the four rows
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u32x2 read_tr(const char *lds)
+{
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (__attribute__((address_space(3))) s16x4 *)(lds)));
+}
+
+// fk_compress walks all positions of a block in steps, one barrier each; where the launch leaves compute units idle that chain
+// is its time (n = 729, m = 292, 12 blocks: 60 workgroups, 12 steps, 12.6 us).  Here a workgroup has MT tiles of 16 rows only
+// and its wavefronts take every NW-th step of 32 positions, each with a V tile of its own, two steps requested ahead and no
+// barrier; the wavefronts' sums meet in LDS at the end.  V rows go to LDS as they lie in memory, their 32-byte pieces at
+// piece ^ (row bits 0, 1, 3): the transposed operand reads of 32 lanes then cover every bank once.
+// FORM 1: compress, any n >= 8.  FORM 2: hidden rows (W1 [m][m] is transposed by its operand reads as V is).
+constexpr int kVT = 32 * D * 2;            // a wavefront's V tile
+constexpr int kWT = 32 * 16 * 2;           // its tile of W1 (FORM 2), per 16 rows
+constexpr size_t split_lds(int NW, int MT, int FORM)
+{
+    return static_cast<size_t>(NW) * (std::max(kVT + (FORM == 2 ? MT * kWT : 0), MT * 16 * D * 4) + MT * 16 * 4);
+}
+
+template <int NW, int MT, int FORM>
+__global__ __launch_bounds__(64 * NW) void fk_split(CPlan p, const uint16_t *__restrict__ K,
+                                                                         const uint16_t *__restrict__ V,
+                                                                         const int32_t *__restrict__ idx,
+                                                                         const uint16_t *__restrict__ U,
+                                                                         const uint16_t *__restrict__ mu,
+                                                                         uint16_t *__restrict__ Kc, uint16_t *__restrict__ Vc)
+{
+    constexpr int WB = static_cast<int>(split_lds(NW, MT, FORM) / NW) - MT * 64;     // a wavefront's LDS: its tiles, then its sums
+    extern __shared__ __align__(16) char sdyn[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int r16 = lane & 15, kg = lane >> 4;
+    char *const sV = sdyn + wave * WB, *const sW = sV + kVT;
+    float *const sA = reinterpret_cast<float *>(sdyn + NW * WB);             // row sums of U [NW][16 MT]
+
+    // an XCD takes a contiguous run of workgroups in (head, batch element, image block) order, as in fk_compress
+    const int bx = blockIdx.x;
+    const int wg = p.per_xcd ? (bx & 7) * p.per_xcd + (bx >> 3) : bx;
+    const int lu = wg / p.JT, jt = wg - lu * p.JT;
+    const int hb = lu / p.I, i = lu - hb * p.I;
+    const int h = hb / p.B, b = hb - h * p.B;
+    const int u = (b * p.Hkv + h) * p.I + i;
+    const int j0 = 16 * MT * jt, n = p.n, m = p.m;
+    const int NKS = (n + 31) / 32, N = NKS > wave ? (NKS - wave + NW - 1) / NW : 0;
+    const int64_t blk = FORM == 2 ? static_cast<int64_t>(u) * n * D
+                                  : b * p.sb + h * p.sh + (static_cast<int64_t>(p.vis0) + static_cast<int64_t>(i) * n) * p.ss;
+    const uint16_t *vsrc = V + blk + 8 * r16;
+
+    // the workgroup's key rows (step a1): index, row, store, each behind requests that are in flight anyway
+    constexpr int KP = (16 * MT * 16 + 64 * NW - 1) / (64 * NW);            // rows of 16 lanes per thread
+    int krow[KP];
+    u32x4 kv[KP];
+    if constexpr (FORM != 2) {
+#pragma unroll
+        for (int k = 0; k < KP; ++k) krow[k] = idx[min(j0 + (static_cast<int>(threadIdx.x) >> 4) + 4 * NW * k, m - 1)];
+    }
+    auto load = [&](int r, u32x4 (&v)[8], u32x4 (&ub)[MT]) __attribute__((always_inline)) {
+        const int pos = 32 * (wave + NW * r);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            v[e] = *reinterpret_cast<const u32x4 *>(vsrc + static_cast<int64_t>(min(pos + 4 * e + kg, n - 1)) * p.ss);
+#pragma unroll
+        for (int q = 0; q < MT; ++q)
+            if constexpr (FORM == 2)
+                ub[q] = *reinterpret_cast<const u32x4_a2 *>(U + (static_cast<size_t>(h) * n + min(pos + (lane >> 1), n - 1)) * m +
+                                                            min(j0 + 16 * q + 8 * (lane & 1), m - 8));
+            else
+                ub[q] = *reinterpret_cast<const u32x4_a2 *>(U + (static_cast<size_t>(h) * m + min(j0 + 16 * q + r16, m - 1)) * n +
+                                                            min(pos + 8 * kg, n - 8));
+    };
+    f32x4 acc[MT][8], accs[MT];
+#pragma unroll
+    for (int q = 0; q < MT; ++q) {
+        accs[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int nt = 0; nt < 8; ++nt) acc[q][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const uint32_t one2 = 0x3f803f80u;
+    const bf16x8 ones = as_bf16x8(make_uint4(one2, one2, one2, one2));
+    // stores: row 4 e + kg, 16-byte piece r16; reads: rows 8 kg + r16 / 4 and four further down, channels 16 nt + 4 (r16 % 4)
+    const int vst = kg * 256 + r16 * 16;                                    // (bits 5..7: the 32-byte piece)
+    const int vrd = (8 * kg + (r16 >> 2)) * 256 + (((r16 >> 2) | ((kg & 1) << 2)) << 5) + (r16 & 3) * 8;
+    const int wrd = (8 * kg + (r16 >> 2)) * 32 + (r16 & 3) * 8;
+    auto step = [&](int r, u32x4 (&v)[8], u32x4 (&ub)[MT]) __attribute__((always_inline)) {
+        const int pos = 32 * (wave + NW * r);
+        if (pos + 32 > n) {                              // uniform, registers only: positions past the end are zeros
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t keep = pos + 4 * e + kg < n ? 0xffffffffu : 0u;
+                v[e] = u32x4{v[e].x & keep, v[e].y & keep, v[e].z & keep, v[e].w & keep};
+            }
+            if constexpr (FORM != 2) {
+#pragma unroll
+                for (int q = 0; q < MT; ++q) ub[q] = drop_elems(ub[q], min(max(pos + 8 * kg - (n - 8), 0), 8));
+            } else {
+                const uint32_t keep = pos + (lane >> 1) < n ? 0xffffffffu : 0u;
+#pragma unroll
+                for (int q = 0; q < MT; ++q) ub[q] = u32x4{ub[q].x & keep, ub[q].y & keep, ub[q].z & keep, ub[q].w & keep};
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int e = 0; e < 8; ++e)                      // row bits 0, 1: kg; bit 3: e bit 1
+            *reinterpret_cast<u32x4 *>(sV + 1024 * e + (vst ^ ((kg | ((e & 2) << 1)) << 5))) = v[e];
+        bf16x8 ua[MT];
+        if constexpr (FORM == 2) {
+#pragma unroll
+            for (int q = 0; q < MT; ++q) *reinterpret_cast<u32x4 *>(sW + q * kWT + lane * 16) = drop_elems(ub[q], min(max(j0 + 16 * q + 8 * (lane & 1) - (m - 8), 0), 8));
+        }
+        __builtin_amdgcn_wave_barrier();                 // (a wavefront's LDS requests are worked off in order)
+#pragma unroll
+        for (int q = 0; q < MT; ++q) {
+            if constexpr (FORM == 2) {
+                const u32x2 a = read_tr(sW + q * kWT + wrd), c = read_tr(sW + q * kWT + wrd + 4 * 32);
+                ua[q] = __builtin_bit_cast(bf16x8, u32x4{a.x, a.y, c.x, c.y});
+            } else {
+                ua[q] = __builtin_bit_cast(bf16x8, ub[q]);
+            }
+        }
+#pragma unroll
+        for (int nt = 0; nt < 8; ++nt) {
+            const u32x2 a = read_tr(sV + (vrd ^ (nt << 5))), c = read_tr(sV + (vrd ^ (nt << 5)) + 4 * 256);
+            const bf16x8 vb = __builtin_bit_cast(bf16x8, u32x4{a.x, a.y, c.x, c.y});
+#pragma unroll
+            for (int q = 0; q < MT; ++q)
+                acc[q][nt] = FORM == 2 ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb, ua[q], acc[q][nt], 0, 0, 0)
+                                       : __builtin_amdgcn_mfma_f32_16x16x32_bf16(ua[q], vb, acc[q][nt], 0, 0, 0);
+        }
+        if constexpr (FORM != 2) {
+#pragma unroll
+            for (int q = 0; q < MT; ++q) accs[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ua[q], ones, accs[q], 0, 0, 0);
+        }
+    };
+
+    u32x4 v0[8] = {}, u0[MT] = {}, v1[8] = {}, u1[MT] = {};
+    if (N > 0) load(0, v0, u0);
+    if (N > 1) load(1, v1, u1);
+    if constexpr (FORM != 2) {
+#pragma unroll
+        for (int k = 0; k < KP; ++k)                     // an index outside the block must not leave it
+            kv[k] = *reinterpret_cast<const u32x4 *>(K + blk + static_cast<int64_t>(min(max(krow[k], 0), n - 1)) * p.ss + 8 * r16);
+    }
+    int r = 0;
+    for (; r + 2 < N; r += 2) {
+        step(r, v0, u0);
+        load(r + 2, v0, u0);
+        step(r + 1, v1, u1);
+        if (r + 3 < N) load(r + 3, v1, u1);
+    }
+    if (r < N) step(r, v0, u0);
+    if (r + 1 < N) step(r + 1, v1, u1);
+    if constexpr (FORM != 2) {
+#pragma unroll
+        for (int k = 0; k < KP; ++k) {
+            const int rl = (static_cast<int>(threadIdx.x) >> 4) + 4 * NW * k;
+            if (rl < 16 * MT && j0 + rl < m)
+                *reinterpret_cast<u32x4 *>(Kc + (static_cast<size_t>(u) * m + j0 + rl) * D + 8 * r16) = kv[k];
+        }
+    }
+
+    // ---- the wavefronts' sums: [wavefront][MT * 8 tiles][lane], then a tile's lane over all wavefronts
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < MT; ++q) {
+#pragma unroll
+        for (int nt = 0; nt < 8; ++nt) *reinterpret_cast<f32x4 *>(sV + ((q * 8 + nt) * 64 + lane) * 16) = acc[q][nt];
+        if (FORM != 2 && r16 == 0) *reinterpret_cast<f32x4 *>(sA + (wave * MT + q) * 16 + 4 * kg) = accs[q];
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+    for (int x = 0; x < MT * 8 / NW; ++x) {
+        const int item = wave + NW * x, q = item >> 3, nt = item & 7;
+        f32x4 s = {0.f, 0.f, 0.f, 0.f}, us = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            s += *reinterpret_cast<const f32x4 *>(sdyn + w * WB + (item * 64 + lane) * 16);
+            if constexpr (FORM != 2) us += *reinterpret_cast<const f32x4 *>(sA + (w * MT + q) * 16 + 4 * kg);
+        }
+        uint32_t o[4];
+        if constexpr (FORM == 2) {
+            // row j0 + 16 q + r16, channels 16 nt + 4 kg ... + 3
+            const int row = j0 + 16 * q + r16;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = f32_to_bf16_bits(activate(s[e], p.act));
+            if (row < m)
+                *reinterpret_cast<u32x2 *>(Kc + (static_cast<size_t>(u) * m + row) * D + 16 * nt + 4 * kg) = u32x2{o[0] | (o[1] << 16), o[2] | (o[3] << 16)};
+        } else {
+            // rows j0 + 16 q + 4 kg ... + 3 of channel 16 nt + r16: centred, rounded once, in the blocked layout
+            const int c = 16 * nt + r16, jr = j0 + 16 * q + 4 * kg, jb = jr >> 3, w8 = min(8, m - 8 * jb);
+            const float muc = __uint_as_float(static_cast<uint32_t>(mu[static_cast<size_t>(h) * D + c]) << 16);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = f32_to_bf16_bits(s[e] - us[e] * muc);
+            uint16_t *vout = Vc + static_cast<size_t>(u) * m * D + static_cast<size_t>(jb) * 8 * D;
+            if (w8 == 8) {
+                *reinterpret_cast<u32x2 *>(vout + c * 8 + (jr & 7)) = u32x2{o[0] | (o[1] << 16), o[2] | (o[3] << 16)};
+            } else if (w8 > 0) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if ((jr & 7) + e < w8) vout[c * w8 + (jr & 7) + e] = static_cast<uint16_t>(o[e]);
+            }
+        }
+    }
+}
+
+template <int NW, int MT, int FORM>
+bool launch_split(const CPlan &p, const uint16_t *K, const uint16_t *V, const int32_t *idx, const uint16_t *U, const uint16_t *mu,
+                  uint16_t *Kc, uint16_t *Vc, hipStream_t stream)
+{
+    static_assert(MT * 8 % NW == 0, "the tiles divide evenly over the wavefronts");
+    constexpr size_t lds = split_lds(NW, MT, FORM);
+    static bool attr_set[kMaxDevices] = {};
+    if (!allow_lds(reinterpret_cast<const void *>(fk_split<NW, MT, FORM>), lds, attr_set)) return false;
+    fk_split<NW, MT, FORM><<<p.nproj, 64 * NW, lds, stream>>>(p, K, V, idx, U, mu, Kc, Vc);
+    return true;
+}
+
 template <int NW, int MT, int FORM>
 bool launch(const CPlan &p, const uint16_t *K, const uint16_t *V, const int32_t *idx, const uint16_t *U, const uint16_t *mu,
             uint16_t *Kc, uint16_t *Vc, hipStream_t stream)
@@ -547,6 +771,45 @@ static void share_tiles(CPlan &p)
     p.per_xcd = p.nproj % 8 == 0 ? p.nproj / 8 : 0;
 }
 
+// Which kernel, for a contraction over k (n, or m for the hidden rows); p shared out by share_tiles().  0: fk_compress; fk_split
+// with 1: 8 wavefronts, one tile; 2: 8 wavefronts, two tiles; 3: 4 wavefronts, one tile (three workgroups per compute unit).
+// Measured on 110 random shapes (us per call, fk_compress / 1 / 2 / 3):
+//   a compute unit for every tile: 1.  12 blocks, n = 729, m = 292 13.1 / 7.9 / 8.9 / 8.2; 2 blocks, n = 148, m = 45 6.5 / 3.9 /
+//     4.7 / 4.0; hidden, m = 122, 28 blocks 7.5 / 3.9 / 4.7 / 4.1;
+//   for every two tiles, and steps enough to pay for the longer sum: 2.  16 blocks, n = 726, m = 499 13.1 / 11.9 / 8.5 / 9.6; but
+//     64 blocks, n = 70, m = 18 6.3 / 5.7 / 4.6 / 4.3;
+//   else a tile at a time where the rounds of fk_compress, whose workgroups pass over all positions in a row, take longer than
+//     the tiles that each read V: 3 or 0, by the times that fit the measurements (0.1 us; within 15 and 9 %) with a margin.
+//     384 blocks, n = 488, m = 73 24.1 / 22.5 (3); 160 blocks, n = 333, m = 139 17.3 / 15.0 (3); 88 blocks, n = 451, m = 207 13.7 (0) /
+//     16.3; 128 blocks, n = 1024, m = 410 28.5 (0) / 52.8.
+static int split_kind(const CPlan &p)
+{
+    if (g_force_nw >= 1 && g_force_nw <= 3) return g_force_nw;
+    if (g_force_nw > 3 || g_force_jt > 0) return 0;
+    const long units = static_cast<long>(p.B) * p.Hkv * p.I;
+    const int steps = (p.n + 31) / 32;
+    if (units * p.tiles <= 256) return 1;
+    if (units * ((p.tiles + 1) / 2) <= 256 && steps >= 7) return 2;
+    const double x = units * p.tiles / 256.0, wgs = p.nproj / 256.0;
+    const int resident = p.TPW > 8 ? 1 : 2, rounds = static_cast<int>((p.nproj + 256 * resident - 1) / (256 * resident));
+    const double split = 24 + (4 + 7 * ((steps + 3) / 4)) * std::max(1.0, 0.64 * x) + 5 * x;
+    const double whole = 20 + rounds * (19 + 6 * ((p.n + kKT - 1) / kKT) + 8 * p.TPW) * (1 + 0.8 * std::max(wgs / rounds - 1, 0.0));
+    return split <= 0.75 * whole ? 3 : 0;
+}
+
+template <int FORM> static bool split_compress(CPlan p, int kind, const uint16_t *K, const uint16_t *V, const int32_t *idx, const uint16_t *U,
+                                               const uint16_t *mu, uint16_t *Kc, uint16_t *Vc, hipStream_t stream)
+{
+    p.JT = kind == 2 ? (p.tiles + 1) / 2 : p.tiles;
+    p.nproj = p.B * p.Hkv * p.I * p.JT;
+    p.per_xcd = p.nproj % 8 == 0 ? p.nproj / 8 : 0;
+    switch (kind) {
+    case 1: return launch_split<8, 1, FORM>(p, K, V, idx, U, mu, Kc, Vc, stream);
+    case 2: return launch_split<8, 2, FORM>(p, K, V, idx, U, mu, Kc, Vc, stream);
+    default: return launch_split<4, 1, FORM>(p, K, V, idx, U, mu, Kc, Vc, stream);
+    }
+}
+
 template <int FORM> static bool launch_compress(const CPlan &p, const CompressCall &c)
 {
     const uint16_t *K = static_cast<const uint16_t *>(c.K), *V = static_cast<const uint16_t *>(c.V);
@@ -590,7 +853,11 @@ kvc_status fast_compress(const CompressCall &c)
                ? reinterpret_cast<unsigned long long *>((reinterpret_cast<uintptr_t>(c.ws) + c.ws_bytes - (1u << 20)) & ~uintptr_t(7))
                : nullptr;
 #endif
-    const bool ok = p.n % kKT == 0 ? launch_compress<0>(p, c) : launch_compress<1>(p, c);
+    const int kind = split_kind(p);
+    const bool ok = kind ? split_compress<1>(p, kind, static_cast<const uint16_t *>(c.K), static_cast<const uint16_t *>(c.V), c.key_idx,
+                                             static_cast<const uint16_t *>(c.U), static_cast<const uint16_t *>(c.mu),
+                                             static_cast<uint16_t *>(c.Kc), static_cast<uint16_t *>(c.Vc), c.stream)
+                    : p.n % kKT == 0 ? launch_compress<0>(p, c) : launch_compress<1>(p, c);
     return ok && hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_HIP;
 }
 
@@ -615,8 +882,10 @@ kvc_status fast_mlp_hidden(const kvc_shape &s, const void *W1, int act, const vo
 #endif
     const uint16_t *k = static_cast<const uint16_t *>(Kc), *w = static_cast<const uint16_t *>(W1);
     uint16_t *out = static_cast<uint16_t *>(H);
-    const bool ok = p.TPW > 8 ? launch<8, 2, 2>(p, nullptr, k, nullptr, w, nullptr, out, nullptr, stream)
-                              : launch<8, 1, 2>(p, nullptr, k, nullptr, w, nullptr, out, nullptr, stream);
+    const int kind = split_kind(p);
+    const bool ok = kind ? split_compress<2>(p, kind, nullptr, k, nullptr, w, nullptr, out, nullptr, stream)
+                    : p.TPW > 8 ? launch<8, 2, 2>(p, nullptr, k, nullptr, w, nullptr, out, nullptr, stream)
+                                : launch<8, 1, 2>(p, nullptr, k, nullptr, w, nullptr, out, nullptr, stream);
     return ok && hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_HIP;
 }
 

@@ -89,3 +89,31 @@ def test_headline_shape_both_forms(knobs):
         e = block_rel_err(unpack_vc(L.gVc, 410, w.head_dim)[sel], Vc_ref)
         print(f"[compress] qwen2vl waves={waves}: block rel err {e:.3e}", flush=True)
         assert e <= tol(w)
+
+
+@pytest.mark.parametrize("kind", [1, 2, 3])
+@pytest.mark.parametrize("n,m", [(8, 8), (9, 1), (31, 7), (32, 16), (33, 17), (64, 33), (127, 15), (255, 130), (257, 9), (288, 65),
+                                 (289, 32), (520, 50), (1025, 24)])
+def test_positions_shared_out_over_the_wavefronts(n, m, kind, knobs):
+    """The kernel for few workgroups, each of its forms: wavefronts without a step, with one, two, three and more, a last step of
+    1 to 32 positions, rows of U at odd addresses, compressed lengths around the 16-row tile, the pair of tiles and the 8-row
+    block; three blocks, so that reads past a block would find another's values."""
+    run_case(wl(n, 3), m, kind, 0, knobs, pre=3, post=2)
+
+
+@pytest.mark.parametrize("kind", [1, 2, 3, 8])
+@pytest.mark.parametrize("m", [8, 9, 31, 33, 64, 127, 257, 290])
+def test_hidden_rows_in_every_form(m, kind, knobs):
+    """The same kernels as the first layer of the two-layer reconstructor (rows of W1 at odd addresses where m is odd)."""
+    knobs(kind, 0)
+    w = wl(max(m, 64), 3, B=2)
+    g = torch.Generator().manual_seed(m)
+    W1 = (torch.randn(2, m, m, generator=g) * m ** -0.5).to(torch.bfloat16)
+    Kc = torch.randn(2, 2, 3, m, 128, generator=g).to(torch.bfloat16)
+    shape = kv.make_shape(2, 4, 2, 128, w.n_img_tokens, 3, m, torch.bfloat16)
+    H = torch.full(Kc.shape, float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    kv.kvc_mlp_hidden(shape, W1.to("cuda:0"), kv.KVC_ACT_GELU, Kc.to("cuda:0"), H)
+    ref = orc.mlp_hidden(f64(Kc), f64(W1), kv.KVC_ACT_GELU, store_code(w))
+    e = block_rel_err(f64(H), ref)
+    print(f"[hidden] m={m} form {kind}: block rel err {e:.3e}", flush=True)
+    assert e <= 2e-3        # the same sums in another order, rounded to bf16 once: few results round the other way
