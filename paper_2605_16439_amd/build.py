@@ -1,13 +1,15 @@
-"""Builds libkvcapsule.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Builds libkvcapsule.so (HIP, gfx950 only) in-tree with hipcc, and the binding's argument marshalling with gcc."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkvcapsule.so")
+CALL = os.path.join(HERE, "_kvc_call.so")      # extension module of the Python binding, host code only
 SOURCES = ["kvc_api.hip", "kvc_generic.hip", "kvc_fast_decode.hip", "kvc_fast_compress.hip",
            "kvc_full_decode.hip", "kvc_stream_decode.hip", "kvc_static_decode.hip",
            "kvc_any_decode.hip", "kvc_float.hip"]
@@ -21,9 +23,9 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
 
 
 def _stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(CALL):
         return True
-    t = os.path.getmtime(LIB)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(CALL))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)]
     inc = os.path.join(HERE, "..", "include")
     deps += [os.path.join(inc, f) for f in os.listdir(inc)]
@@ -55,6 +57,11 @@ def build(force: bool = True, verbose: bool = False) -> str:
             print("\n".join(lines))
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-Wall", "-Wextra", "-shared", "-fPIC",
+           "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "kvc_call.c"), "-o", CALL]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    if r.returncode != 0:
+        raise RuntimeError("gcc failed on kvc_call.c:\n" + r.stdout.decode())
     return LIB
 
 

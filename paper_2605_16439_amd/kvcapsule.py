@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libkvcapsule.so (C ABI in include/kvcapsule.h).
+"""Thin binding of libkvcapsule.so (C ABI in include/kvcapsule.h): ctypes, and for the
+calls that a program makes per layer the extension module _kvc_call (csrc/kvc_call.c).
 
 Argument marshalling only: every step of the hot path runs in the HIP kernels of
 the library.  PyTorch is used for device memory and the current stream.  There is
@@ -63,6 +64,22 @@ class KvcError(RuntimeError):
 
 
 _lib = None
+_native = None                 # _kvc_call, bound to the library's functions
+_BOUND = ("kvc_compress", "kvc_compress_generic", "kvc_reconstruct_attend_decode", "kvc_reconstruct_attend_decode_generic",
+          "kvc_reconstruct_attend_decode_static", "kvc_reconstruct_attend_decode_ragged", "kvc_mlp_hidden",
+          "kvc_static_attend_decode", "kvc_attend_full_decode")
+
+
+def _call():
+    """The marshalling module, bound to the library's functions at first use."""
+    global _native
+    if _native is None:
+        L = lib()
+        from . import _kvc_call
+
+        _kvc_call.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _BOUND))
+        _native = _kvc_call
+    return _native
 
 
 def lib() -> ctypes.CDLL:
@@ -202,6 +219,18 @@ def _stream(stream) -> ctypes.c_void_p:
     return ctypes.c_void_p(stream.cuda_stream)
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream_int(stream) -> int:
+    """The stream's handle.  The current stream's without a stream object: that alone takes 2.8 us per call."""
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
+
+
 def make_params(key_idx, theta, U, mu, theta_packed=None, U_packed=None) -> KvcParams:
     return KvcParams(_ptr(key_idx), _ptr(theta), _ptr(U), _ptr(mu), _ptr(theta_packed), _ptr(U_packed))
 
@@ -241,11 +270,7 @@ def kvc_compress(shape: KvcShape, params: KvcParams, K: torch.Tensor, V: torch.T
                  vis_start: int, Kc: torch.Tensor, Vc: torch.Tensor, workspace: torch.Tensor,
                  stream=None, generic: bool = False, check: bool = True) -> int:
     """K, V: [B, H_kv, S, d] (d contiguous); Kc, Vc: [B, H_kv, I, m, d] outputs."""
-    assert K.stride() == V.stride() and K.stride(3) == 1
-    wp, wb = _ws(workspace)
-    fn = lib().kvc_compress_generic if generic else lib().kvc_compress
-    st = fn(ctypes.byref(shape), ctypes.byref(params), _ptr(K), _ptr(V), K.stride(0), K.stride(1),
-            K.stride(2), int(vis_start), K.shape[2], _ptr(Kc), _ptr(Vc), wp, wb, _stream(stream))
+    st = (_native or _call()).compress(shape, params, K, V, vis_start, Kc, Vc, workspace, _stream_int(stream), generic)
     if check and st != KVC_OK:
         raise KvcError(st, "kvc_compress")
     return st
@@ -256,12 +281,8 @@ def kvc_reconstruct_attend_decode(shape: KvcShape, params: KvcParams, q, Kc, Vc,
                                   out, lse_out, workspace, stream=None, generic: bool = False,
                                   check: bool = True) -> int:
     """q, out: [B, H_q, d]; Kc, Vc: capsule; K_text, V_text: [B, H_kv, text_cap, d]."""
-    wp, wb = _ws(workspace)
-    fn = lib().kvc_reconstruct_attend_decode_generic if generic else \
-        lib().kvc_reconstruct_attend_decode
-    st = fn(ctypes.byref(shape), ctypes.byref(params), _ptr(q), _ptr(Kc), _ptr(Vc), _ptr(K_text),
-            _ptr(V_text), int(text_len), int(text_cap), _ptr(k_new), _ptr(v_new),
-            ctypes.c_float(softmax_scale), _ptr(out), _ptr(lse_out), wp, wb, _stream(stream))
+    st = (_native or _call()).decode(shape, params, q, Kc, Vc, K_text, V_text, text_len, text_cap, k_new, v_new,
+                                     softmax_scale, out, lse_out, workspace, _stream_int(stream), generic)
     if check and st != KVC_OK:
         raise KvcError(st, "kvc_reconstruct_attend_decode")
     return st
@@ -276,13 +297,12 @@ def kvc_attend_full_workspace_bytes(batch, n_q_heads, n_kv_heads, head_dim, dtyp
 def kvc_attend_full_decode(q, K, V, kv_len: int, k_new, v_new, softmax_scale: float, out, lse_out,
                            workspace, stream=None, check: bool = True) -> int:
     """Full-cache decode attention.  q, out: [B, H_q, d]; K, V: [B, H_kv, kv_cap, d] (d contiguous)."""
-    assert K.stride() == V.stride() and K.stride(3) == 1
+    strides = K.stride()
+    assert strides == V.stride() and strides[3] == 1
     B, Hq, d = q.shape
-    wp, wb = _ws(workspace)
-    st = lib().kvc_attend_full_decode(B, Hq, K.shape[1], d, _dtype_code(q.dtype), _ptr(q), _ptr(K), _ptr(V),
-                                      K.stride(0), K.stride(1), K.stride(2), int(kv_len), K.shape[2],
-                                      _ptr(k_new), _ptr(v_new), ctypes.c_float(softmax_scale), _ptr(out),
-                                      _ptr(lse_out), wp, wb, _stream(stream))
+    _, Hkv, cap, _ = K.shape
+    st = (_native or _call()).full(B, Hq, Hkv, d, _dtype_code(q.dtype), q, K, V, strides[0], strides[1], strides[2], kv_len,
+                                   cap, k_new, v_new, softmax_scale, out, lse_out, workspace, _stream_int(stream))
     if check and st != KVC_OK:
         raise KvcError(st, "kvc_attend_full_decode")
     return st
@@ -292,10 +312,8 @@ def kvc_reconstruct_attend_decode_static(shape: KvcShape, params: KvcParams, q, 
                                          text_len: int, text_cap: int, k_new, v_new, softmax_scale: float,
                                          out, lse_out, stream=None, check: bool = True) -> int:
     """kvc_reconstruct_attend_decode with the library's own scratch array instead of a workspace."""
-    st = lib().kvc_reconstruct_attend_decode_static(
-        ctypes.byref(shape), ctypes.byref(params), _ptr(q), _ptr(Kc), _ptr(Vc), _ptr(K_text), _ptr(V_text),
-        int(text_len), int(text_cap), _ptr(k_new), _ptr(v_new), ctypes.c_float(softmax_scale), _ptr(out),
-        _ptr(lse_out), _stream(stream))
+    st = (_native or _call()).decode_static(shape, params, q, Kc, Vc, K_text, V_text, text_len, text_cap, k_new, v_new,
+                                            softmax_scale, out, lse_out, _stream_int(stream))
     if check and st != KVC_OK:
         raise KvcError(st, "kvc_reconstruct_attend_decode_static")
     return st
@@ -320,11 +338,8 @@ def kvc_reconstruct_attend_decode_ragged(shape: KvcShape, params: KvcParams, q, 
                                          check: bool = True) -> int:
     """n_images, text_len: int32 device tensors [B]."""
     assert n_images.dtype == torch.int32 and text_len.dtype == torch.int32
-    wp, wb = _ws(workspace)
-    st = lib().kvc_reconstruct_attend_decode_ragged(
-        ctypes.byref(shape), ctypes.byref(params), _ptr(q), _ptr(Kc), _ptr(Vc), _ptr(K_text), _ptr(V_text),
-        _ptr(n_images), _ptr(text_len), int(text_cap), _ptr(k_new), _ptr(v_new), ctypes.c_float(softmax_scale),
-        _ptr(out), _ptr(lse_out), wp, wb, _stream(stream))
+    st = (_native or _call()).ragged(shape, params, q, Kc, Vc, K_text, V_text, n_images, text_len, text_cap, k_new, v_new,
+                                     softmax_scale, out, lse_out, workspace, _stream_int(stream))
     if check and st != KVC_OK:
         raise KvcError(st, "kvc_reconstruct_attend_decode_ragged")
     return st
@@ -332,7 +347,7 @@ def kvc_reconstruct_attend_decode_ragged(shape: KvcShape, params: KvcParams, q, 
 
 def kvc_mlp_hidden(shape: KvcShape, W1: torch.Tensor, activation: int, Kc: torch.Tensor, H: torch.Tensor,
                    stream=None, check: bool = True) -> int:
-    st = lib().kvc_mlp_hidden(ctypes.byref(shape), _ptr(W1), int(activation), _ptr(Kc), _ptr(H), _stream(stream))
+    st = (_native or _call()).hidden(shape, W1, activation, Kc, H, _stream_int(stream))
     if check and st != KVC_OK:
         raise KvcError(st, "kvc_mlp_hidden")
     return st
@@ -340,10 +355,8 @@ def kvc_mlp_hidden(shape: KvcShape, W1: torch.Tensor, activation: int, Kc: torch
 
 def kvc_static_attend_decode(shape: KvcShape, q, Kc, Vc, K_text, V_text, text_len: int, text_cap: int, k_new, v_new,
                              softmax_scale: float, out, lse_out, workspace, stream=None, check: bool = True) -> int:
-    wp, wb = _ws(workspace)
-    st = lib().kvc_static_attend_decode(ctypes.byref(shape), _ptr(q), _ptr(Kc), _ptr(Vc), _ptr(K_text), _ptr(V_text),
-                                        int(text_len), int(text_cap), _ptr(k_new), _ptr(v_new),
-                                        ctypes.c_float(softmax_scale), _ptr(out), _ptr(lse_out), wp, wb, _stream(stream))
+    st = (_native or _call()).static_decode(shape, q, Kc, Vc, K_text, V_text, text_len, text_cap, k_new, v_new, softmax_scale,
+                                            out, lse_out, workspace, _stream_int(stream))
     if check and st != KVC_OK:
         raise KvcError(st, "kvc_static_attend_decode")
     return st
