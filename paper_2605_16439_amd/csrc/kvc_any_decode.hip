@@ -144,7 +144,7 @@ size_t pass_lds(int m, int PS, bool packed)
 {
     const size_t s = 3 * 16 * (align_up(m, 32) + 16) * 2;
     const size_t vis = std::max(s + planes_p(PS) + kStage, packed ? size_t(0) : kPartial) + 2 * 16 * kGW * sizeof(float);
-    const size_t txt = kSW * (D * kLDX + 2 * 16) * sizeof(uint32_t);
+    const size_t txt = kSW * (kWalkLds + 2 * 16 * sizeof(float));
     return std::max(vis, txt);
 }
 
@@ -171,8 +171,8 @@ __global__ __launch_bounds__(64 * kGW) void ga_pass(const uint16_t *__restrict__
         const int id = blockIdx.x - p.nvis;
         const int bh = quot(id, p.qNTX), tc = id - bh * p.NTX;
         const int b = quot(bh, p.qHkv), h = bh - b * p.Hkv;
-        uint32_t (*sVt)[D * kLDX] = reinterpret_cast<uint32_t (*)[D * kLDX]>(dyn);
-        float (*sM)[16] = reinterpret_cast<float (*)[16]>(sVt + kSW), (*sL)[16] = sM + kSW;
+        char *const sVt = reinterpret_cast<char *>(dyn);
+        float (*sM)[16] = reinterpret_cast<float (*)[16]>(sVt + kSW * kWalkLds), (*sL)[16] = sM + kSW;
         const bool fresh = k_new != nullptr;
         int t_in = p.t_in, t = p.t;
         if constexpr (RAG) {
@@ -194,10 +194,10 @@ __global__ __launch_bounds__(64 * kGW) void ga_pass(const uint16_t *__restrict__
 #pragma unroll
             for (int k = 0; k < 4; ++k) qf[k] = qp[4 * k];
             Rows rw;
-            rw.I = 0; rw.m = 8; rw.KS = 1; rw.SV = 0; rw.qKS = 0; rw.t = t; rw.cs = 1 << 30; rw.st = kSW * p.NTC; rw.qst = p.qst; rw.scale = p.scale;
-            walk<true>(rw, Ktb, Vtb, kn, vn, fresh ? t_in : -1, qf, s0, sVt[wave], m_run, l_run, acc);
+            rw.I = 0; rw.m = 8; rw.KS = 1; rw.SV = 0; rw.qKS = 0; rw.t = t; rw.cs = 1 << 30; rw.ws = 1; rw.st = kSW * p.NTC; rw.qst = p.qst; rw.scale = p.scale;
+            walk<true>(rw, Ktb, Vtb, kn, vn, fresh ? t_in : -1, qf, s0, sVt + wave * kWalkLds, m_run, l_run, acc);
         }
-        merge_waves(sVt, sM, sL, m_run, l_run, acc, G,
+        merge_waves<kSW>(sVt, sM, sL, m_run, l_run, acc, G,
                     p.Ypart + (static_cast<size_t>(bh) * p.nparts + p.NUG * p.F + tc) * p.rec);
         // Sec. 3.2: the text cache keeps growing as in the backbone -- store the new token's k, v
         const int own = t_in / kTextStep;

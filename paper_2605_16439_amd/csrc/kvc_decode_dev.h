@@ -137,6 +137,14 @@ __device__ inline float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff000
 // spread over the banks and the operand reads of one tile stay conflict-free
 __device__ inline int vt_index(int c, int x) { return c * kLDV + ((((x >> 3) ^ (c >> 4)) & (kXC / 8 - 1)) << 3) + (x & 7); }
 
+// transposed read of 16-bit elements: lane i of 16 passes the address of 4 elements of row i / 4 (columns 4 (i % 4) ...) of a
+// [4][16] tile in LDS and gets column i of the four rows
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u32x2 read_tr(const char *lds)
+{
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(lds)));
+}
+
 // 128-bit right shift by ds dwords and bs bits (registers only; identity for ds = bs = 0)
 __device__ __forceinline__ u32x4 shift_window(u32x4 wv, int ds, uint32_t bs)
 {

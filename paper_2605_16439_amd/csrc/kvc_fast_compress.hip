@@ -38,6 +38,7 @@ namespace kvc {
 namespace {
 
 using dd::drop_elems;
+using dd::read_tr;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -492,15 +493,6 @@ __global__ __launch_bounds__(64 * NW) void fk_compress(CPlan p, const uint16_t *
 }
 
 // ---- few workgroups: the contraction shared out over the wavefronts --------------------------------
-// transposed read of 16-bit elements: lane i of 16 passes the address of 4 elements of row i / 4 (columns 4 (i % 4) ...) of a
-// [4][16] tile and gets column i of the four rows
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ u32x2 read_tr(const char *lds)
-{
-    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (__attribute__((address_space(3))) s16x4 *)(lds)));
-}
-
 // fk_compress walks all positions of a block in steps, one barrier each; where the launch leaves compute units idle that chain
 // is its time (n = 729, m = 292, 12 blocks: 60 workgroups, 12 steps, 12.6 us).  Here a workgroup has MT tiles of 16 rows only
 // and its wavefronts take every NW-th step of 32 positions, each with a V tile of its own, two steps requested ahead and no

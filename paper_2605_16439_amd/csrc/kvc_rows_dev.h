@@ -11,14 +11,15 @@ using namespace dd;
 
 constexpr int kSW = 4;                // wavefronts
 constexpr int kSR = 32;               // rows per wavefront and step
-constexpr int kLDX = 24;              // 32-bit words per channel of the transposed value tile (16 row pairs; 96 bytes: no bank conflicts)
 constexpr int kLDO = D + 4;           // floats per head row of a wavefront's output in LDS
+constexpr int kWalkLds = 16 * kLDO * 4;       // a wavefront's LDS: its tile of 32 rows of values, then its output rows
+static_assert(kWalkLds >= kSR * D * 2 && kWalkLds % 256 == 0, "32 rows of 256 bytes, whole passes over the banks");
 
 // what walk() needs to know of a sequence's rows
 struct Rows {
     int I, m, KS, SV;                 // compressed rows: blocks of m rows, KS 32-row steps each, SV = I KS steps
     int t;                            // rows of the text cache
-    int cs, st;                       // steps per wavefront and run, at most; their distance
+    int cs, ws, st;                   // steps per wavefront and run, at most; distance between wavefronts' first steps; between steps
     unsigned qKS, qst;
     float scale;
 };
@@ -69,12 +70,12 @@ __device__ __forceinline__ u32x4 finite_elems(u32x4 v)
     return u32x4_mk(one(v.x), one(v.y), one(v.z), one(v.w));
 }
 
-// One wavefront's pass over its steps of a run: s0 + wave, then every p.st-th.  TEXT: rows of the text cache, else compressed
-// rows.  GUARD: infinities among the values stay infinities (see walk()).
-template <bool TEXT, bool GUARD>
+// One wavefront's pass over its steps of a run: s0 + wave p.ws, then every p.st-th.  TEXT: rows of the text cache, else compressed
+// rows.  GUARD: infinities among the values stay infinities (see walk()).  NB: steps in flight, 2 or (half the registers) 1.
+template <bool TEXT, bool GUARD, int NB>
 __device__ __forceinline__ void walk_once(const Rows &p, const uint16_t *__restrict__ Kb, const uint16_t *__restrict__ Vb,
                                      const uint16_t *__restrict__ kn, const uint16_t *__restrict__ vn, int t_new,
-                                     const u32x4 (&qf)[4], int s0, uint32_t *vt, float &m_run, float &l_run, f32x4 (&acc)[8])
+                                     const u32x4 (&qf)[4], int s0, char *vt, float &m_run, float &l_run, f32x4 (&acc)[8])
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r16 = lane & 15, kg = lane >> 4;
@@ -108,14 +109,12 @@ __device__ __forceinline__ void walk_once(const Rows &p, const uint16_t *__restr
             for (int k = 0; k < 4; ++k) kf[tt][k] = kp[4 * k];
         }
         if constexpr (TEXT) {
-            // rows base + 2 (kg + 4 k) + e, 16 lanes per row
+            // rows base + 4 k + kg, 16 lanes per row
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const int x = min(base + 2 * (kg + 4 * k) + e, last);
-                    vf[2 * k + e] = *(reinterpret_cast<const u32x4 *>(x == t_new ? vn : Vb + static_cast<size_t>(x) * D) + r16);
-                }
+            for (int k = 0; k < 8; ++k) {
+                const int x = min(base + 4 * k + kg, last);
+                vf[k] = *(reinterpret_cast<const u32x4 *>(x == t_new ? vn : Vb + static_cast<size_t>(x) * D) + r16);
+            }
         } else {
             // 8-row block 4 ks + kg of the record; the record's shorter last block [D][wt] is read as a dword-aligned
             // window around the lane's values (shifted into place in compute()), a block past it reads a valid one
@@ -138,16 +137,14 @@ __device__ __forceinline__ void walk_once(const Rows &p, const uint16_t *__restr
         if constexpr (TEXT) {
             if (GUARD && left < kSR) {                           // uniform, registers only: rows past the end are zeros
 #pragma unroll
-                for (int k = 0; k < 8; ++k) vf[k] = keep_elems(vf[k], 2 * (kg + 4 * (k >> 1)) + (k & 1) < left ? 8 : 0);
+                for (int k = 0; k < 8; ++k) vf[k] = keep_elems(vf[k], 4 * k + kg < left ? 8 : 0);
             }
+            // rows as they lie in memory, their 32-byte pieces at piece ^ (row bits 0, 1, 3): the transposed reads of 32 lanes
+            // below cover every bank once.  (Against pairs of rows packed into 32-bit words, 64 stores instead of 8: 6000 text
+            // rows, 16 (batch element, KV head) pairs, 18.7 -> 14.8 us per call.)
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t a = vf[2 * k][j], c2 = vf[2 * k + 1][j];
-                    vt[(8 * r16 + 2 * j) * kLDX + kg + 4 * k] = (a & 0xffffu) | (c2 << 16);
-                    vt[(8 * r16 + 2 * j + 1) * kLDX + kg + 4 * k] = (a >> 16) | (c2 & 0xffff0000u);
-                }
+            for (int k = 0; k < 8; ++k)
+                *reinterpret_cast<u32x4 *>(vt + 1024 * k + ((kg * 256 + r16 * 16) ^ ((kg | ((k & 2) << 1)) << 5))) = vf[k];
         }
         // logits of rows base + 8 kg + 4 tt + e for head r16
         float sc[8];
@@ -185,7 +182,9 @@ __device__ __forceinline__ void walk_once(const Rows &p, const uint16_t *__restr
         for (int ct = 0; ct < 8; ++ct) {
             u32x4 v;
             if constexpr (TEXT) {
-                v = *reinterpret_cast<const u32x4 *>(vt + (16 * ct + r16) * kLDX + 4 * kg);
+                const char *x = vt + (8 * kg + (r16 >> 2)) * 256 + ((((r16 >> 2) | ((kg & 1) << 2)) ^ ct) << 5) + (r16 & 3) * 8;
+                const u32x2 a = read_tr(x), c2 = read_tr(x + 4 * 256);
+                v = u32x4_mk(a.x, a.y, c2.x, c2.y);
             } else {
                 v = vf[ct];
                 if (GUARD ? left < kSR : wt != 0 && ks == p.KS - 1) {        // uniform, registers only
@@ -207,11 +206,19 @@ __device__ __forceinline__ void walk_once(const Rows &p, const uint16_t *__restr
     // Two steps in flight in two register sets.  No step is requested that the run does not have: with runs of one or
     // two steps a request ahead of the end would double what the kernel reads.
     const int all = TEXT ? (p.t + kSR - 1) / kSR : p.SV;
-    const int ST = p.st, left_w = all - s0 - wave, N = left_w > 0 ? min(quot(left_w + ST - 1, p.qst), p.cs) : 0;
+    const int sw = s0 + wave * p.ws;
+    const int ST = p.st, left_w = all - sw, N = left_w > 0 ? min(quot(left_w + ST - 1, p.qst), p.cs) : 0;
     if (N == 0) return;
-    const int sw = s0 + wave;
-    u32x4 kA[2][4], vA[8], kB[2][4] = {}, vB[8] = {};
+    u32x4 kA[2][4], vA[8];
     load(sw, kA, vA);
+    if constexpr (NB == 1) {
+        for (int it = 0; it < N; ++it) {
+            compute(sw + ST * it, kA, vA);
+            if (it + 1 < N) load(sw + ST * (it + 1), kA, vA);
+        }
+        return;
+    }
+    u32x4 kB[2][4] = {}, vB[8] = {};
     if (N > 1) load(sw + ST, kB, vB);
     int it = 0;
     for (; it + 2 < N; it += 2) {
@@ -228,10 +235,10 @@ __device__ __forceinline__ void walk_once(const Rows &p, const uint16_t *__restr
 // channel) and the lower terms of the others make NaNs of infinities among the values.  Such values are not expected, so the
 // sums are looked at once, behind the pass, and where they hold a NaN the pass is repeated with the values guarded: guarding
 // every step costs 5 %, the look 1.5 % (B = 16, 32/8 heads, 5 blocks of m = 231, 256 text rows: 23.9, 25.1 and 24.2 us).
-template <bool TEXT>
+template <bool TEXT, int NB = 2>
 __device__ __forceinline__ void walk(const Rows &p, const uint16_t *__restrict__ Kb, const uint16_t *__restrict__ Vb,
                                      const uint16_t *__restrict__ kn, const uint16_t *__restrict__ vn, int t_new,
-                                     const u32x4 (&qf)[4], int s0, uint32_t *vt, float &m_run, float &l_run, f32x4 (&acc)[8])
+                                     const u32x4 (&qf)[4], int s0, char *vt, float &m_run, float &l_run, f32x4 (&acc)[8])
 {
     auto start = [&]() {
         m_run = -INFINITY;
@@ -240,45 +247,47 @@ __device__ __forceinline__ void walk(const Rows &p, const uint16_t *__restrict__
         for (int ct = 0; ct < 8; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
     start();
-    walk_once<TEXT, false>(p, Kb, Vb, kn, vn, t_new, qf, s0, vt, m_run, l_run, acc);
+    walk_once<TEXT, false, NB>(p, Kb, Vb, kn, vn, t_new, qf, s0, vt, m_run, l_run, acc);
     f32x4 sum = acc[0];
 #pragma unroll
     for (int ct = 1; ct < 8; ++ct) sum += acc[ct];
     const float x = (sum[0] + sum[1]) + (sum[2] + sum[3]);
     if (__any(x != x)) {
         start();
-        walk_once<TEXT, true>(p, Kb, Vb, kn, vn, t_new, qf, s0, vt, m_run, l_run, acc);
+        walk_once<TEXT, true, NB>(p, Kb, Vb, kn, vn, t_new, qf, s0, vt, m_run, l_run, acc);
     }
 }
 
-// The kSW wavefronts of a run merge into one part record: [G][D] un-normalised output, [G] maxima, [G] sums.
-// Every thread of the workgroup calls this; those beyond the kSW wavefronts only meet the barrier.
-__device__ __forceinline__ void merge_waves(uint32_t (*sVt)[D * kLDX], float (*sM)[16], float (*sL)[16], float m_run, float l_run,
+// The NW wavefronts of a run merge into one part record: [G][D] un-normalised output, [G] maxima, [G] sums.  sVt: kWalkLds bytes
+// per wavefront.  Every thread of the workgroup calls this; those beyond the NW wavefronts only meet the barrier.
+template <int NW>
+__device__ __forceinline__ void merge_waves(char *sVt, float (*sM)[16], float (*sL)[16], float m_run, float l_run,
                                             const f32x4 (&acc)[8], int G, float *yp)
 {
-    static_assert(D * kLDX >= 16 * kLDO, "a wavefront's output rows reuse its value tile");
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r16 = lane & 15, kg = lane >> 4;
-    if (wave < kSW) {
+    if (wave < NW) {
         l_run += __shfl_xor(l_run, 16, 64);
         l_run += __shfl_xor(l_run, 32, 64);
-        float *fo = reinterpret_cast<float *>(sVt[wave]);         // [16 heads][kLDO]
+        float *fo = reinterpret_cast<float *>(sVt + wave * kWalkLds);     // [16 heads][kLDO]
 #pragma unroll
         for (int ct = 0; ct < 8; ++ct) *reinterpret_cast<f32x4 *>(fo + r16 * kLDO + 16 * ct + 4 * kg) = acc[ct];
         if (kg == 0) { sM[wave][r16] = m_run; sL[wave][r16] = l_run; }
     }
     __syncthreads();
-    if (wave >= kSW) return;
-    for (int idx = threadIdx.x; idx < G * (D / 4); idx += 64 * kSW) {
+    if (wave >= NW) return;
+    for (int idx = threadIdx.x; idx < G * (D / 4); idx += 64 * NW) {
         const int g = idx / (D / 4), c4 = (idx - g * (D / 4)) * 4;
-        const float M = fmaxf(fmaxf(sM[0][g], sM[1][g]), fmaxf(sM[2][g], sM[3][g]));
+        float M = sM[0][g];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) M = fmaxf(M, sM[w][g]);
         const float mref = M == -INFINITY ? 0.f : M;
         f32x4 y = {0.f, 0.f, 0.f, 0.f};
         float l = 0.f;
 #pragma unroll
-        for (int w = 0; w < kSW; ++w) {
+        for (int w = 0; w < NW; ++w) {
             const float a = __expf(sM[w][g] - mref);
-            const f32x4 o = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(sVt[w]) + g * kLDO + c4);
+            const f32x4 o = *reinterpret_cast<const f32x4 *>(reinterpret_cast<const float *>(sVt + w * kWalkLds) + g * kLDO + c4);
             y[0] += a * o[0]; y[1] += a * o[1]; y[2] += a * o[2]; y[3] += a * o[3];
             l += a * sL[w][g];
         }

@@ -11,15 +11,16 @@
 // stored as 16-byte pieces of 8 consecutive rows of one channel, which is the operand of P V when a lane holds
 // the probabilities of 8 consecutive rows -- so the rows of a score tile are numbered such that it does (tile tt
 // of a step, row i: key row 8 (i / 4) + 4 tt + i % 4), and values go from memory into the matrix cores without
-// LDS.  Text values are row-major and are transposed through a wavefront-private LDS tile.
+// LDS.  Text values are row-major and are transposed by the reads of a wavefront-private LDS tile.
 //
 // The weights are not rounded to bf16: p = p1 + p2 + p3 with three bf16 terms (24 bits, what a float holds), one
 // matrix instruction each; the matrix cores idle otherwise (32 instructions of 16 cycles per 16 KB and
 // wavefront: 20 times the rate at which memory delivers).
 //
 // Headline capsule (B = 4, 28 / 4 heads, 8 blocks of m = 410, 513 text rows, 31 MB): 595 us on the scalar
-// kernels (output kernel 472 us: a workgroup per query head), 12.4 us here -- this kernel 9 to 10 us, the merge 2 to 3
-// (15.0 us while every wavefront also requested the step behind its run; runs of two steps instead of one 13.3).
+// kernels (output kernel 472 us: a workgroup per query head), 11.0 us here -- this kernel 8 to 9 us, the merge 2 to 3
+// (15.0 us while every wavefront also requested the step behind its run; runs of two steps instead of one 13.3; 12.0 while the
+// text values were packed into pairs of rows on their way to LDS).
 #include "kvc_rows_dev.h"
 
 #include <algorithm>
@@ -43,7 +44,7 @@ __global__ __launch_bounds__(64 * kSW, 2) void static_split(const uint16_t *__re
                                                          uint16_t *__restrict__ Vt, const uint16_t *__restrict__ k_new,
                                                          const uint16_t *__restrict__ v_new, StPlan p)
 {
-    __shared__ __align__(16) uint32_t sVt[kSW][D * kLDX];
+    __shared__ __align__(256) char sVt[kSW * kWalkLds];
     __shared__ float sM[kSW][16], sL[kSW][16];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r16 = lane & 15, kg = lane >> 4;
@@ -68,12 +69,12 @@ __global__ __launch_bounds__(64 * kSW, 2) void static_split(const uint16_t *__re
     const bool text = pt >= p.NV;
     const int s0 = (text ? pt - p.NV : pt) * p.cs * kSW;
     if (text)
-        walk<true>(p, Ktb, Vtb, kn, vn, fresh ? p.t_in : -1, qf, s0, sVt[wave], m_run, l_run, acc);
+        walk<true>(p, Ktb, Vtb, kn, vn, fresh ? p.t_in : -1, qf, s0, sVt + wave * kWalkLds, m_run, l_run, acc);
     else
         walk<false>(p, Kc + static_cast<size_t>(bh) * p.I * p.m * D, Vc + static_cast<size_t>(bh) * p.I * p.m * D, kn, vn, -1, qf, s0,
-                    sVt[wave], m_run, l_run, acc);
+                    sVt + wave * kWalkLds, m_run, l_run, acc);
 
-    merge_waves(sVt, sM, sL, m_run, l_run, acc, p.G, p.Ypart + (static_cast<size_t>(bh) * p.NP + pt) * p.rec);
+    merge_waves<kSW>(sVt, sM, sL, m_run, l_run, acc, p.G, p.Ypart + (static_cast<size_t>(bh) * p.NP + pt) * p.rec);
     // the cache grows as in the backbone: the run that owns row t_in stores the new token
     if (fresh && text && p.t_in >= kSR * s0 && p.t_in < kSR * (s0 + kSW * p.cs) && threadIdx.x < 32) {
         const int half = threadIdx.x >> 4, piece = threadIdx.x & 15;
@@ -101,7 +102,7 @@ bool make_st_plan(StPlan &p, const kvc_shape &s, int t, int t_in, int cap)
     p.NV = (wv + p.cs - 1) / p.cs;
     p.NP = p.NV + (wt + p.cs - 1) / p.cs;
     p.rec = static_cast<int>(align_up(p.G * D + 2 * p.G, 4));
-    p.st = kSW; p.qst = quot_multiplier(kSW);
+    p.ws = 1; p.st = kSW; p.qst = quot_multiplier(kSW);
     p.qNP = quot_multiplier(p.NP); p.qHkv = quot_multiplier(p.Hkv); p.qKS = quot_multiplier(p.KS);
     // quot(): dividends below 2^32 / divisor
     return p.NP > 0 && bh * p.NP * std::max(p.NP, p.Hkv) < (1ll << 32) && static_cast<long>(p.SV) * p.KS < (1ll << 32);
