@@ -76,6 +76,11 @@ void kvc_dev_stream_decode(int32_t mode);
 /* Decode calls the one-pass kernel has served since the library was loaded (host-side count). */
 int64_t kvc_dev_stream_calls(void);
 
+/* The kernel with resident parameters (n = 256): -1 built-in rule, 0 never, 1 wherever an instance exists; and the decode calls
+ * it has served (host-side count). */
+void kvc_dev_resident_decode(int32_t mode);
+int64_t kvc_dev_resident_calls(void);
+
 /* Decode calls that the one-pass kernel for other block lengths and for small calls has served (host-side count). */
 int64_t kvc_dev_any_calls(void);
 

@@ -12,7 +12,7 @@ LIB = os.path.join(HERE, "libkvcapsule.so")
 CALL = os.path.join(HERE, "_kvc_call.so")      # extension module of the Python binding, host code only
 SOURCES = ["kvc_api.hip", "kvc_generic.hip", "kvc_fast_decode.hip", "kvc_fast_compress.hip",
            "kvc_full_decode.hip", "kvc_stream_decode.hip", "kvc_static_decode.hip",
-           "kvc_any_decode.hip", "kvc_float.hip"]
+           "kvc_any_decode.hip", "kvc_resident_decode.hip", "kvc_float.hip"]
 # packed-fp32 code generation is switched off on purpose: some packed forms have given
 # wrong results on this hardware, so the compiler must not emit them
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",

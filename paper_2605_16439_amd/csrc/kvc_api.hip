@@ -142,12 +142,14 @@ size_t least_decode_ws_bytes(const kvc_shape &s, int32_t max_text)
 kvc_status dispatch_decode(const DecodeCall &c)
 {
     kvc_status st = KVC_OK;
+    if (!resident_decode_default() && resident_decode(c, &st)) return st;       // developer knob
     // small calls with packed parameters: one latency-bound pass, with float32 weights, instead of three or four launches
     // (small_call in kvc_any_decode.hip); with plain parameters, or a workspace that the shape's other kernels may refuse,
     // these shapes stay on the tuned kernels
     if (c.theta_packed && c.U_packed && fast_decode_default() && c.ws_bytes >= least_decode_ws_bytes(c.s, c.cap) && any_decode(c, &st, true))
         return st;
     if (stream_decode(c, &st)) return st;
+    if (fast_decode_default() && resident_decode(c, &st)) return st;
     if (fast_decode_supported(c.s)) return fast_decode(c);
     return other_decode(c);
 }
@@ -519,6 +521,10 @@ void kvc_dev_stream_decode(int32_t mode) { stream_decode_knob(mode); }
 int64_t kvc_dev_stream_calls(void) { return stream_decode_calls(); }
 
 int64_t kvc_dev_any_calls(void) { return any_decode_calls(); }
+
+void kvc_dev_resident_decode(int32_t mode) { resident_decode_knob(mode); }
+
+int64_t kvc_dev_resident_calls(void) { return resident_decode_calls(); }
 
 int32_t kvc_dev_decode_plan(const kvc_shape *shape, int32_t text_len, int32_t text_cap, int32_t kernel, int32_t plan[8])
 {

@@ -172,6 +172,11 @@ bool any_decode_supported(const kvc_shape &s);
 size_t any_decode_ws_bytes(const kvc_shape &s, int32_t max_text);
 // (small_only: only where the tuned kernels of the shape would take longer, which needs the packed parameters)
 bool any_decode(const DecodeCall &c, kvc_status *st, bool small_only);
+// decode with resident parameters (bf16, head_dim 128, n = 256, packed parameters): true when the call was taken
+bool resident_decode(const DecodeCall &c, kvc_status *st);
+void resident_decode_knob(int mode);
+bool resident_decode_default();
+long resident_decode_calls();
 bool any_decode_plan(const kvc_shape &s, int t, int cap, int32_t *plan);
 long any_decode_calls();
 bool fast_decode_default();                          // no developer knob of the tuned kernels is set

@@ -41,7 +41,7 @@ EXPORTS = [
     "kvc_capsule_value_offset", "kvc_unpack_values",
     "kvc_reconstruct_attend_decode_ragged", "kvc_mlp_hidden", "kvc_static_attend_decode",
     "kvc_pack_theta", "kvc_pack_u", "kvc_dev_stream_decode", "kvc_dev_stream_calls",
-    "kvc_dev_any_calls", "kvc_dev_decode_plan",
+    "kvc_dev_any_calls", "kvc_dev_decode_plan", "kvc_dev_resident_decode", "kvc_dev_resident_calls",
 ]
 
 
@@ -149,6 +149,10 @@ def lib() -> ctypes.CDLL:
         L.kvc_dev_stream_calls.argtypes = []
         L.kvc_dev_any_calls.restype = i64
         L.kvc_dev_any_calls.argtypes = []
+        L.kvc_dev_resident_decode.restype = None
+        L.kvc_dev_resident_decode.argtypes = [i32]
+        L.kvc_dev_resident_calls.restype = i64
+        L.kvc_dev_resident_calls.argtypes = []
         L.kvc_dev_decode_plan.restype = i32
         L.kvc_dev_decode_plan.argtypes = [ctypes.POINTER(KvcShape), i32, i32, i32, ctypes.POINTER(i32)]
         L.kvc_capsule_value_offset.restype = i64
