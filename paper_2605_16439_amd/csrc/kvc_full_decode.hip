@@ -24,24 +24,21 @@
 // instead of 245, one wavefront per SIMD, and calls of more than one workgroup per CU lose by it (us per call, this loop
 // against that: B = 16, 32 / 32 heads, 1001 rows 51.0 / 54.7, 3137 rows 144.1 / 148.7; B = 12, 2001 rows 72.0 / 77.7;
 // the first shape 18.7 / 19.4).
-#include "kvc_internal.h"
+#include "kvc_decode_dev.h"
 
 #include <algorithm>
 
 namespace kvc {
+
+using namespace dd;
+
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
-constexpr int D = 128;            // head_dim of this path
 constexpr int kRW = 32;           // cache rows per wave and step (one k-step of the second product)
 constexpr int kWaves = 4;
 constexpr int kStep = kRW * kWaves;   // rows per workgroup and step
-constexpr int kLDW = 18;          // 32-bit words per channel of the transposed value tile: 16 row pairs + 2
 constexpr int kLDF = D + 4;       // floats per head row of a wave's output in LDS
+constexpr int kTileBytes = 16 * kLDF * 4;     // a wave's LDS: 32 value rows, then its output rows
 constexpr int kMaxSplits = 64;    // the finalize kernel keeps one part per lane
 
 struct FullPlan {
@@ -52,16 +49,12 @@ struct FullPlan {
     float *Ypart;
 };
 
-__device__ inline int quot(int x, unsigned q) { return q ? static_cast<int>(__umulhi(static_cast<unsigned>(x), q)) : x; }
-inline unsigned quot_multiplier(int d) { return d > 1 ? static_cast<unsigned>((1ull << 32) / static_cast<unsigned>(d)) + 1u : 0u; }
-__device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
-
 __global__ __launch_bounds__(64 * kWaves) void full_split(const uint16_t *__restrict__ q, uint16_t *__restrict__ K,
                                                            uint16_t *__restrict__ V, const uint16_t *__restrict__ k_new,
                                                            const uint16_t *__restrict__ v_new, FullPlan p)
 {
-    static_assert(D * kLDW >= 16 * kLDF, "a wave's output rows reuse its value tile");
-    __shared__ __align__(16) uint32_t sVt[kWaves][D * kLDW];
+    static_assert(kTileBytes >= 16 * kLDF * 4 && kTileBytes >= kRW * D * 2, "a wave's output rows reuse its value tile");
+    __shared__ __align__(256) char sVt[kWaves][kTileBytes];
     __shared__ float sM[kWaves][16], sL[kWaves][16];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r16 = lane & 15, kg = lane >> 4;
@@ -74,7 +67,7 @@ __global__ __launch_bounds__(64 * kWaves) void full_split(const uint16_t *__rest
     const uint16_t *kn = k_new + static_cast<size_t>(bh) * D, *vn = v_new + static_cast<size_t>(bh) * D;
 
     // rows of one step: key rows as MFMA A operands (lane = row r16 of a 16-row tile, 16 bytes of
-    // each 64-byte k-step), value rows coalesced (16 lanes per row, a lane takes a pair of rows).
+    // each 64-byte k-step), value rows coalesced (16 lanes per row).
     // No test around a load: rows beyond the split are clamped to its last row.
     auto load_tile = [&](int it, u32x4 (&kf)[2][4], u32x4 (&vf)[4][2]) {
         const int r0 = lo + kStep * it + kRW * wave;
@@ -90,7 +83,7 @@ __global__ __launch_bounds__(64 * kWaves) void full_split(const uint16_t *__rest
         for (int k = 0; k < 4; ++k)
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
-                const int x = min(r0 + 2 * (kg + 4 * k) + e, hi - 1);
+                const int x = min(r0 + 4 * (2 * k + e) + kg, hi - 1);
                 const uint16_t *vrow = (fresh && x == p.t_in) ? vn : Vb + x * p.ss;
                 vf[k][e] = *(reinterpret_cast<const u32x4 *>(vrow) + r16);
             }
@@ -113,21 +106,17 @@ __global__ __launch_bounds__(64 * kWaves) void full_split(const uint16_t *__rest
     f32x4 acc[D / 16];
 #pragma unroll
     for (int ct = 0; ct < D / 16; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-    uint32_t *vt = sVt[wave];
+    char *vt = sVt[wave];
 
     auto compute = [&](int it, const u32x4 (&kf)[2][4], const u32x4 (&vf)[4][2]) {
         const int r0 = lo + kStep * it + kRW * wave;
-        // value rows -> LDS, transposed: rows (2 pair, 2 pair + 1) of a channel share one word
+        // value rows -> LDS as they lie in memory, the 32-byte pieces of row x at piece ^ (x % 8): the transposed reads of 32
+        // lanes below cover every bank once
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int pair = kg + 4 * k;
+        for (int k = 0; k < 4; ++k)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t a = vf[k][0][j], c2 = vf[k][1][j];
-                vt[(8 * r16 + 2 * j) * kLDW + pair] = (a & 0xffffu) | (c2 << 16);
-                vt[(8 * r16 + 2 * j + 1) * kLDW + pair] = (a >> 16) | (c2 & 0xffff0000u);
-            }
-        }
+            for (int e = 0; e < 2; ++e)
+                *reinterpret_cast<u32x4 *>(vt + 1024 * (2 * k + e) + ((kg * 256 + r16 * 16) ^ ((kg | 4 * e) << 5))) = vf[k][e];
         // logits of rows r0 + 16 tt + 4 kg + e for head r16
         float sc[2][4];
 #pragma unroll
@@ -165,8 +154,8 @@ __global__ __launch_bounds__(64 * kWaves) void full_split(const uint16_t *__rest
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int ct = 0; ct < D / 16; ++ct) {
-            const uint32_t *vr = vt + (16 * ct + r16) * kLDW + 2 * kg;
-            const u32x2 v0 = *reinterpret_cast<const u32x2 *>(vr), v1 = *reinterpret_cast<const u32x2 *>(vr + 8);
+            const char *vr = vt + (((4 * kg + (r16 >> 2)) * 256 + (r16 & 3) * 8) ^ ((((4 * kg + (r16 >> 2)) & 7) ^ ct) << 5));
+            const u32x2 v0 = read_tr(vr), v1 = read_tr(vr + 16 * 256);
             f32x4 o = acc[ct];
             o[0] *= alpha; o[1] *= alpha; o[2] *= alpha; o[3] *= alpha;
             acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(u32x4{v0[0], v0[1], v1[0], v1[1]}), pfrag, o, 0, 0, 0);
