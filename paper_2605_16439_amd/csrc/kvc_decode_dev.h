@@ -25,7 +25,6 @@ constexpr int kJC = 64;         // capsule rows per fc_fused workgroup (one 16-r
 constexpr int kXC = 128;        // text rows per fa_scores text workgroup
 constexpr int kMaxParts = 256;  // fd_finalize keeps one scale per part in LDS
 constexpr int kSWLD = kXC + 8;  // padded row (bf16) of the text probabilities in LDS
-constexpr int kLDV = kXC + 8;   // padded row (bf16) of the transposed text values in LDS
 constexpr int kWLD = kJC + 8;   // padded row (bf16) of the W tile in LDS
 constexpr size_t kLdsBudget = 150 * 1024;
 constexpr int kCtrStride = 16;  // 64-bit words per arrival counter: one counter per 128-byte line
@@ -132,10 +131,9 @@ __host__ __device__ inline f32x2 f32x2_mk(float a, float b) { return f32x2{a, b}
 __device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 __device__ inline float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ inline float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-// element (channel c, row x) of the transposed text-value tile; the 16-byte chunks of a channel
-// row are XOR-swizzled with the index of the channel's 16-row MFMA tile: the transposing stores
-// spread over the banks and the operand reads of one tile stay conflict-free
-__device__ inline int vt_index(int c, int x) { return c * kLDV + ((((x >> 3) ^ (c >> 4)) & (kXC / 8 - 1)) << 3) + (x & 7); }
+// byte of 16-byte piece pc of row x in a tile of 256-byte value rows that is read transposed: the 32-byte pieces at
+// piece ^ (row bits 0, 1, 3), with which the reads of 32 lanes (rows 8 kg + 0..3 of two kg) cover every bank once
+__device__ inline int vt_byte(int x, int pc) { return (x * 256 + pc * 16) ^ (((x & 3) | ((x >> 1) & 4)) << 5); }
 
 // transposed read of 16-bit elements: lane i of 16 passes the address of 4 elements of row i / 4 (columns 4 (i % 4) ...) of a
 // [4][16] tile in LDS and gets column i of the four rows
@@ -175,7 +173,7 @@ __device__ inline bool row_valid(const Plan &p, int r) { return (r & 63) < p.RV 
 // fa_scores when there are no vision tokens.
 // Part record in Ypart: [G][D] floats of un-normalised output, [G] maxima, [G] sums.
 // ------------------------------------------------------------------------------------------
-constexpr size_t kTextLds = (16 * kSWLD + D * kLDV) * sizeof(uint16_t) + 2 * 4 * 16 * sizeof(float);
+constexpr size_t kTextLds = (16 * kSWLD + D * kXC) * sizeof(uint16_t) + 2 * 4 * 16 * sizeof(float);
 
 // GT: the group size, or 0 to take it from the plan.  RAG: per-sequence text lengths (ragged batch).  tid: the thread's index within the four waves
 // that work on this chunk (a workgroup of eight waves runs two chunks side by side, each half with
@@ -194,8 +192,8 @@ __device__ __forceinline__ void text_part(const Plan &p, const uint16_t *__restr
     const int r16 = lane & 15, kg = lane >> 4;
     // ---------------- text rows: one chunk of kXC rows of one (batch, KV head) ----------------
     uint16_t (*sWb)[kSWLD] = reinterpret_cast<uint16_t (*)[kSWLD]>(lds);               // probabilities [head][row], bf16
-    uint16_t *sVt = lds + 16 * kSWLD;                                                  // V^T [channel][row]
-    float (*sRed)[4][16] = reinterpret_cast<float (*)[4][16]>(lds + 16 * kSWLD + D * kLDV);   // per-wave maxima / sums per head
+    char *sV = reinterpret_cast<char *>(lds + 16 * kSWLD);                             // V rows, see vt_byte()
+    float (*sRed)[4][16] = reinterpret_cast<float (*)[4][16]>(lds + 16 * kSWLD + D * kXC);    // per-wave maxima / sums per head
     const int bh = quot(id, p.qNXC), xc = id - bh * p.NXC;
     const int b = quot(bh, p.qHkv), h = bh - b * p.Hkv;
     const bool fresh = k_new != nullptr;                       // row t_in comes from k_new / v_new
@@ -210,15 +208,14 @@ __device__ __forceinline__ void text_part(const Plan &p, const uint16_t *__restr
     // a chunk beyond the sequence's rows keeps lo = hi: every load is clamped to a valid row, every logit masked
     const int lo = xc * kXC, hi = max(min(t, lo + kXC), lo);
     const int xlast = max(min(hi, t) - 1, 0);                 // the last row the chunk (or, if it is empty, the sequence) has
-    // value rows of the chunk (16 lanes per row, a lane takes pairs of consecutive rows) and key
-    // rows of this wave's two 16-row tiles
+    // value rows of the chunk (16 lanes per row) and key rows of this wave's two 16-row tiles
     const int rowl = wave * 4 + kg, cs = r16;
     u32x4 vb[kXC / 32][2], kf[2][4], qf[4];
 #pragma unroll
     for (int it = 0; it < kXC / 32; ++it)
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-            const int x = min(lo + 2 * (rowl + 16 * it) + e, xlast);
+            const int x = min(lo + rowl + 32 * it + 16 * e, xlast);
             const uint16_t *vrow = (fresh && x == t_in) ? v_new + static_cast<size_t>(bh) * D
                                                           : Vt + (static_cast<size_t>(bh) * p.cap + x) * D;
             vb[it][e] = *(reinterpret_cast<const u32x4 *>(vrow) + cs);
@@ -255,18 +252,10 @@ __device__ __forceinline__ void text_part(const Plan &p, const uint16_t *__restr
     mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
     if (kg == 0) sRed[0][wave][r16] = mx;
-    // value rows -> LDS transposed: rows (x, x+1) of channel c share one 32-bit word
 #pragma unroll
-    for (int it = 0; it < kXC / 32; ++it) {
-        const int xl2 = 2 * (rowl + 16 * it);
-        const uint32_t a[4] = {vb[it][0].x, vb[it][0].y, vb[it][0].z, vb[it][0].w};
-        const uint32_t c2[4] = {vb[it][1].x, vb[it][1].y, vb[it][1].z, vb[it][1].w};
+    for (int it = 0; it < kXC / 32; ++it)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            *reinterpret_cast<uint32_t *>(sVt + vt_index(8 * cs + 2 * e, xl2)) = (a[e] & 0xffffu) | (c2[e] << 16);
-            *reinterpret_cast<uint32_t *>(sVt + vt_index(8 * cs + 2 * e + 1, xl2)) = (a[e] >> 16) | (c2[e] & 0xffff0000u);
-        }
-    }
+        for (int e = 0; e < 2; ++e) *reinterpret_cast<u32x4 *>(sV + vt_byte(rowl + 32 * it + 16 * e, cs)) = vb[it][e];
     __syncthreads();
     TS(0, 2);
     // probabilities relative to the chunk's own maximum, straight from the accumulator layout
@@ -296,7 +285,9 @@ __device__ __forceinline__ void text_part(const Plan &p, const uint16_t *__restr
         f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < kXC / 32; ++ks) {
-            const bf16x8 afrag = *reinterpret_cast<const bf16x8 *>(sVt + vt_index(16 * ct + r16, 32 * ks + 8 * kg));
+            const char *vr = sV + vt_byte(32 * ks + 8 * kg + (r16 >> 2), 2 * ct) + (r16 & 3) * 8;       // (rows + 4: the same bits)
+            const u32x2 v0 = read_tr(vr), v1 = read_tr(vr + 4 * 256);
+            const bf16x8 afrag = as_bf16x8(u32x4_mk(v0.x, v0.y, v1.x, v1.y));
             const bf16x8 bfrag = *reinterpret_cast<const bf16x8 *>(&sWb[r16][32 * ks + 8 * kg]);
             o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afrag, bfrag, o, 0, 0, 0);
         }
