@@ -13,7 +13,10 @@
 // Bound: at the sizes that run in fp32 (checks, calibration: one layer, a few sequences) launches and the latency of
 // the dependent phases; the scalar kernels that these replace spent it in serial loops over n or m with one load per
 // multiply-add, in 58 (projection) and 8 (output) workgroups.  One layer, B = 1, 8/2 heads, d = 64, n = 576, m = 231:
-// compression 244 -> 8 us, decode step about 80 us in six launches -> 20 us in two; both with their gaps 335 -> 25 us.
+// compression 244 -> 8 us, decode step about 80 us in six launches -> 14.5 us in two; both with their gaps 335 -> 24 us.  (What
+// gx_pass spends beyond latency is instructions: 64-bit addresses per load, moved in front of the loop over tiles, took 120
+// registers and 0.9 us more, d = 256 three.  The first share of every phase's loads requested at the start: no gain, and 1.6 us
+// lost at n = 9.)
 #include "kvc_decode_dev.h"
 
 #include <algorithm>
@@ -48,12 +51,18 @@ template <> struct Vec4<bf16_t> {
                         __uint_as_float(static_cast<uint32_t>(v[2]) << 16), __uint_as_float(static_cast<uint32_t>(v[3]) << 16));
     }
 };
+template <class T> using raw4 = typename Vec4<T>::raw;
+// element i of a matrix whose bytes 32 bits count: a scalar base and a 32-bit offset per lane
+template <class T> __device__ __forceinline__ const T *at(const T *base, uint32_t i)
+{
+    return reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + i * static_cast<uint32_t>(sizeof(T)));
+}
+template <class T> __device__ __forceinline__ raw4<T> load4_raw(const T *p) { return *reinterpret_cast<const raw4<T> *>(p); }
 template <class T> __device__ __forceinline__ f32x4 load4(const T *p) { return Vec4<T>::wide(*reinterpret_cast<const typename Vec4<T>::raw *>(p)); }
 // elements c .. c + 3 of a row of len >= 4: past the end zeros, and no load past the end
-template <class T> __device__ __forceinline__ f32x4 load4_in(const T *row, int c, int len)
+__device__ __forceinline__ f32x4 past_end(f32x4 v, int c, int len)
 {
-    const int c0 = min(c, len - 4), sh = c - c0;
-    const f32x4 v = load4(row + c0);
+    const int sh = c - min(c, len - 4);
     f32x4 r;
     r[0] = sh == 0 ? v[0] : sh == 1 ? v[1] : sh == 2 ? v[2] : sh == 3 ? v[3] : 0.f;
     r[1] = sh == 0 ? v[1] : sh == 1 ? v[2] : sh == 2 ? v[3] : 0.f;
@@ -61,6 +70,9 @@ template <class T> __device__ __forceinline__ f32x4 load4_in(const T *row, int c
     r[3] = sh == 0 ? v[3] : 0.f;
     return r;
 }
+template <class T> __device__ __forceinline__ f32x4 load4_in(const T *row, int c, int len) { return past_end(load4(row + min(c, len - 4)), c, len); }
+// LDS barrier that leaves loads from memory in flight
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 // acc += sum over e of A[., 4 kg + e] B[4 kg + e, .]: sixteen steps of the contraction
 __device__ __forceinline__ f32x4 mfma16(f32x4 a, f32x4 b, f32x4 acc)
 {
@@ -198,14 +210,20 @@ __global__ __launch_bounds__(64 * kXW) void gx_pass(const T *__restrict__ q, con
         qf[s4] = c < d ? v : f32x4{0.f, 0.f, 0.f, 0.f};
     }
     // scores of 16 key rows (lane: row r16, channels 16 s4 + 4 kg ...): D[row][head], unscaled
-    auto score = [&](const T *row) __attribute__((always_inline)) {
+    auto product = [&](const raw4<T> (&xr)[DT]) __attribute__((always_inline)) {
         f32x4 x[DT];
 #pragma unroll
-        for (int s4 = 0; s4 < DT; ++s4) x[s4] = load4(row + min(16 * s4 + 4 * kg, d - 4));
+        for (int s4 = 0; s4 < DT; ++s4) x[s4] = Vec4<T>::wide(xr[s4]);
         f32x4 a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s4 = 0; s4 < DT; ++s4) a = mfma16(x[s4], qf[s4], a);
         return a;
+    };
+    auto score = [&](const T *row) __attribute__((always_inline)) {
+        raw4<T> x[DT];
+#pragma unroll
+        for (int s4 = 0; s4 < DT; ++s4) x[s4] = load4_raw(row + min(16 * s4 + 4 * kg, d - 4));
+        return product(x);
     };
     // running maximum, sum and un-normalised output of row r16: image block r16 / G of a tile, or a text run's head r16
     float m_run = -INFINITY, l_run = 0.f;
@@ -301,41 +319,72 @@ __global__ __launch_bounds__(64 * kXW) void gx_pass(const T *__restrict__ q, con
             const int i0 = (ug * p.NUT + ut) * p.UP, nu = min(p.UP, n_img - i0);
             if (nu <= 0) break;                           // the same for the whole workgroup
             const T *kc_b = Kc + (static_cast<size_t>(bh) * p.I + i0) * m * d, *vc_b = Vc + (static_cast<size_t>(bh) * p.I + i0) * m * d;
-            // ---- step 1: S = q Kc^T
-            for (int it = wave; it < nu * TT; it += kXW) {
-                const int u = quot(it, p.qT), jt = it - u * TT, j = 16 * jt + 4 * kg;
-                f32x4 a = score(kc_b + (static_cast<size_t>(u) * m + min(16 * jt + r16, m - 1)) * d);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) a[e] = j + e < m ? a[e] : 0.f;
-                if (r16 < G) *reinterpret_cast<f32x4 *>(sS + (u * G + r16) * LDM + j) = a;
-            }
-            __syncthreads();
-            // ---- step 2: L^T[pos][row] = sum_j theta[j][pos] S[row][j]; wavefront: position tiles tg + 4 i, every other 32 rows j
-            const int tg = wave & 3, kh = wave >> 2;
-            f32x4 aL[NP];
-#pragma unroll
-            for (int i = 0; i < NP; ++i) aL[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            // (what follows depends on the lane, not on the tile: kept from being moved in front of the loop, where its
+            // addresses would take up registers throughout)
+            int lane_l = lane;
+            asm volatile("" : "+v"(lane_l));
+            const int r16 = lane_l & 15, kg = lane_l >> 4;
+            const int tg = wave & 3, kh = wave >> 2;      // step 2: position tiles tg + 4 i, every other 32 rows j
             int pos[NP];
 #pragma unroll
             for (int i = 0; i < NP; ++i) pos[i] = min(p0 + 16 * (tg + 4 * i) + r16, n - 1);
-            for (int k = kh; k < p.KB; k += 2) {
-                float x[8][NP];
+            auto load_tile = [&](int it, raw4<T> (&x)[DT]) __attribute__((always_inline)) {
+                const int u = quot(it, p.qT), jt = it - u * TT;
+                const T *base = kc_b + static_cast<size_t>(u) * m * d;
+#pragma unroll
+                for (int s4 = 0; s4 < DT; ++s4) x[s4] = load4_raw(at(base, static_cast<uint32_t>(min(16 * jt + r16, m - 1) * d + min(16 * s4 + 4 * kg, d - 4))));
+            };
+            auto load_theta = [&](int k, T (&x)[8][NP]) __attribute__((always_inline)) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
 #pragma unroll
-                    for (int i = 0; i < NP; ++i) x[e][i] = to_f(th_b[static_cast<size_t>(min(32 * k + 4 * e + kg, m - 1)) * n + pos[i]]);
+                    for (int i = 0; i < NP; ++i) x[e][i] = *at(th_b, static_cast<uint32_t>(min(32 * k + 4 * e + kg, m - 1) * n + pos[i]));
+            };
+            auto load_u = [&](int jt, raw4<T> (&x)[PS / 16]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int k = 0; k < PS / 16; ++k)
+                    x[k] = load4_raw(at(u_b, static_cast<uint32_t>(min(16 * jt + r16, m - 1) * n + min(p0 + 16 * k + 4 * kg, n - 4))));
+            };
+            const int sfull = m >> 4, send = (m + 15) >> 4;      // step 4: 16-row steps inside full 8-row blocks, all steps
+            auto value = [&](const T *rec, int k, int c) __attribute__((always_inline)) {
+                const int cc = min(16 * (ct4 + kXW * c) + r16, d - 1);
+                return at(rec, static_cast<uint32_t>((2 * k + (kg >> 1)) * 8 * d + cc * 8 + 4 * (kg & 1)));
+            };
+            // ---- step 1: S = q Kc^T
+            auto store_scores = [&](int it, f32x4 a) __attribute__((always_inline)) {
+                const int u = quot(it, p.qT), jt = it - u * TT, j = 16 * jt + 4 * kg;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[e] = j + e < m ? a[e] : 0.f;
+                if (r16 < G) *reinterpret_cast<f32x4 *>(sS + (u * G + r16) * LDM + j) = a;
+            };
+            for (int it = wave; it < nu * TT; it += kXW) {
+                raw4<T> x[DT];
+                load_tile(it, x);
+                store_scores(it, product(x));
+            }
+            lds_barrier();
+            // ---- step 2: L^T[pos][row] = sum_j theta[j][pos] S[row][j]
+            f32x4 aL[NP];
+#pragma unroll
+            for (int i = 0; i < NP; ++i) aL[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            auto theta_step = [&](int k, const T (&x)[8][NP]) __attribute__((always_inline)) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const float sv = sS[r16 * LDM + 32 * k + 4 * e + kg];
 #pragma unroll
-                    for (int i = 0; i < NP; ++i) aL[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e][i], sv, aL[i], 0, 0, 0);
+                    for (int i = 0; i < NP; ++i) aL[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(to_f(x[e][i]), sv, aL[i], 0, 0, 0);
                 }
+            };
+            for (int k = kh; k < p.KB; k += 2) {
+                T x[8][NP];
+                load_theta(k, x);
+                theta_step(k, x);
             }
             if (kh == 1) {
 #pragma unroll
                 for (int i = 0; i < NP; ++i) *reinterpret_cast<f32x4 *>(sX + ((tg + 4 * i) * 64 + lane) * 4) = aL[i];
             }
-            __syncthreads();
+            lds_barrier();
             float mx = -INFINITY;
             if (kh == 0) {
 #pragma unroll
@@ -351,7 +400,7 @@ __global__ __launch_bounds__(64 * kXW) void gx_pass(const T *__restrict__ q, con
                 mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
                 if (kg == 0) sRed[r16 * kXW + tg] = mx;
             }
-            __syncthreads();
+            lds_barrier();
             {
                 const f32x4 a = *reinterpret_cast<const f32x4 *>(sRed + r16 * kXW);
                 mx = fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));
@@ -371,47 +420,59 @@ __global__ __launch_bounds__(64 * kXW) void gx_pass(const T *__restrict__ q, con
                 sm += __shfl_xor(sm, 32, 64);
                 if (kg == 0) sRed[16 * kXW + r16 * kXW + tg] = sm;
             }
-            __syncthreads();
+            lds_barrier();
             float sm;
             {
                 const f32x4 a = *reinterpret_cast<const f32x4 *>(sRed + 16 * kXW + r16 * kXW);
                 sm = (a[0] + a[1]) + (a[2] + a[3]);
             }
             // ---- step 3: W^T[j][row] = sum_pos U[j][pos] P[row][pos]
-            for (int jt = wave; jt < TT; jt += kXW) {
-                const T *row = u_b + static_cast<size_t>(min(16 * jt + r16, m - 1)) * n;
+            auto u_tile = [&](int jt, const raw4<T> (&x)[PS / 16]) __attribute__((always_inline)) {
                 f32x4 a = {0.f, 0.f, 0.f, 0.f};
-                f32x4 x[PS / 16];
 #pragma unroll
-                for (int k = 0; k < PS / 16; ++k) x[k] = load4_in(row, p0 + 16 * k + 4 * kg, n);
-#pragma unroll
-                for (int k = 0; k < PS / 16; ++k) a = mfma16(x[k], *reinterpret_cast<const f32x4 *>(sP + r16 * LDP + 16 * k + 4 * kg), a);
+                for (int k = 0; k < PS / 16; ++k)
+                    a = mfma16(past_end(Vec4<T>::wide(x[k]), p0 + 16 * k + 4 * kg, n),
+                               *reinterpret_cast<const f32x4 *>(sP + r16 * LDP + 16 * k + 4 * kg), a);
                 const int j = 16 * jt + 4 * kg;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) a[e] = j + e < m ? a[e] : 0.f;
                 *reinterpret_cast<f32x4 *>(sS + r16 * LDM + j) = a;
+            };
+            for (int jt = wave; jt < TT; jt += kXW) {
+                raw4<T> x[PS / 16];
+                load_u(jt, x);
+                u_tile(jt, x);
             }
-            __syncthreads();
+            lds_barrier();
             // ---- step 4: Y^T[c][row] = sum_j Vc^T[c][j] W[row][j]; of a block's product the rows of that block are taken
             f32x4 o[CW], yu[CW];
 #pragma unroll
             for (int c = 0; c < CW; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-            const int sfull = m >> 4, send = (m + 15) >> 4;      // 16-row steps inside full 8-row blocks, all steps
             for (int u = 0; u < nu; ++u) {
                 const bool mine = r16 >= u * G && r16 < (u + 1) * G;
                 const T *rec = vc_b + static_cast<size_t>(u) * m * d;
                 auto weights = [&](int k) __attribute__((always_inline)) { return *reinterpret_cast<const f32x4 *>(sS + r16 * LDM + 16 * k + 4 * kg); };
 #pragma unroll
                 for (int c = 0; c < CW; ++c) yu[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-                // (unrolled: the loads of four steps together)
-#pragma unroll 4
-                for (int k = kh4; k < sfull; k += KH) {
+                int k = kh4;
+                // (four steps at a time: their loads together)
+                for (; k + 3 * KH < sfull; k += 4 * KH) {
+                    raw4<T> x[4][CW];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int c = 0; c < CW; ++c) x[r][c] = load4_raw(value(rec, k + KH * r, c));
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const f32x4 w = weights(k + KH * r);
+#pragma unroll
+                        for (int c = 0; c < CW; ++c) yu[c] = mfma16(Vec4<T>::wide(x[r][c]), w, yu[c]);
+                    }
+                }
+                for (; k < sfull; k += KH) {
                     const f32x4 w = weights(k);
 #pragma unroll
-                    for (int c = 0; c < CW; ++c) {
-                        const int cc = min(16 * (ct4 + kXW * c) + r16, d - 1);
-                        yu[c] = mfma16(load4(rec + static_cast<size_t>(2 * k + (kg >> 1)) * 8 * d + cc * 8 + 4 * (kg & 1)), w, yu[c]);
-                    }
+                    for (int c = 0; c < CW; ++c) yu[c] = mfma16(load4(value(rec, k, c)), w, yu[c]);
                 }
                 if (sfull < send && (KH == 1 || (sfull & 1) == kh4)) {
                     const f32x4 w = weights(sfull);
@@ -433,7 +494,7 @@ __global__ __launch_bounds__(64 * kXW) void gx_pass(const T *__restrict__ q, con
                     for (int e = 0; e < 4; ++e) o[c][e] = mine ? yu[c][e] : o[c][e];
             }
             if (r16 < nu * G) advance(mx, sm, o);         // rows of the tile that hold no image block keep their state
-            __syncthreads();                              // W and P have been read
+            lds_barrier();                              // W and P have been read
         }
     }
 
