@@ -49,6 +49,7 @@ struct GPlan {
     int NGR, chunk, nvis;             // (head, sequence, unit group) groups, groups per XCD, vision workgroups
     int NTX, NTC, nparts, rec;        // text runs per (batch element, KV head), those of a cache filled to its capacity:
                                       // run r takes the steps r, r + NTC, r + 2 NTC, ...
+    int own;                          // plain theta: the partial logits have LDS of their own
     int t, t_in, cap;
     unsigned qF, qBU, qNUG, qT, qNTX, qHkv, qKS, qNTC, qst;
     float scale;
@@ -134,16 +135,17 @@ __device__ __forceinline__ void pipe2(int N, Step step, Load load, u32x4 (&b0)[C
 
 // LDS of a vision workgroup: three planes of S (then W), three planes of P, staging tiles of the wavefronts (keys in
 // step 1; rows of U in step 3 where U is plain), row statistics.  Rows are 32 mod 64 bytes apart: operand reads
-// without bank conflicts.  Where theta is plain the partial logits of the wavefronts take the place of all of it
-// between step 2 and the softmax.
+// without bank conflicts.  Where theta is plain the partial logits of the wavefronts lie over the staging tiles between
+// step 2 and the softmax where the LDS has room for them behind S and P (GPlan::own: two barriers less), else over all of it.
 constexpr size_t kStage = kGW * 16 * D * 2;
 constexpr int kLDL = 132;             // floats per row of a wavefront's partial logits [16][128]
 constexpr size_t kPartial = kGW * 16 * kLDL * sizeof(float);
 __host__ __device__ constexpr size_t planes_p(int PS) { return static_cast<size_t>(3) * 16 * (PS + 16) * 2; }
-size_t pass_lds(int m, int PS, bool packed)
+size_t pass_lds(int m, int PS, bool packed, bool own)
 {
     const size_t s = 3 * 16 * (align_up(m, 32) + 16) * 2;
-    const size_t vis = std::max(s + planes_p(PS) + kStage, packed ? size_t(0) : kPartial) + 2 * 16 * kGW * sizeof(float);
+    const size_t vis = (own ? s + planes_p(PS) + kPartial : std::max(s + planes_p(PS) + kStage, packed ? size_t(0) : kPartial)) +
+                       2 * 16 * kGW * sizeof(float);
     const size_t txt = kSW * (kWalkLds + 2 * 16 * sizeof(float));
     return std::max(vis, txt);
 }
@@ -223,8 +225,9 @@ __global__ __launch_bounds__(64 * kGW) void ga_pass(const uint16_t *__restrict__
     uint16_t *sS = dyn, *sP = dyn + 3 * PLM;              // W takes the place of S
     char *sTile = reinterpret_cast<char *>(sP) + planes_p(PS) + wave * (16 * D * 2);     // this wavefront's staging tile
     // row statistics behind everything else: maxima, sums per wavefront [16][kGW] (packed), per row [16] (plain)
+    const uint32_t part_at = !PK && p.own ? static_cast<uint32_t>(3 * PLM * 2 + planes_p(PS)) : 0u;
     float *sRed = reinterpret_cast<float *>(reinterpret_cast<char *>(dyn) +
-                                            max(static_cast<size_t>(3) * PLM * 2 + planes_p(PS) + kStage, PK ? size_t(0) : kPartial));
+                                            max(static_cast<uint32_t>(3 * PLM * 2 + planes_p(PS) + kStage), PK ? 0u : static_cast<uint32_t>(part_at + kPartial)));
     int n_img = p.I;
     if constexpr (RAG) n_img = min(max(p.n_img[b], 0), p.I);
 
@@ -484,8 +487,8 @@ __global__ __launch_bounds__(64 * kGW) void ga_pass(const uint16_t *__restrict__
             TS(5, 2);
             if (NX > 0) load_u(0, ua0);
             if (NX > 1) load_u(1, ua1);
-            lds_barrier();                               // S and the staging tiles are free: partial logits in their place
-            float *sL = reinterpret_cast<float *>(dyn);
+            if (!p.own) lds_barrier();                   // uniform.  S has been read: partial logits in its place
+            float *sL = reinterpret_cast<float *>(reinterpret_cast<char *>(dyn) + part_at);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {                // lane: positions 8 (4 kg + e) + i of query row r16
                 float *dst = sL + (wave * 16 + r16) * kLDL + 8 * (4 * kg + e);
@@ -517,7 +520,7 @@ __global__ __launch_bounds__(64 * kGW) void ga_pass(const uint16_t *__restrict__
                 }
             rsm = half_reduce(rsm, [](float a, float b) { return a + b; });
             if ((threadIdx.x & 31) == 0) { sRed[row] = rmx; sRed[16 + row] = rsm; }
-            lds_barrier();                               // the partial logits have been read
+            if (!p.own) lds_barrier();                   // the partial logits have been read
 #pragma unroll
             for (int i = 0; i < NPW; ++i) store_planes(sP + row * LDP + 128 * i + pl, PLP, x[i]);
             lds_barrier();
@@ -668,10 +671,10 @@ bool make_gplan(GPlan &p, const kvc_shape &s, int t, int t_in, int cap)
     int ps = 128;
     p.UP = up_max;
     for (int w : {512, 256})
-        if (p.n > w / 2 && groups(up_max) * ((p.n + w - 1) / w) >= 256 && pass_lds(p.m, w, false) <= kPassLds) { ps = w; break; }
+        if (p.n > w / 2 && groups(up_max) * ((p.n + w - 1) / w) >= 256 && pass_lds(p.m, w, false, false) <= kPassLds) { ps = w; break; }
     p.PS = ps;
     p.F = (p.n + ps - 1) / ps;
-    if (p.F > kMaxVisParts || pass_lds(p.m, ps, false) > kPassLds) return false;
+    if (p.F > kMaxVisParts || pass_lds(p.m, ps, false, false) > kPassLds) return false;
     // (as many runs as give every one the same number of steps in a full cache: the chip is full of workgroups where the
     // text is long, and takes 12 runs of two steps in less time than 16 of one or two)
     auto steps = [](int rows) { return (rows + kTextStep - 1) / kTextStep; };
@@ -699,6 +702,8 @@ bool make_gplan(GPlan &p, const kvc_shape &s, int t, int t_in, int cap)
     p.qF = quot_multiplier(p.F); p.qBU = quot_multiplier(p.B * p.NUG); p.qNUG = quot_multiplier(p.NUG);
     p.qT = quot_multiplier(2 * p.KS); p.qNTX = quot_multiplier(p.NTX); p.qHkv = quot_multiplier(p.Hkv); p.qKS = quot_multiplier(p.KS);
     p.qNTC = quot_multiplier(p.NTC); p.qst = quot_multiplier(kSW * p.NTC);
+    // (the registers allow one workgroup per compute unit anyway: none is kept out by the LDS that this takes)
+    p.own = pass_lds(p.m, p.PS, false, true) <= kPassLds;
     p.n_img = p.tlen = nullptr;
     // quot(): dividends below 2^32 / divisor; 32-bit offsets into a head's theta and U
     const long lim = 1l << 31;
@@ -712,7 +717,7 @@ template <int NPW, bool PK, bool RAG> bool launch_g3(const GPlan &p, const Decod
     static bool attr_set[kMaxDevices] = {};
     if (!allow_lds(reinterpret_cast<const void *>(ga_pass<NPW, PK, RAG>), kPassLds, attr_set)) return false;
     const int grid = p.nvis + p.B * p.Hkv * p.NTX;
-    ga_pass<NPW, PK, RAG><<<grid, 64 * kGW, pass_lds(p.m, p.PS, PK), c.stream>>>(
+    ga_pass<NPW, PK, RAG><<<grid, 64 * kGW, pass_lds(p.m, p.PS, PK, !PK && p.own), c.stream>>>(
         static_cast<const uint16_t *>(c.q), static_cast<const uint16_t *>(c.Kc),
         static_cast<const uint16_t *>(PK ? c.theta_packed : c.theta), static_cast<const uint16_t *>(PK ? c.U_packed : c.U),
         static_cast<const uint16_t *>(c.Vc), static_cast<uint16_t *>(c.Kt), static_cast<uint16_t *>(c.Vt),
