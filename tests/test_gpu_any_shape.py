@@ -173,6 +173,17 @@ def test_decode_several_tiles_per_workgroup(hq, hkv, B, I, n, m, t, ps, tiles, p
     assert kv.lib().kvc_dev_any_calls() == calls + 1
 
 
+# Partial logits of plain parameters in LDS of their own up to m = 768, 640 and 384 (slices of 128, 256 and 512 positions), in the
+# place of the scores beyond: both sides of each line, and several tiles per workgroup on both sides
+@pytest.mark.parametrize("hq,hkv,B,I,n,m,ps,tiles", [
+    (4, 2, 1, 2, 1023, 768, 128, 1), (4, 2, 1, 2, 1023, 769, 128, 1), (7, 1, 1, 60, 1023, 769, 128, 5), (7, 1, 1, 60, 1023, 736, 128, 5),
+    (8, 8, 8, 2, 1023, 640, 256, 1), (8, 8, 8, 2, 1023, 641, 256, 1), (8, 8, 16, 2, 1023, 384, 512, 1), (8, 8, 16, 2, 1023, 385, 512, 1)])
+def test_decode_partial_logits_in_both_places(hq, hkv, B, I, n, m, ps, tiles):
+    plan = decode_plan(hq, hkv, B, I, n, m, 6, 6)
+    assert (plan[0], plan[2]) == (ps, tiles)
+    decode_case(wl(n, I, B=B, hq=hq, hkv=hkv, t=5), m)
+
+
 @pytest.mark.parametrize("hq,hkv,I,n,m,ni,ps,tiles", [
     (7, 1, 99, 136, 41, [1, 4, 99, 50, 0], 128, 3), (16, 1, 25, 304, 20, [25, 1, 0, 24, 13, 2], 256, 2), (16, 1, 25, 600, 33, [25, 1, 0, 24, 13, 2], 512, 2),
     (32, 8, 2, 304, 40, [2, 1, 0, 2] * 4, 256, 1), (8, 8, 3, 520, 40, [3, 0, 1, 2] * 8, 512, 1)])
