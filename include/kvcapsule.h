@@ -41,7 +41,9 @@
  *    two-layer key reconstructor for m >= 8; decode for 8 <= n <= 6144, m <= 1152 and G <= 16.  Decode kernels tuned
  *    further, with scores and weights rounded to bf16 between the steps, serve n in {256, 576, 1024}, G in
  *    {1, 2, 4, 6, 7, 8} and at most 256 partial results per (batch element, KV head), save small calls with packed
- *    parameters and a text_cap of at most 8192; every other decode keeps them at float32 precision.  fp32, bf16 with
+ *    parameters and a text_cap of at most 8192 (n = 256 with m <= 128, packed parameters, B H_kv I >= 64 and
+ *    text_cap <= 2 I m + 128 in one pass that keeps theta and U in registers, whatever the text's length); every other
+ *    decode keeps them at float32 precision.  fp32, bf16 with
  *    another d, and bf16 with d = 128 beyond those limits run compression (n >= 4) and decode (4 <= n <= 12288,
  *    m <= 1952, G <= 16) on the fp32 matrix instruction.  What is left runs shape-agnostic scalar kernels: same
  *    results within rounding, far lower speed; decode is limited to n <= 16384 (KVC_ERR_UNSUPPORTED beyond).

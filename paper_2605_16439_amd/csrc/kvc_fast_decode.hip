@@ -9,7 +9,7 @@
 //               one 16x16x32 MFMA tile per 16 key rows.
 //   text_part   (a device function, run by extra workgroups of fc_fused) handles 128 rows of the
 //               text cache completely: logits, exp relative to the chunk's own maximum,
-//               P V_text (V_text transposed through LDS), and writes a finished part record; the
+//               P V_text (V_text transposed by the reads from LDS), and writes a finished part record; the
 //               chunk that owns row text_len also stores the new token's k, v (Sec. 3.2: text KV
 //               is kept as it is).
 //   fb_probs    L = S theta (step 2) as a skinny GEMM per KV head, 64 (or 128) query rows x 64

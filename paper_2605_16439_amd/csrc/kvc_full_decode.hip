@@ -11,19 +11,19 @@
 //                  logits S = sigma K q^T by 16x16x32 MFMA with the key rows as A operand straight
 //                  from memory; P = exp(S - max) stays in registers and is the B operand of the
 //                  second product as it comes out of the first (the 32 rows of a step are numbered
-//                  the same way on both sides of the contraction); the value rows are transposed
-//                  through a wave-private LDS tile to become its A operand.  The next step's rows
+//                  the same way on both sides of the contraction); the value rows are transposed by the
+//                  reads from a wave-private LDS tile to become its A operand.  The next step's rows
 //                  are requested before the current step is multiplied.  The four waves merge
 //                  through LDS into one part record.
 //   finalize       the parts of a (batch element, query head) are merged by the finalize kernel of
 //                  the capsule path (a lane per part, shuffles only).
 //
 // Bound: HBM (2 B H_kv (S + 1) d 2 bytes are read once; 4 flop per byte).  B = 4, 28 / 4 heads, 8705 rows, 71 MB:
-// 23.3 us per call with 368 workgroups, 18.7 us (3.8 TB/s, the merge launch included) with one per CU
-// (groups_per_split).  Two workgroups fit a CU, and have to: requesting two steps before the loop takes 284 registers
-// instead of 245, one wavefront per SIMD, and calls of more than one workgroup per CU lose by it (us per call, this loop
-// against that: B = 16, 32 / 32 heads, 1001 rows 51.0 / 54.7, 3137 rows 144.1 / 148.7; B = 12, 2001 rows 72.0 / 77.7;
-// the first shape 18.7 / 19.4).
+// 23.3 us per call with 368 workgroups, 18.7 us with one per CU (groups_per_split), 18.3 us (3.9 TB/s, the merge launch
+// included) since the values are transposed by the LDS reads.  Two workgroups fit a CU, and have to: requesting two
+// steps before the loop takes 284 registers instead of 245, one wavefront per SIMD, and calls of more than one
+// workgroup per CU lose by it (us per call, this loop against that: B = 16, 32 / 32 heads, 1001 rows 51.0 / 54.7, 3137
+// rows 144.1 / 148.7; B = 12, 2001 rows 72.0 / 77.7; the first shape 18.7 / 19.4).
 #include "kvc_decode_dev.h"
 
 #include <algorithm>
