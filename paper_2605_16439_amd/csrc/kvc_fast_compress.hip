@@ -59,7 +59,7 @@ struct CPlan {
     int B, Hkv, n, I, m, vis0;
     int tiles, TPW, JT;         // 16-row tiles of U, tiles per workgroup, workgroups per image block
     int nproj;
-    int per_xcd;                // workgroups per XCD when they divide evenly over the 8 XCDs, else 0
+    int per_xcd;                // workgroups per XCD (fk_compress: when they divide evenly over the 8 XCDs, else 0)
     int act;                    // FORM 2: kvc_activation
     int64_t sb, sh, ss;
 #if defined(KVC_TIMELINE)
@@ -521,9 +521,11 @@ __global__ __launch_bounds__(64 * NW) void fk_split(CPlan p, const uint16_t *__r
     char *const sV = sdyn + wave * WB, *const sW = sV + kVT;
     float *const sA = reinterpret_cast<float *>(sdyn + NW * WB);             // row sums of U [NW][16 MT]
 
-    // an XCD takes a contiguous run of workgroups in (head, batch element, image block) order, as in fk_compress
-    const int bx = blockIdx.x;
-    const int wg = p.per_xcd ? (bx & 7) * p.per_xcd + (bx >> 3) : bx;
+    // an XCD takes a contiguous run of workgroups in (head, batch element, image block) order, as in fk_compress; the grid is
+    // eight runs, what of it lies behind the last workgroup ends here.  (Without runs where the number is no multiple of 8, a
+    // block's V in the L2 of several XCDs: 132 blocks, n = 256, m = 106 14.2 us; with them 9.7.)
+    const int wg = static_cast<int>(blockIdx.x & 7) * p.per_xcd + static_cast<int>(blockIdx.x >> 3);
+    if (wg >= p.nproj) return;
     const int lu = wg / p.JT, jt = wg - lu * p.JT;
     const int hb = lu / p.I, i = lu - hb * p.I;
     const int h = hb / p.B, b = hb - h * p.B;
@@ -698,7 +700,7 @@ bool launch_split(const CPlan &p, const uint16_t *K, const uint16_t *V, const in
     constexpr size_t lds = split_lds(NW, MT, FORM);
     static bool attr_set[kMaxDevices] = {};
     if (!allow_lds(reinterpret_cast<const void *>(fk_split<NW, MT, FORM>), lds, attr_set)) return false;
-    fk_split<NW, MT, FORM><<<p.nproj, 64 * NW, lds, stream>>>(p, K, V, idx, U, mu, Kc, Vc);
+    fk_split<NW, MT, FORM><<<8 * p.per_xcd, 64 * NW, lds, stream>>>(p, K, V, idx, U, mu, Kc, Vc);
     return true;
 }
 
@@ -772,8 +774,8 @@ static void share_tiles(CPlan &p)
 //     64 blocks, n = 70, m = 18 6.3 / 5.7 / 4.6 / 4.3;
 //   else a tile at a time where the rounds of fk_compress, whose workgroups pass over all positions in a row, take longer than
 //     the tiles that each read V: 3 or 0, by the times that fit the measurements (0.1 us; within 15 and 9 %) with a margin.
-//     384 blocks, n = 488, m = 73 24.1 / 22.5 (3); 160 blocks, n = 333, m = 139 17.3 / 15.0 (3); 88 blocks, n = 451, m = 207 13.7 (0) /
-//     16.3; 128 blocks, n = 1024, m = 410 28.5 (0) / 52.8.
+//     52 blocks, n = 256, m = 145 7.8 / 6.7 (3); 24 blocks, n = 1024, m = 325 13.7 / 11.4 (3); 132 blocks, n = 256, m = 106 9.1 (0) /
+//     9.7; 24 blocks, n = 576, m = 358 10.2 (0) / 10.4; 128 blocks, n = 1024, m = 410 28.5 (0) / 52.8.
 static int split_kind(const CPlan &p)
 {
     if (g_force_nw >= 1 && g_force_nw <= 3) return g_force_nw;
@@ -786,7 +788,7 @@ static int split_kind(const CPlan &p)
     const int resident = p.TPW > 8 ? 1 : 2, rounds = static_cast<int>((p.nproj + 256 * resident - 1) / (256 * resident));
     const double split = 24 + (4 + 7 * ((steps + 3) / 4)) * std::max(1.0, 0.64 * x) + 5 * x;
     const double whole = 20 + rounds * (19 + 6 * ((p.n + kKT - 1) / kKT) + 8 * p.TPW) * (1 + 0.8 * std::max(wgs / rounds - 1, 0.0));
-    return split <= 0.75 * whole ? 3 : 0;
+    return split <= 0.7 * whole ? 3 : 0;
 }
 
 template <int FORM> static bool split_compress(CPlan p, int kind, const uint16_t *K, const uint16_t *V, const int32_t *idx, const uint16_t *U,
@@ -794,7 +796,7 @@ template <int FORM> static bool split_compress(CPlan p, int kind, const uint16_t
 {
     p.JT = kind == 2 ? (p.tiles + 1) / 2 : p.tiles;
     p.nproj = p.B * p.Hkv * p.I * p.JT;
-    p.per_xcd = p.nproj % 8 == 0 ? p.nproj / 8 : 0;
+    p.per_xcd = (p.nproj + 7) / 8;
     switch (kind) {
     case 1: return launch_split<8, 1, FORM>(p, K, V, idx, U, mu, Kc, Vc, stream);
     case 2: return launch_split<8, 2, FORM>(p, K, V, idx, U, mu, Kc, Vc, stream);
